@@ -187,8 +187,8 @@ struct Quad {
 template <class T, int EPT>
 __global__ void __launch_bounds__(256)
 fit3_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, double* __restrict__ U,
-            double* __restrict__ mom_post, unsigned long long* __restrict__ counters, VGrid G,
-            typename Bits<T>::U* __restrict__ max_out) {
+            double* __restrict__ mom_post, unsigned long long* __restrict__ counters,
+            unsigned* __restrict__ clip_part, VGrid G, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
     T* blk = reinterpret_cast<T*>(smem_raw);
     __shared__ double red[21 * 4];
@@ -292,7 +292,7 @@ fit3_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, double* _
         double c[1] = {(double)nclip};
         block_sum<1>(c, red);
         if (threadIdx.x == 0) {
-            if (c[0] > 0) atomicAdd(&counters[0], (unsigned long long)c[0]);
+            clip_part[cell] = (unsigned)c[0];
             if (!ok) atomicAdd(&counters[1], 1ull);
         }
     }
@@ -972,63 +972,142 @@ hipError_t launch_moments1(const T* f, double* mom, long long cells, int nv, dou
     return hipGetLastError();
 }
 
-// counters[0] += sum of the per-block clip counts part[0..n), in two launches
-// like the maxima (launch_max_finalize): up to kFinStage blocks sum ranges
-// into a stage of 64-bit sums right after the partials, one wave adds the
-// stage to the counter.  Integer sums: exact in any order.
-__global__ void __launch_bounds__(256)
-count_stage_kernel(const unsigned* __restrict__ part, long long n, long long chunk,
-                   unsigned long long* __restrict__ out, int add) {
-    __shared__ unsigned long long red[256 / kWave];
+// The maxima and clip counts of the fits of a step (up to two species) from
+// their per-block partials, all in one launch: block (or block row) 2 s folds
+// species s's maxima into its slot, 2 s + 1 adds its clip counts to
+// counters[0].  Up to kFoldOne partials each: one 1024-thread block per fold
+// (at 32768 cells 4.6 us for both species, where two launches per fold took
+// 8 x 3-10 us); more: ranges into a stage of 64-bit entries right behind the
+// partials, then one wave per fold.  Counts are integers and the only
+// unordered additions are two atomic ones: exact in any order.
+template <class U>
+struct FitFold {
+    const U* part[VL_MAX_SPECIES];
+    U* slot[VL_MAX_SPECIES];                  // null: no maximum to fold
+    const unsigned* clips[VL_MAX_SPECIES];
+    unsigned long long* counters;             // null: no counts wanted
+    long long n;
+};
+
+__device__ __forceinline__ unsigned long long wave_count(unsigned long long acc) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+    return acc;
+}
+
+template <class U>
+__global__ void __launch_bounds__(1024) fit_fold_kernel(FitFold<U> F) {
+    const int s = blockIdx.x >> 1, n = (int)F.n;
+    if ((blockIdx.x & 1) == 0) {
+        if (F.slot[s]) fold_max_block<U>(F.part[s], n, F.slot[s]);
+        return;
+    }
+    if (!F.counters) return;
+    __shared__ unsigned long long red[1024 / kWave];
+    const unsigned* clips = F.clips[s];
+    const int tid = threadIdx.x;
+    typedef unsigned Vec __attribute__((ext_vector_type(4)));
+    const int nvec = ((uintptr_t)clips & 15u) ? 0 : n / 4;
+    unsigned long long acc = 0;
+#pragma unroll 8
+    for (int i = tid; i < nvec; i += 1024) {
+        const Vec v = reinterpret_cast<const Vec*>(clips)[i];
+        acc += (unsigned long long)v[0] + v[1] + v[2] + v[3];
+    }
+    for (int i = nvec * 4 + tid; i < n; i += 1024) acc += clips[i];
+    acc = wave_count(acc);
+    if ((tid & (kWave - 1)) == 0) red[tid / kWave] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < 1024 / kWave; ++w) acc += red[w];
+        if (acc) atomicAdd(F.counters, acc);
+    }
+}
+
+// First level for long partials: block x of row y folds its range into entry x
+// of the row's stage.
+template <class U>
+__global__ void __launch_bounds__(256) fit_stage_kernel(FitFold<U> F, long long chunk) {
+    const int s = blockIdx.y >> 1;
+    const bool count = (blockIdx.y & 1) != 0;
+    if (count ? !F.counters : !F.slot[s]) return;
     const long long lo = (long long)blockIdx.x * chunk;
-    const long long hi = lo + chunk < n ? lo + chunk : n;
+    const long long hi = lo + chunk < F.n ? lo + chunk : F.n;
+    __shared__ unsigned long long red[256 / kWave];
     unsigned long long acc = 0;
     for (long long b = lo; b < hi; b += 8 * 256) {
-        unsigned v[8];
+        unsigned long long v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const long long i = b + u * 256 + threadIdx.x;
-            v[u] = i < hi ? part[i] : 0u;
+            v[u] = i < hi ? (count ? (unsigned long long)F.clips[s][i] : (unsigned long long)F.part[s][i]) : 0ull;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
+        for (int u = 0; u < 8; ++u) acc = count ? acc + v[u] : (v[u] > acc ? v[u] : acc);
     }
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const unsigned long long y = __shfl_xor(acc, o, kWave);
+        acc = count ? acc + y : (y > acc ? y : acc);
+    }
     if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 256 / kWave; ++w) acc += red[w];
-        if (add)
-            out[0] += acc;
-        else
-            out[blockIdx.x] = acc;
+        for (int w = 1; w < 256 / kWave; ++w) acc = count ? acc + red[w] : (red[w] > acc ? red[w] : acc);
+        const void* part = count ? (const void*)F.clips[s] : (const void*)F.part[s];
+        auto* stage = (unsigned long long*)((char*)part + fin_stage(F.n, count ? sizeof(unsigned) : sizeof(U)));
+        stage[blockIdx.x] = acc;
     }
 }
 
-__global__ void __launch_bounds__(kWave)
-count_final_kernel(const unsigned long long* __restrict__ stage, int g, unsigned long long* __restrict__ counters) {
-    unsigned long long a = (int)threadIdx.x < g ? stage[threadIdx.x] : 0ull;
+template <class U>
+__global__ void __launch_bounds__(kWave) fit_final_kernel(FitFold<U> F, int g) {
+    const int s = blockIdx.x >> 1;
+    const bool count = (blockIdx.x & 1) != 0;
+    if (count ? !F.counters : !F.slot[s]) return;
+    const void* part = count ? (const void*)F.clips[s] : (const void*)F.part[s];
+    const auto* stage = (const unsigned long long*)((const char*)part +
+                                                    fin_stage(F.n, count ? sizeof(unsigned) : sizeof(U)));
+    unsigned long long acc = (int)threadIdx.x < g ? stage[threadIdx.x] : 0ull;
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, kWave);
-    if (threadIdx.x == 0) counters[0] += a;
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const unsigned long long y = __shfl_xor(acc, o, kWave);
+        acc = count ? acc + y : (y > acc ? y : acc);
+    }
+    if (threadIdx.x != 0) return;
+    if (!count) *F.slot[s] = (U)acc;
+    else if (acc) atomicAdd(F.counters, acc);
 }
 
-static void launch_count_finalize(const unsigned* part, long long n, unsigned long long* counters, hipStream_t st) {
-    const FinSplit fs = fin_split(n);
-    if (fs.blocks == 1) {
-        hipLaunchKernelGGL(count_stage_kernel, dim3(1), dim3(256), 0, st, part, n, n, counters, 1);
-        return;
+template <class T>
+hipError_t launch_fit_fold(int ns, const MaxSink* sinks, unsigned* const* clips, void* counters, long long cells,
+                           hipStream_t st) {
+    using U = typename Bits<T>::U;
+    FitFold<U> F{};
+    F.counters = (unsigned long long*)counters;
+    F.n = cells;
+    bool any = counters != nullptr;
+    for (int s = 0; s < ns; ++s) {
+        const bool fold = sinks[s].slot && !sinks[s].direct(cells);
+        F.part[s] = (const U*)sinks[s].part;
+        F.slot[s] = fold ? (U*)sinks[s].slot : nullptr;
+        F.clips[s] = clips[s];
+        any = any || fold;
     }
-    auto* stage = (unsigned long long*)((char*)part + fin_stage(n, sizeof(unsigned)));
-    hipLaunchKernelGGL(count_stage_kernel, dim3(fs.blocks), dim3(256), 0, st, part, n, fs.chunk, stage, 0);
-    hipLaunchKernelGGL(count_final_kernel, dim3(1), dim3(kWave), 0, st, (const unsigned long long*)stage, fs.blocks,
-                       counters);
+    if (!any) return hipSuccess;
+    if (cells <= kFoldOne) {
+        hipLaunchKernelGGL((fit_fold_kernel<U>), dim3(2 * ns), dim3(1024), 0, st, F);
+        return hipGetLastError();
+    }
+    const FinSplit fs = fin_split(cells);
+    hipLaunchKernelGGL((fit_stage_kernel<U>), dim3(fs.blocks, 2 * ns), dim3(256), 0, st, F, fs.chunk);
+    hipLaunchKernelGGL((fit_final_kernel<U>), dim3(2 * ns), dim3(kWave), 0, st, F, fs.blocks);
+    return hipGetLastError();
 }
 
 template <class T>
 hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
-                       long long cells, const VGridArgs& a, void* max_out, void* part, unsigned* clip_part,
+                       long long cells, const VGridArgs& a, const MaxSink& sink, unsigned* clip_part,
                        double* scratch, hipStream_t st) {
     VGrid G{a.nv[0], a.nv[1], a.nv[2], {a.lo[0], a.lo[1], a.lo[2]}, {a.dv[0], a.dv[1], a.dv[2]}, a.m, 1.0f / (float)a.nv[2]};
     const int nv = a.nv[0] * a.nv[1] * a.nv[2];
@@ -1036,7 +1115,7 @@ hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, 
     const int threads = 256;
     const int ept = (nv + threads - 1) / threads;
     auto* cnt = (unsigned long long*)counters;
-    auto* mo = (typename Bits<T>::U*)(max_out ? part : nullptr);
+    auto* mo = sink.target<T>(cells);
     unsigned* cp = cnt ? clip_part : nullptr;
     const int N = cube_edge(a);
     if (N) {
@@ -1061,41 +1140,35 @@ hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, 
                 hipLaunchKernelGGL((fit3_stream_kernel<T, kBigCube, 256>), grid, dim3(256), 0, st, fin, fout, P,
                                    mom_post, cp, G, X, mo);
         }
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess && cnt)
-            launch_count_finalize(clip_part, cells, cnt, st);
-        if (e == hipSuccess && max_out) e = launch_max_finalize<T>(part, cells, max_out, st);
-        return e == hipSuccess ? hipGetLastError() : e;
+        return hipGetLastError();
     }
     if (ept <= 4)
         hipLaunchKernelGGL((fit3_kernel<T, 4>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, G, mo);
+                           mom_post, cnt, cp, G, mo);
     else if (ept <= 8)
         hipLaunchKernelGGL((fit3_kernel<T, 8>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, G, mo);
+                           mom_post, cnt, cp, G, mo);
     else if (ept <= 16)
         hipLaunchKernelGGL((fit3_kernel<T, 16>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, G, mo);
+                           mom_post, cnt, cp, G, mo);
     else if (ept <= 32)
         hipLaunchKernelGGL((fit3_kernel<T, 32>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, G, mo);
+                           mom_post, cnt, cp, G, mo);
     else
         return hipErrorInvalidValue;
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !max_out) return e;
-    return launch_max_finalize<T>(part, cells, max_out, st);
+    return hipGetLastError();
 }
 
 template <class T>
 hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
-                       long long cells, int nv, double vlo, double dv, double m, void* max_out, void* part,
+                       long long cells, int nv, double vlo, double dv, double m, const MaxSink& sink,
                        hipStream_t st) {
     hipLaunchKernelGGL((fit1_kernel<T>), dim3((unsigned)cells), dim3(threads_for(nv)), sizeof(T) * (size_t)nv, st,
                        fin, fout, mom_pre, U, mom_post, (unsigned long long*)counters, nv, vlo, dv, m,
-                       (typename Bits<T>::U*)(max_out ? part : nullptr));
+                       sink.target<T>(cells));
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !max_out) return e;
-    return launch_max_finalize<T>(part, cells, max_out, st);
+    if (e != hipSuccess || !sink.slot || sink.direct(cells)) return e;
+    return launch_max_finalize<T>(sink.part, cells, sink.slot, st);
 }
 
 #define VL_INST(T)                                                                                              \
@@ -1103,9 +1176,11 @@ hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, double* U, 
     template hipError_t launch_moments1<T>(const T*, double*, long long, int, double, double, double,            \
                                            hipStream_t);                                                        \
     template hipError_t launch_fit3<T>(const T*, T*, const double*, double*, double*, void*, long long,         \
-                                       const VGridArgs&, void*, void*, unsigned*, double*, hipStream_t);        \
+                                       const VGridArgs&, const MaxSink&, unsigned*, double*, hipStream_t);      \
+    template hipError_t launch_fit_fold<T>(int, const MaxSink*, unsigned* const*, void*, long long,             \
+                                           hipStream_t);                                                       \
     template hipError_t launch_fit1<T>(const T*, T*, const double*, double*, double*, void*, long long, int,    \
-                                       double, double, double, void*, void*, hipStream_t);
+                                       double, double, double, const MaxSink&, hipStream_t);
 VL_INST(float)
 VL_INST(double)
 #undef VL_INST

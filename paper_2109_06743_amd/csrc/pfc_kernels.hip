@@ -25,10 +25,10 @@ namespace vl {
 // Offsets within a row are 32-bit (nx * Nv < 2^31 is checked on the host) and
 // advance by one row per element; only windows that cross the periodic seam
 // take the wrapping path.
-template <class T, int CX>
+template <class T, int CX, bool kFold>
 __global__ void __launch_bounds__(256)
 pfc_x_kernel(const T* __restrict__ fin, T* __restrict__ fout, int nx, int Nv, float inv_inner, double vx_lo,
-             double dvx, double tau_dx, const T* __restrict__ finf_p, typename Bits<T>::U* __restrict__ max_out) {
+             double dvx, double tau_dx, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     // work index = (v block fastest, then x chunk, then row), XCD-contiguous
     const unsigned nvb = (Nv + 255) / 256, nch = (nx + CX - 1) / CX;
     const unsigned w = xcd_work_index(blockIdx.x, gridDim.x);
@@ -37,7 +37,7 @@ pfc_x_kernel(const T* __restrict__ fin, T* __restrict__ fout, int nx, int Nv, fl
     const size_t rowoff = (size_t)(w / (nvb * nch)) * nx * Nv;
     const T* __restrict__ src = fin + rowoff;
     T* __restrict__ dst = fout + rowoff;
-    const T F2 = T(2) * *finf_p;
+    const T F2 = T(2) * max_of<T, kFold>(finf_r);
     T mx = T(0);
     if (v < Nv) {
         const int ivx = row_of(v, inv_inner);
@@ -160,9 +160,9 @@ struct XYArgs {
     double vx_lo, dvx, tau_dx, vy_lo, dvy, tau_dy;
 };
 
-template <class T, int C, bool WIDE>
+template <class T, int C, bool WIDE, bool kFold>
 __global__ void __launch_bounds__(256)
-pfc_xy_kernel(const T* __restrict__ fin, T* __restrict__ fout, XYArgs A, const T* __restrict__ finf_p,
+pfc_xy_kernel(const T* __restrict__ fin, T* __restrict__ fout, XYArgs A, MaxRef finf_r,
               typename Bits<T>::U* __restrict__ max_out) {
     const unsigned gw = xcd_work_index(blockIdx.x, gridDim.x) * 4u + (threadIdx.x >> 6);
     const int lane = threadIdx.x & (kWave - 1);
@@ -170,7 +170,7 @@ pfc_xy_kernel(const T* __restrict__ fin, T* __restrict__ fout, XYArgs A, const T
     const unsigned rest = gw / (unsigned)A.nchunks;
     const int c0 = (int)(rest % (unsigned)A.nst) * C;
     const unsigned seg = rest / (unsigned)A.nst;
-    const T F2 = T(2) * *finf_p;
+    const T F2 = T(2) * max_of<T, kFold>(finf_r);
     T mx = T(0);
     if (seg < (unsigned)A.nseg) {                    // wave-uniform
         const int nx = A.nx, ny = A.ny, Nv = A.Nv;
@@ -453,10 +453,10 @@ __device__ __forceinline__ void sweep_affine(T* blk, int dd, const double* C, co
     }
 }
 
-template <class T, int NMAX, int NTH = 256>
+template <class T, int NMAX, int NTH, bool kFold>
 __global__ void __launch_bounds__(NTH)
 pfc_v3b_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B,
-               V3Params P, const T* __restrict__ finf_p, typename Bits<T>::U* __restrict__ max_out) {
+               V3Params P, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
     T* blk = reinterpret_cast<T*>(smem_raw);
     __shared__ double EB[6];
@@ -464,7 +464,7 @@ pfc_v3b_kernel(const T* fin, T* fout, const double* __restrict__ E, const double
     const long long cell = blockIdx.x;
     const int nv = P.nvx * P.nvy * P.nvz;
     const int pz = P.nvz | 1;
-    const T finf = *finf_p;
+    const T finf = max_of<T, kFold>(finf_r);
     if (threadIdx.x < 3) {
         EB[threadIdx.x] = E[cell * 3 + threadIdx.x];
         EB[3 + threadIdx.x] = B ? B[cell * 3 + threadIdx.x] : 0.0;
@@ -522,17 +522,17 @@ __device__ __forceinline__ T zeroflux_out(const T* g, int n, int p, long long K,
 
 // 1V velocity sweep: one block per spatial cell, the pencil staged in shared
 // memory (nv + 4 values).  s = (q/m) E_i tau / dv.  In place is allowed.
-template <class T>
+template <class T, bool kFold>
 __global__ void __launch_bounds__(256)
 pfc_v1_kernel(const T* fin, T* fout, int nv, const double* __restrict__ E, double qm_tau_dv,
-              const T* __restrict__ finf_p, typename Bits<T>::U* __restrict__ max_out) {
+              MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
     T* g = reinterpret_cast<T*>(smem_raw);
     const int ix = blockIdx.x;
     const double s = qm_tau_dv * E[ix];
     const bool pos = s >= 0.0;
     const Shift<T> sh(fabs(s));
-    const T finf = *finf_p;
+    const T finf = max_of<T, kFold>(finf_r);
     const T* src = fin + (long long)ix * nv;
     T* dst = fout + (long long)ix * nv;
     for (int k = threadIdx.x; k < nv + 4; k += blockDim.x) {
@@ -624,17 +624,17 @@ __device__ __forceinline__ void sweep3(T* blk, int d, double sigma, const V3Para
     }
 }
 
-template <class T, int NMAX>
+template <class T, int NMAX, bool kFold>
 __global__ void __launch_bounds__(256)
 pfc_v3_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B,
-              V3Params P, const T* __restrict__ finf_p, typename Bits<T>::U* __restrict__ max_out) {
+              V3Params P, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
     T* blk = reinterpret_cast<T*>(smem_raw);
     __shared__ double EB[6];
     const long long cell = blockIdx.x;
     const int nv = P.nvx * P.nvy * P.nvz;
     const int pz = P.nvz | 1;
-    const T finf = *finf_p;
+    const T finf = max_of<T, kFold>(finf_r);
     if (threadIdx.x < 3) {
         EB[threadIdx.x] = E[cell * 3 + threadIdx.x];
         EB[3 + threadIdx.x] = B ? B[cell * 3 + threadIdx.x] : 0.0;
@@ -862,10 +862,10 @@ __device__ __forceinline__ void sweep_cube(T* blk, int d, double sigma, const V3
     }
 }
 
-template <class T, int N, int NTH>
+template <class T, int N, int NTH, bool kFold>
 __global__ void __launch_bounds__(NTH)
 pfc_v3_cube_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B, V3Params P,
-                   const T* __restrict__ finf_p, typename Bits<T>::U* __restrict__ max_out) {
+                   MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     constexpr int PZ = N | 1;
     constexpr int NV = N * N * N;
     constexpr int PER = NV / NTH;            // values per thread (NTH divides N^3)
@@ -876,7 +876,7 @@ pfc_v3_cube_kernel(const T* fin, T* fout, const double* __restrict__ E, const do
     __shared__ T blk[N * N * PZ];
     __shared__ double EB[6];
     const long long cell = xcd_work_index(blockIdx.x, gridDim.x);
-    const T F2 = T(2) * *finf_p;
+    const T F2 = T(2) * max_of<T, kFold>(finf_r);
     if (threadIdx.x < 3) {
         EB[threadIdx.x] = E[cell * 3 + threadIdx.x];
         EB[3 + threadIdx.x] = B ? B[cell * 3 + threadIdx.x] : 0.0;
@@ -1063,10 +1063,10 @@ pfc_v3_cube_kernel(const T* fin, T* fout, const double* __restrict__ E, const do
 // shifts by a cell or more is swept in the cell's output block, in its own
 // positions, which nothing else reads or writes meanwhile (in place as well:
 // the pencil's input has been read by then).
-template <class T, int N, int NTH, int PL>
+template <class T, int N, int NTH, int PL, bool kFold>
 __global__ void __launch_bounds__(NTH)
 pfc_v3_planes_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B,
-                     V3Params P, const T* __restrict__ finf_p, typename Bits<T>::U* __restrict__ max_out) {
+                     V3Params P, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     constexpr int PZ = N | 1;
     constexpr int NN = N * N;
     constexpr int NP = (NN + NTH - 1) / NTH;     // v_x pencils per thread (the last one partial)
@@ -1076,7 +1076,7 @@ pfc_v3_planes_kernel(const T* fin, T* fout, const double* __restrict__ E, const 
     __shared__ T blk[PL * N * PZ];
     const int t = threadIdx.x;
     const long long cell = xcd_work_index(blockIdx.x, gridDim.x);
-    const T F2 = T(2) * *finf_p;
+    const T F2 = T(2) * max_of<T, kFold>(finf_r);
     T* dst = fout + cell * (N * NN);
     const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(fin + cell * (N * NN)), 0, N * XB, kBufWord3);
     const auto rd = __builtin_amdgcn_make_buffer_rsrc(dst, 0, N * XB, kBufWord3);
@@ -1220,11 +1220,19 @@ array_max_kernel(const T* __restrict__ f, long long n, typename Bits<T>::U* __re
 }
 
 // Maximum of the per-block partial maxima part[0..n) into *slot (bits of
-// non-negative values order like the values), in two launches: up to
+// non-negative values order like the values).  Up to kFoldOne partials: one
+// 1024-thread block, 16-byte loads, eight in flight per thread (32768 FP32
+// partials: 13.2 us in the two launches below, 4.8 us in one).  More: up to
 // kFinStage blocks each fold a contiguous range of the partials (eight loads
 // in flight per thread) into stage[b], placed right after the partials
-// (fin_stage); one wave folds the stage into the slot.  With a single range
-// the first launch writes the slot itself.  Fixed order.
+// (fin_stage), and one wave folds the stage into the slot: 2 MB of partials
+// are more than one CU reads quickly (524288: 10.7 + 4.7 us).  Fixed order.
+template <class U>
+__global__ void __launch_bounds__(1024)
+max_fold_kernel(const U* __restrict__ part, int n, U* __restrict__ slot) {
+    fold_max_block<U>(part, n, slot);
+}
+
 template <class U>
 __global__ void __launch_bounds__(256)
 max_stage_kernel(const U* __restrict__ part, long long n, long long chunk, U* __restrict__ out) {
@@ -1269,11 +1277,11 @@ __global__ void __launch_bounds__(kWave) max_final_kernel(const U* __restrict__ 
 template <class T>
 hipError_t launch_max_finalize(const void* part, long long n, void* slot, hipStream_t st) {
     using U = typename Bits<T>::U;
-    const FinSplit fs = fin_split(n);
-    if (fs.blocks == 1) {
-        hipLaunchKernelGGL((max_stage_kernel<U>), dim3(1), dim3(256), 0, st, (const U*)part, n, n, (U*)slot);
+    if (n <= kFoldOne) {
+        hipLaunchKernelGGL((max_fold_kernel<U>), dim3(1), dim3(1024), 0, st, (const U*)part, (int)n, (U*)slot);
         return hipGetLastError();
     }
+    const FinSplit fs = fin_split(n);
     U* stage = (U*)((char*)part + fin_stage(n, sizeof(U)));
     hipLaunchKernelGGL((max_stage_kernel<U>), dim3(fs.blocks), dim3(256), 0, st, (const U*)part, n, fs.chunk, stage);
     hipLaunchKernelGGL((max_final_kernel<U>), dim3(1), dim3(kWave), 0, st, (const U*)stage, fs.blocks, (U*)slot);
@@ -1281,29 +1289,29 @@ hipError_t launch_max_finalize(const void* part, long long n, void* slot, hipStr
 }
 
 // ------------------------------------------------------------ launchers ----
-// A launcher given max_out (the slot that receives the maximum of its output)
-// has its kernel store per-block maxima in part (>= grid-size entries of 8
-// bytes) and then reduces them into the slot.
+// A launcher given a sink has its kernel store per-block maxima in it (in the
+// slot itself where they fit, else in the sink's partials, which it then
+// reduces into the slot).
 constexpr int kChunkX = 16;
 
 long long pfc_x_blocks(int rows, int nx, long long Nv) { return ((Nv + 255) / 256) * ((nx + kChunkX - 1) / kChunkX) * rows; }
 constexpr long long kArrayMaxBlocks = 4096;
 
 template <class T>
-static hipError_t finish_max(void* max_out, void* part, long long blocks, hipStream_t st) {
+static hipError_t finish_max(const MaxSink& sink, long long blocks, hipStream_t st) {
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !max_out) return e;
-    return launch_max_finalize<T>(part, blocks, max_out, st);
+    if (e != hipSuccess || !sink.slot || sink.direct(blocks)) return e;
+    return launch_max_finalize<T>(sink.part, blocks, sink.slot, st);
 }
 
 template <class T>
 hipError_t launch_pfc_x(const T* fin, T* fout, int rows, int nx, long long Nv, int inner, double vx_lo,
-                        double dvx, double tau_dx, const void* finf, void* max_out, void* part, hipStream_t st) {
+                        double dvx, double tau_dx, MaxRef finf, const MaxSink& sink, hipStream_t st) {
     const long long blocks = pfc_x_blocks(rows, nx, Nv);
-    hipLaunchKernelGGL((pfc_x_kernel<T, kChunkX>), dim3((unsigned)blocks), dim3(256), 0, st, fin, fout, nx, (int)Nv,
-                       1.0f / (float)inner, vx_lo, dvx, tau_dx, (const T*)finf,
-                       (typename Bits<T>::U*)(max_out ? part : nullptr));
-    return finish_max<T>(max_out, part, blocks, st);
+    hipLaunchKernelGGL((finf.n > 1 ? pfc_x_kernel<T, kChunkX, true> : pfc_x_kernel<T, kChunkX, false>), dim3((unsigned)blocks), dim3(256), 0, st, fin, fout, nx, (int)Nv,
+                       1.0f / (float)inner, vx_lo, dvx, tau_dx, finf,
+                       sink.target<T>(blocks));
+    return finish_max<T>(sink, blocks, st);
 }
 
 // x cells per thread: 8 in both storage types (FP64: 256 registers, one wave
@@ -1371,7 +1379,7 @@ long long pfc_xy_blocks(int nx, int ny, int nvx, int nvy, int nvz) {
 template <class T, int C>
 static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int nvx, int nvy, int nvz, double vx_lo,
                                      double dvx, double tau_dx, double vy_lo, double dvy, double tau_dy, int per,
-                                     const void* finf, void* max_out, void* part, hipStream_t st) {
+                                     MaxRef finf, const MaxSink& sink, hipStream_t st) {
     XYArgs A;
     A.nx = nx;
     A.ny = ny;
@@ -1402,7 +1410,7 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     // the stores of one step span rows i-2-Kmax .. i-1+Kmax of one pass
     const size_t rowbytes = (size_t)nx * A.Nv * sizeof(T);
     const bool wide = (double)(2 * kb + 3) * (double)rowbytes >= 4294967296.0;
-    auto* mo = (typename Bits<T>::U*)(max_out ? part : nullptr);
+    auto* mo = sink.target<T>(blocks);
     // Workgroups resident per CU, set through a reservation of shared memory
     // the kernel does not use: with fewer waves in flight the walks of large
     // velocity blocks thrash the caches and the address translation less.
@@ -1413,12 +1421,12 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     const size_t cellb = (size_t)A.Nv * sizeof(T);
     const size_t shm = cellb >= 65536 ? 102400 : (cellb <= 8192 ? 61440 : 0);
     if (wide)
-        hipLaunchKernelGGL((pfc_xy_kernel<T, C, true>), dim3((unsigned)blocks), dim3(256), shm, st, fin, fout, A,
-                           (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_xy_kernel<T, C, true, true> : pfc_xy_kernel<T, C, true, false>), dim3((unsigned)blocks), dim3(256), shm, st, fin, fout, A,
+                           finf, mo);
     else
-        hipLaunchKernelGGL((pfc_xy_kernel<T, C, false>), dim3((unsigned)blocks), dim3(256), shm, st, fin, fout, A,
-                           (const T*)finf, mo);
-    return finish_max<T>(max_out, part, blocks, st);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_xy_kernel<T, C, false, true> : pfc_xy_kernel<T, C, false, false>), dim3((unsigned)blocks), dim3(256), shm, st, fin, fout, A,
+                           finf, mo);
+    return finish_max<T>(sink, blocks, st);
 }
 
 // Columns per lane: xy_cols for most blocks; for FP32 velocity blocks of 64 KB
@@ -1430,24 +1438,24 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
 // 6, 10 or 12 columns are slower than 8 at 12^3.
 template <class T>
 hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy, int nvz, double vx_lo, double dvx,
-                         double tau_dx, double vy_lo, double dvy, double tau_dy, int per, const void* finf,
-                         void* max_out, void* part, hipStream_t st) {
+                         double tau_dx, double vy_lo, double dvy, double tau_dy, int per, MaxRef finf,
+                         const MaxSink& sink, hipStream_t st) {
     const size_t cellb = (size_t)nvx * nvy * nvz * sizeof(T);
     if (cellb >= 65536)
         return launch_pfc_xy_cols<T, xy_cols_big<T>()>(fin, fout, nx, ny, nvx, nvy, nvz, vx_lo, dvx, tau_dx, vy_lo, dvy, tau_dy,
-                                             per, finf, max_out, part, st);
+                                             per, finf, sink, st);
     return launch_pfc_xy_cols<T, xy_cols<T>()>(fin, fout, nx, ny, nvx, nvy, nvz, vx_lo, dvx, tau_dx, vy_lo, dvy,
-                                               tau_dy, per, finf, max_out, part, st);
+                                               tau_dy, per, finf, sink, st);
 }
 
 template <class T>
 hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, const double* E, double qm_tau_dv,
-                         const void* finf, void* max_out, void* part, hipStream_t st) {
+                         MaxRef finf, const MaxSink& sink, hipStream_t st) {
     const int threads = nv >= 256 ? 256 : ((nv + 63) / 64) * 64;
     const size_t shm = sizeof(T) * (size_t)(nv + 4);
-    hipLaunchKernelGGL((pfc_v1_kernel<T>), dim3(nx), dim3(threads), shm, st, fin, fout, nv, E, qm_tau_dv,
-                       (const T*)finf, (typename Bits<T>::U*)(max_out ? part : nullptr));
-    return finish_max<T>(max_out, part, nx, st);
+    hipLaunchKernelGGL((finf.n > 1 ? pfc_v1_kernel<T, true> : pfc_v1_kernel<T, false>), dim3(nx), dim3(threads), shm, st, fin, fout, nv, E, qm_tau_dv,
+                       finf, sink.target<T>(nx));
+    return finish_max<T>(sink, nx, st);
 }
 
 size_t v3_shared_bytes(int nvx, int nvy, int nvz, size_t elem) {
@@ -1456,7 +1464,7 @@ size_t v3_shared_bytes(int nvx, int nvy, int nvz, size_t elem) {
 
 template <class T>
 hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E, const double* B,
-                         const V3Params& P, const void* finf, void* max_out, void* part, hipStream_t st) {
+                         const V3Params& P, MaxRef finf, const MaxSink& sink, hipStream_t st) {
     const int nmax = P.nvx > P.nvy ? (P.nvx > P.nvz ? P.nvx : P.nvz) : (P.nvy > P.nvz ? P.nvy : P.nvz);
     const size_t shm = v3_shared_bytes(P.nvx, P.nvy, P.nvz, sizeof(T));
     int maxpen = P.nvx * P.nvy;
@@ -1466,91 +1474,91 @@ hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E
     if (threads > 256) threads = 256;
     if (threads < 64) threads = 64;
     const bool cube = P.nvx == P.nvy && P.nvy == P.nvz;
-    auto* mo = (typename Bits<T>::U*)(max_out ? part : nullptr);
+    auto* mo = sink.target<T>(cells);
     const dim3 grid((unsigned)cells);
     if (cube && P.nvx == kBigCube) {
         // one cell per CU (its LDS); 578 threads = two v_x pencils each
         if constexpr (sizeof(T) == 4)
-            hipLaunchKernelGGL((pfc_v3_cube_kernel<T, kBigCube, 578>), grid, dim3(578), 0, st, fin, fout, E, B, P,
-                               (const T*)finf, mo);
+            hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, kBigCube, 578, true> : pfc_v3_cube_kernel<T, kBigCube, 578, false>), grid, dim3(578), 0, st, fin, fout, E, B, P,
+                               finf, mo);
         else        // the FP64 block is twice the LDS: half its v_x planes at a time
-            hipLaunchKernelGGL((pfc_v3_planes_kernel<T, kBigCube, 512, 17>), grid, dim3(512), 0, st, fin, fout, E, B,
-                               P, (const T*)finf, mo);
-        return finish_max<T>(max_out, part, cells, st);
+            hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_planes_kernel<T, kBigCube, 512, 17, true> : pfc_v3_planes_kernel<T, kBigCube, 512, 17, false>), grid, dim3(512), 0, st, fin, fout, E, B,
+                               P, finf, mo);
+        return finish_max<T>(sink, cells, st);
     }
     if (cube && P.nvx == 16) {
-        hipLaunchKernelGGL((pfc_v3_cube_kernel<T, 16, 256>), grid, dim3(256), 0, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, 16, 256, true> : pfc_v3_cube_kernel<T, 16, 256, false>), grid, dim3(256), 0, st, fin, fout, E, B, P, finf, mo);
     } else if (cube && P.nvx == 12) {
-        hipLaunchKernelGGL((pfc_v3_cube_kernel<T, 12, 192>), grid, dim3(192), 0, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, 12, 192, true> : pfc_v3_cube_kernel<T, 12, 192, false>), grid, dim3(192), 0, st, fin, fout, E, B, P, finf, mo);
     } else if (cube && P.nvx == 8) {
-        hipLaunchKernelGGL((pfc_v3_cube_kernel<T, 8, 64>), grid, dim3(64), 0, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, 8, 64, true> : pfc_v3_cube_kernel<T, 8, 64, false>), grid, dim3(64), 0, st, fin, fout, E, B, P, finf, mo);
     } else if (nmax <= 8) {
-        hipLaunchKernelGGL((pfc_v3_kernel<T, 8>), grid, dim3(threads), shm, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_kernel<T, 8, true> : pfc_v3_kernel<T, 8, false>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
     } else if (nmax <= 16) {
-        hipLaunchKernelGGL((pfc_v3_kernel<T, 16>), grid, dim3(threads), shm, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_kernel<T, 16, true> : pfc_v3_kernel<T, 16, false>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
     } else if (nmax <= 32) {
-        hipLaunchKernelGGL((pfc_v3_kernel<T, 32>), grid, dim3(threads), shm, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_kernel<T, 32, true> : pfc_v3_kernel<T, 32, false>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
     } else {
         return hipErrorInvalidValue;
     }
-    return finish_max<T>(max_out, part, cells, st);
+    return finish_max<T>(sink, cells, st);
 }
 
 // V(tau) by the backsubstitution split (any grid with every axis <= 32, and
 // the 34^3 cube in FP32, whose padded block, 158 KB, fills one CU's LDS).
 template <class T>
 hipError_t launch_pfc_v3b(const T* fin, T* fout, long long cells, const double* E, const double* B,
-                          const V3Params& P, const void* finf, void* max_out, void* part, hipStream_t st) {
+                          const V3Params& P, MaxRef finf, const MaxSink& sink, hipStream_t st) {
     const int nmax = P.nvx > P.nvy ? (P.nvx > P.nvz ? P.nvx : P.nvz) : (P.nvy > P.nvz ? P.nvy : P.nvz);
     const size_t shm = v3_shared_bytes(P.nvx, P.nvy, P.nvz, sizeof(T));
-    auto* mo = (typename Bits<T>::U*)(max_out ? part : nullptr);
+    auto* mo = sink.target<T>(cells);
     const dim3 grid((unsigned)cells);
     const bool cube12 = P.nvx == 12 && P.nvy == 12 && P.nvz == 12;
     if (nmax <= 8)
-        hipLaunchKernelGGL((pfc_v3b_kernel<T, 8>), grid, dim3(64), shm, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 8, 256, true> : pfc_v3b_kernel<T, 8, 256, false>), grid, dim3(64), shm, st, fin, fout, E, B, P, finf, mo);
     else if (cube12)    // 144 pencils per sweep: three waves instead of four (8.2 -> 6.0 ms per
                         // 1024x512x12^3 launch)
-        hipLaunchKernelGGL((pfc_v3b_kernel<T, 12, 192>), grid, dim3(192), shm, st, fin, fout, E, B, P,
-                           (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 12, 192, true> : pfc_v3b_kernel<T, 12, 192, false>), grid, dim3(192), shm, st, fin, fout, E, B, P,
+                           finf, mo);
     else if (nmax <= 16)
-        hipLaunchKernelGGL((pfc_v3b_kernel<T, 16>), grid, dim3(256), shm, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 16, 256, true> : pfc_v3b_kernel<T, 16, 256, false>), grid, dim3(256), shm, st, fin, fout, E, B, P, finf, mo);
     else if (nmax <= 32)
-        hipLaunchKernelGGL((pfc_v3b_kernel<T, 32>), grid, dim3(256), shm, st, fin, fout, E, B, P, (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 32, 256, true> : pfc_v3b_kernel<T, 32, 256, false>), grid, dim3(256), shm, st, fin, fout, E, B, P, finf, mo);
     else if constexpr (sizeof(T) == 4) {
         if (nmax > kBigCube || shm > 160 * 1024) return hipErrorInvalidValue;
         // one workgroup per CU (the block fills the LDS): 1024 threads, about
         // one pencil each per sweep (1156 per sweep); 256 threads: 7.6 -> 3.0
         // ms per 128x64x34^3 launch
-        hipLaunchKernelGGL((pfc_v3b_kernel<T, kBigCube, 1024>), grid, dim3(1024), shm, st, fin, fout, E, B, P,
-                           (const T*)finf, mo);
+        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, kBigCube, 1024, true> : pfc_v3b_kernel<T, kBigCube, 1024, false>), grid, dim3(1024), shm, st, fin, fout, E, B, P,
+                           finf, mo);
     } else {
         return hipErrorInvalidValue;
     }
-    return finish_max<T>(max_out, part, cells, st);
+    return finish_max<T>(sink, cells, st);
 }
 
 template <class T>
-hipError_t launch_array_max(const T* f, long long n, void* out, void* part, hipStream_t st) {
+hipError_t launch_array_max(const T* f, long long n, const MaxSink& sink, hipStream_t st) {
     long long blocks = (n + 255) / 256;
     if (blocks > kArrayMaxBlocks) blocks = kArrayMaxBlocks;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL((array_max_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, st, f, n,
-                       (typename Bits<T>::U*)part);
-    return finish_max<T>(out, part, blocks, st);
+                       sink.target<T>(blocks));
+    return finish_max<T>(sink, blocks, st);
 }
 
 #define VL_INST(T)                                                                                         \
     template hipError_t launch_pfc_x<T>(const T*, T*, int, int, long long, int, double, double, double,     \
-                                        const void*, void*, void*, hipStream_t);                           \
-    template hipError_t launch_pfc_v1<T>(const T*, T*, int, int, const double*, double, const void*, void*, \
-                                         void*, hipStream_t);                                              \
+                                        MaxRef, const MaxSink&, hipStream_t);                              \
+    template hipError_t launch_pfc_v1<T>(const T*, T*, int, int, const double*, double, MaxRef,             \
+                                         const MaxSink&, hipStream_t);                                     \
     template hipError_t launch_pfc_v3<T>(const T*, T*, long long, const double*, const double*,             \
-                                         const V3Params&, const void*, void*, void*, hipStream_t);         \
+                                         const V3Params&, MaxRef, const MaxSink&, hipStream_t);            \
     template hipError_t launch_pfc_v3b<T>(const T*, T*, long long, const double*, const double*,            \
-                                          const V3Params&, const void*, void*, void*, hipStream_t);        \
-    template hipError_t launch_array_max<T>(const T*, long long, void*, void*, hipStream_t);                \
+                                          const V3Params&, MaxRef, const MaxSink&, hipStream_t);           \
+    template hipError_t launch_array_max<T>(const T*, long long, const MaxSink&, hipStream_t);              \
     template hipError_t launch_pfc_xy<T>(const T*, T*, int, int, int, int, int, double, double, double, double, \
-                                         double, double, int, const void*, void*, void*, hipStream_t);     \
+                                         double, double, int, MaxRef, const MaxSink&, hipStream_t);        \
     template hipError_t launch_max_finalize<T>(const void*, long long, void*, hipStream_t);
 VL_INST(float)
 VL_INST(double)

@@ -26,19 +26,21 @@ struct vl_ctx {
     std::vector<hipEvent_t> pool;
     double t_ms[VL_T_COUNT] = {0};
     int64_t t_cnt[VL_T_COUNT] = {0};
-    // device scratch: kSlots maxima per species, then the DFT coefficients,
-    // then the diagnostics partials
+    // device scratch: kSlots slots of kSlotMax maxima per species (slot_n: the
+    // entries each holds), then the DFT coefficients, then the diagnostics
+    // partials
     unsigned long long* slots = nullptr;
+    int slot_n[4][VL_MAX_SPECIES] = {{1, 1}, {1, 1}, {1, 1}, {1, 1}};
     double* dft = nullptr;
     double* part = nullptr;
     long long cells = 0;
     long long nv[VL_MAX_SPECIES] = {0, 0};
     // per-cell fitting parameters (3V), allocated on the first fit
     double* fit_scratch = nullptr;
-    // per-block partial maxima (8 bytes each) and clip counts (4 bytes each)
-    // of the largest grid any launch of this geometry uses
-    void* bpart = nullptr;
-    unsigned* bclip = nullptr;
+    // per-block partial maxima (8 bytes each) of the largest grid any launch of
+    // this geometry uses, and clip counts (4 bytes per cell), per species
+    void* bpart[VL_MAX_SPECIES] = {nullptr, nullptr};
+    unsigned* bclip[VL_MAX_SPECIES] = {nullptr, nullptr};
     long long max_blocks = 0;
     char err[512] = {0};
 };
@@ -106,7 +108,15 @@ double dx_of(const vl_config& c) { return (c.x_hi - c.x_lo) / c.nx; }
 double dy_of(const vl_config& c) { return c.dim_x == 2 ? (c.y_hi - c.y_lo) / c.ny : 1.0; }
 double dv_of(const vl_species& s, int d) { return (s.v_hi[d] - s.v_lo[d]) / s.nv[d]; }
 
-unsigned long long* slot(vl_ctx* c, int which, int s) { return c->slots + which * VL_MAX_SPECIES + s; }
+// Maximum slot `which` of species s, as the input of a consumer and as the
+// sink of a producer.
+void* slot(vl_ctx* c, int which, int s) { return c->slots + (size_t)(which * VL_MAX_SPECIES + s) * vl::kSlotMax; }
+vl::MaxRef max_in(vl_ctx* c, int which, int s) { return {slot(c, which, s), c->slot_n[which][s]}; }
+vl::MaxSink max_to(vl_ctx* c, int which, int s) {
+    return {slot(c, which, s), c->bpart[s], &c->slot_n[which][s],
+            (which == 0 || which == 2) ? vl::kDirectX : vl::kDirectV};     // slots 1 and 3 feed V
+}
+constexpr vl::MaxSink kNoMax{};
 
 vl_status ensure_device(vl_ctx* ctx) {
     int dev = -1;
@@ -116,7 +126,7 @@ vl_status ensure_device(vl_ctx* ctx) {
     if (ctx->slots && ctx->device == dev) return VL_OK;
     if (ctx->slots && ctx->device != dev)
         return fail(ctx, VL_EDEVICE, "context was first used on device %d, current device is %d", ctx->device, dev);
-    const size_t bytes = sizeof(unsigned long long) * kSlots * VL_MAX_SPECIES +
+    const size_t bytes = sizeof(unsigned long long) * kSlots * VL_MAX_SPECIES * vl::kSlotMax +
                          sizeof(double) * (2 * (size_t)ctx->cfg.nx + 2 + kPartials);
     void* p = nullptr;
     VL_HIP(hipMalloc(&p, bytes));
@@ -124,12 +134,15 @@ vl_status ensure_device(vl_ctx* ctx) {
     void* q = nullptr;
     // per-block maxima (8 bytes a block), then the clip counts (4 bytes), each
     // followed by the stage of its two-level reduction
-    const size_t part_bytes = 8 * (size_t)ctx->max_blocks + vl::kFinSlack;
-    VL_HIP(hipMalloc(&q, part_bytes + 4 * (size_t)ctx->max_blocks + vl::kFinSlack));
-    ctx->bpart = q;
-    ctx->bclip = (unsigned*)((char*)q + part_bytes);
+    const size_t part_bytes = (8 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
+    const size_t clip_bytes = (4 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
+    VL_HIP(hipMalloc(&q, (part_bytes + clip_bytes) * ctx->cfg.nspecies));
+    for (int s = 0; s < ctx->cfg.nspecies; ++s) {
+        ctx->bpart[s] = (char*)q + s * (part_bytes + clip_bytes);
+        ctx->bclip[s] = (unsigned*)((char*)ctx->bpart[s] + part_bytes);
+    }
     ctx->slots = (unsigned long long*)p;
-    ctx->dft = (double*)(ctx->slots + kSlots * VL_MAX_SPECIES);
+    ctx->dft = (double*)(ctx->slots + (size_t)kSlots * VL_MAX_SPECIES * vl::kSlotMax);
     ctx->part = ctx->dft + 2 * (size_t)ctx->cfg.nx + 2;
     ctx->device = dev;
     return VL_OK;
@@ -178,33 +191,32 @@ size_t step_doubles(const vl_config& c) {
 
 // ------------------------------------------------------------ typed paths --
 template <class T>
-vl_status advect_x_typed(vl_ctx* ctx, int s, const T* fin, T* fout, double tau, const void* finf,
-                         void* max_x, void* max_y, hipStream_t st) {
+vl_status advect_x_typed(vl_ctx* ctx, int s, const T* fin, T* fout, double tau, vl::MaxRef finf,
+                         const vl::MaxSink& sink, hipStream_t st) {
     const vl_config& c = ctx->cfg;
     const vl_species& sp = c.sp[s];
     if (c.dim_x == 1) {
         Timed tm(ctx, VL_T_PFC_X, st);
         VL_HIP((vl::launch_pfc_x<T>(fin, fout, 1, c.nx, sp.nv[0], 1, sp.v_lo[0], dv_of(sp, 0), tau / dx_of(c), finf,
-                                    max_x, ctx->bpart, st)));
+                                    sink, st)));
         return VL_OK;
     }
     // 2X3V: x and y sweeps fused into one pass (the x-swept array stays in registers)
     Timed tm(ctx, VL_T_PFC_X, st);
     VL_HIP((vl::launch_pfc_xy<T>(fin, fout, c.nx, c.ny, sp.nv[0], sp.nv[1], sp.nv[2], sp.v_lo[0], dv_of(sp, 0),
                                  tau / dx_of(c), sp.v_lo[1], dv_of(sp, 1), tau / dy_of(c),
-                                 c.bc_y == VL_BC_PERIODIC ? 1 : 0, finf, max_y, ctx->bpart, st)));
+                                 c.bc_y == VL_BC_PERIODIC ? 1 : 0, finf, sink, st)));
     return VL_OK;
 }
 
 template <class T>
 vl_status advect_v_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* E, const double* B, double tau,
-                         const void* finf, void* max_out, hipStream_t st) {
+                         vl::MaxRef finf, const vl::MaxSink& sink, hipStream_t st) {
     const vl_config& c = ctx->cfg;
     const vl_species& sp = c.sp[s];
     Timed tm(ctx, VL_T_PFC_V, st);
     if (c.dim_v == 1) {
-        VL_HIP((vl::launch_pfc_v1<T>(fin, fout, c.nx, sp.nv[0], E, sp.q / sp.m * tau / dv_of(sp, 0), finf, max_out,
-                                     ctx->bpart, st)));
+        VL_HIP((vl::launch_pfc_v1<T>(fin, fout, c.nx, sp.nv[0], E, sp.q / sp.m * tau / dv_of(sp, 0), finf, sink, st)));
         return VL_OK;
     }
     vl::V3Params P;
@@ -220,9 +232,9 @@ vl_status advect_v_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double
     P.tau = tau;
     P.inv_nvz = 1.0f / (float)sp.nv[2];
     if (c.vsplit == VL_VSPLIT_BACKSUB)
-        VL_HIP((vl::launch_pfc_v3b<T>(fin, fout, ctx->cells, E, B, P, finf, max_out, ctx->bpart, st)));
+        VL_HIP((vl::launch_pfc_v3b<T>(fin, fout, ctx->cells, E, B, P, finf, sink, st)));
     else
-        VL_HIP((vl::launch_pfc_v3<T>(fin, fout, ctx->cells, E, B, P, finf, max_out, ctx->bpart, st)));
+        VL_HIP((vl::launch_pfc_v3<T>(fin, fout, ctx->cells, E, B, P, finf, sink, st)));
     return VL_OK;
 }
 
@@ -251,29 +263,40 @@ vl_status moments_typed(vl_ctx* ctx, int s, const T* f, double* mom, hipStream_t
 
 template <class T>
 vl_status fit_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post,
-                    int64_t* counters, void* max_out, hipStream_t st) {
+                    int64_t* counters, const vl::MaxSink& sink, hipStream_t st) {
     const vl_config& c = ctx->cfg;
     const vl_species& sp = c.sp[s];
     Timed tm(ctx, VL_T_FIT, st);
     if (c.dim_v == 1)
         VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, sp.nv[0], sp.v_lo[0],
-                                   dv_of(sp, 0), sp.m, max_out, ctx->bpart, st)));
+                                   dv_of(sp, 0), sp.m, sink, st)));
     else {
         if (!ctx->fit_scratch) {
             void* p = nullptr;
             VL_HIP(hipMalloc(&p, sizeof(double) * vl::kFitCellDoubles * (size_t)ctx->cells));
             ctx->fit_scratch = (double*)p;
         }
-        VL_HIP((vl::launch_fit3<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, grid_args(sp), max_out,
-                                   ctx->bpart, ctx->bclip, ctx->fit_scratch, st)));
+        // the caller folds the partials (fit_fold) after its last fit
+        VL_HIP((vl::launch_fit3<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, grid_args(sp), sink,
+                                   ctx->bclip[s], ctx->fit_scratch, st)));
     }
     return VL_OK;
 }
 
+// Folds the maxima and clip counts that the 3V fits of species [s0, s0 + ns)
+// left (sinks as given to fit_typed).
 template <class T>
-vl_status array_max_typed(vl_ctx* ctx, int s, const T* f, void* out, hipStream_t st) {
+vl_status fit_fold(vl_ctx* ctx, int s0, int ns, const vl::MaxSink* sinks, int64_t* counters, hipStream_t st) {
+    if (ctx->cfg.dim_v == 1) return VL_OK;
+    Timed tm(ctx, VL_T_FIT, st);
+    VL_HIP((vl::launch_fit_fold<T>(ns, sinks, ctx->bclip + s0, counters, ctx->cells, st)));
+    return VL_OK;
+}
+
+template <class T>
+vl_status array_max_typed(vl_ctx* ctx, int s, const T* f, int which, hipStream_t st) {
     Timed tm(ctx, VL_T_MAX, st);
-    VL_HIP((vl::launch_array_max<T>(f, ctx->cells * ctx->nv[s], out, ctx->bpart, st)));
+    VL_HIP((vl::launch_array_max<T>(f, ctx->cells * ctx->nv[s], max_to(ctx, which, s), st)));
     return VL_OK;
 }
 
@@ -441,7 +464,7 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
     vl_status r;
     for (int s = 0; s < ns; ++s)
         if (!S->f_max_valid)
-            if ((r = array_max_typed<T>(ctx, s, (const T*)S->f[s], slot(ctx, 0, s), st)) != VL_OK) return r;
+            if ((r = array_max_typed<T>(ctx, s, (const T*)S->f[s], 0, st)) != VL_OK) return r;
 
     if (c.dim_x == 2) {
         const long long cells = ctx->cells;
@@ -472,14 +495,13 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
             T* f = (T*)S->f[s];
             T* tmp = (T*)S->f_tmp[s];
             // X(dt/2): f -> tmp; V(dt): tmp in place; X(dt/2): tmp -> f
-            if ((r = advect_x_typed<T>(ctx, s, f, tmp, 0.5 * dt, slot(ctx, 0, s), nullptr, slot(ctx, 1, s),
-                                       st)) != VL_OK)
+            if ((r = advect_x_typed<T>(ctx, s, f, tmp, 0.5 * dt, max_in(ctx, 0, s), max_to(ctx, 1, s), st)) != VL_OK)
                 return r;
-            if ((r = advect_v_typed<T>(ctx, s, tmp, tmp, E_h, B_h, dt, slot(ctx, 1, s), slot(ctx, 2, s), st)) !=
+            if ((r = advect_v_typed<T>(ctx, s, tmp, tmp, E_h, B_h, dt, max_in(ctx, 1, s), max_to(ctx, 2, s), st)) !=
                 VL_OK)
                 return r;
-            if ((r = advect_x_typed<T>(ctx, s, tmp, f, 0.5 * dt, slot(ctx, 2, s), nullptr,
-                                       c.fit ? nullptr : slot(ctx, 0, s), st)) != VL_OK)
+            if ((r = advect_x_typed<T>(ctx, s, tmp, f, 0.5 * dt, max_in(ctx, 2, s),
+                                       c.fit ? kNoMax : max_to(ctx, 0, s), st)) != VL_OK)
                 return r;
             if ((r = moments_typed<T>(ctx, s, f, S->mom_pre[s], st)) != VL_OK) return r;
             if (!c.fit) {
@@ -504,8 +526,10 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
             }
             for (int s = 0; s < ns; ++s)
                 if ((r = fit_typed<T>(ctx, s, (T*)S->f[s], (T*)S->f[s], S->mom_pre[s], S->U[s], S->mom_post[s],
-                                      S->counters, slot(ctx, 0, s), st)) != VL_OK)
+                                      S->counters, max_to(ctx, 0, s), st)) != VL_OK)
                     return r;
+            const vl::MaxSink sinks[2] = {max_to(ctx, 0, 0), ns > 1 ? max_to(ctx, 0, 1) : kNoMax};
+            if ((r = fit_fold<T>(ctx, 0, ns, sinks, S->counters, st)) != VL_OK) return r;
         }
         const double* mom_t1[2] = {S->mom_post[0], ns > 1 ? S->mom_post[1] : nullptr};
         Timed tm(ctx, VL_T_FIELDS, st);
@@ -522,19 +546,18 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
         T* f = (T*)S->f[s];
         T* tmp = (T*)S->f_tmp[s];
         const double L = c.x_hi - c.x_lo;
-        if ((r = advect_x_typed<T>(ctx, s, f, tmp, 0.5 * dt, slot(ctx, 0, s), slot(ctx, 1, s), nullptr, st)) !=
-            VL_OK)
+        if ((r = advect_x_typed<T>(ctx, s, f, tmp, 0.5 * dt, max_in(ctx, 0, s), max_to(ctx, 1, s), st)) != VL_OK)
             return r;
         if ((r = moments_typed<T>(ctx, s, tmp, mom_half, st)) != VL_OK) return r;
         {
             Timed tm(ctx, VL_T_FIELDS, st);
             VL_HIP(vl::launch_poisson(mom_half, nx, L, c.sp[0].q, ctx->dft, S->fields, st));
         }
-        if ((r = advect_v_typed<T>(ctx, s, tmp, tmp, S->fields, nullptr, dt, slot(ctx, 1, s), slot(ctx, 2, s), st)) !=
-            VL_OK)
+        if ((r = advect_v_typed<T>(ctx, s, tmp, tmp, S->fields, nullptr, dt, max_in(ctx, 1, s), max_to(ctx, 2, s),
+                                   st)) != VL_OK)
             return r;
-        if ((r = advect_x_typed<T>(ctx, s, tmp, f, 0.5 * dt, slot(ctx, 2, s),
-                                   c.fit ? nullptr : slot(ctx, 0, s), nullptr, st)) != VL_OK)
+        if ((r = advect_x_typed<T>(ctx, s, tmp, f, 0.5 * dt, max_in(ctx, 2, s), c.fit ? kNoMax : max_to(ctx, 0, s),
+                                   st)) != VL_OK)
             return r;
         if ((r = moments_typed<T>(ctx, s, f, S->mom_pre[s], st)) != VL_OK) return r;
         if (c.fit) {
@@ -547,7 +570,7 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
             if ((r = fluid_step_impl(ctx, s, S->U[s], S->mom_post[s], S->mom_pre[s], E_t, nullptr, E_t1, nullptr, E_th,
                                      nullptr, dt, fwork, st)) != VL_OK)
                 return r;
-            if ((r = fit_typed<T>(ctx, s, f, f, S->mom_pre[s], S->U[s], S->mom_post[s], S->counters, slot(ctx, 0, s),
+            if ((r = fit_typed<T>(ctx, s, f, f, S->mom_pre[s], S->U[s], S->mom_post[s], S->counters, max_to(ctx, 0, s),
                                   st)) != VL_OK)
                 return r;
         } else {
@@ -606,13 +629,14 @@ vl_status fit_noalloc_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const dou
     const vl_species& sc = c.sp[s];
     if (c.dim_v == 1) {
         VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, sc.nv[0], sc.v_lo[0],
-                                   dv_of(sc, 0), sc.m, nullptr, nullptr, st)));
+                                   dv_of(sc, 0), sc.m, kNoMax, st)));
         return VL_OK;
     }
     double* params = (double*)sp;
     unsigned* clip = (unsigned*)((char*)sp + kNoAllocParamBytes);
-    VL_HIP((vl::launch_fit3<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, grid_args(sc), nullptr, nullptr,
-                               clip, params, st)));
+    VL_HIP((vl::launch_fit3<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, grid_args(sc), kNoMax, clip,
+                               params, st)));
+    VL_HIP((vl::launch_fit_fold<T>(1, &kNoMax, &clip, counters, ctx->cells, st)));
     return VL_OK;
 }
 
@@ -729,7 +753,7 @@ vl_status vl_destroy(vl_ctx* ctx) {
     for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
     if (ctx->slots) (void)hipFree(ctx->slots);
     if (ctx->fit_scratch) (void)hipFree(ctx->fit_scratch);
-    if (ctx->bpart) (void)hipFree(ctx->bpart);
+    if (ctx->bpart[0]) (void)hipFree(ctx->bpart[0]);
     delete ctx;
     return VL_OK;
 }
@@ -742,15 +766,12 @@ vl_status vl_pfc_advect_x(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out,
     if (f_out == f_in) return fail(ctx, VL_EALIAS, "f_out aliases f_in");
     if ((r = ensure_device(ctx)) != VL_OK) return r;
     hipStream_t st = (hipStream_t)stream;
-    void* S = slot(ctx, 3, s);
     if (ctx->cfg.f_dtype == VL_F32) {
-        if ((r = array_max_typed<float>(ctx, s, (const float*)f_in, S, st)) != VL_OK) return r;
-        return advect_x_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, tau, S, nullptr,
-                                     nullptr, st);
+        if ((r = array_max_typed<float>(ctx, s, (const float*)f_in, 3, st)) != VL_OK) return r;
+        return advect_x_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, tau, max_in(ctx, 3, s), kNoMax, st);
     }
-    if ((r = array_max_typed<double>(ctx, s, (const double*)f_in, S, st)) != VL_OK) return r;
-    return advect_x_typed<double>(ctx, s, (const double*)f_in, (double*)f_out, tau, S, nullptr,
-                                  nullptr, st);
+    if ((r = array_max_typed<double>(ctx, s, (const double*)f_in, 3, st)) != VL_OK) return r;
+    return advect_x_typed<double>(ctx, s, (const double*)f_in, (double*)f_out, tau, max_in(ctx, 3, s), kNoMax, st);
 }
 
 vl_status vl_pfc_advect_v(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out, const double* E, const double* B,
@@ -762,13 +783,12 @@ vl_status vl_pfc_advect_v(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out,
     if (f_out == f_in) return fail(ctx, VL_EALIAS, "f_out aliases f_in");
     if ((r = ensure_device(ctx)) != VL_OK) return r;
     hipStream_t st = (hipStream_t)stream;
-    void* S = slot(ctx, 3, s);
     if (ctx->cfg.f_dtype == VL_F32) {
-        if ((r = array_max_typed<float>(ctx, s, (const float*)f_in, S, st)) != VL_OK) return r;
-        return advect_v_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, E, B, tau, S, nullptr, st);
+        if ((r = array_max_typed<float>(ctx, s, (const float*)f_in, 3, st)) != VL_OK) return r;
+        return advect_v_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, E, B, tau, max_in(ctx, 3, s), kNoMax, st);
     }
-    if ((r = array_max_typed<double>(ctx, s, (const double*)f_in, S, st)) != VL_OK) return r;
-    return advect_v_typed<double>(ctx, s, (const double*)f_in, (double*)f_out, E, B, tau, S, nullptr, st);
+    if ((r = array_max_typed<double>(ctx, s, (const double*)f_in, 3, st)) != VL_OK) return r;
+    return advect_v_typed<double>(ctx, s, (const double*)f_in, (double*)f_out, E, B, tau, max_in(ctx, 3, s), kNoMax, st);
 }
 
 vl_status vl_moments(vl_ctx* ctx, int32_t s, const void* f, double* mom, vl_stream stream) {
@@ -788,11 +808,14 @@ vl_status vl_moment_fit(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out, c
     if (!f_in || !f_out || !mom_pre || !U) return fail(ctx, VL_EINVAL, "null argument");
     if ((r = ensure_device(ctx)) != VL_OK) return r;
     hipStream_t st = (hipStream_t)stream;
-    return DISPATCH(ctx,
-                    fit_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, mom_pre, U, mom_post, counters,
-                                     nullptr, st),
-                    fit_typed<double>(ctx, s, (const double*)f_in, (double*)f_out, mom_pre, U, mom_post, counters,
-                                      nullptr, st));
+    r = DISPATCH(ctx,
+                 fit_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, mom_pre, U, mom_post, counters, kNoMax,
+                                  st),
+                 fit_typed<double>(ctx, s, (const double*)f_in, (double*)f_out, mom_pre, U, mom_post, counters,
+                                   kNoMax, st));
+    if (r != VL_OK) return r;
+    return DISPATCH(ctx, fit_fold<float>(ctx, s, 1, &kNoMax, counters, st),
+                    fit_fold<double>(ctx, s, 1, &kNoMax, counters, st));
 }
 
 vl_status vl_moment_fit_noalloc(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out, const double* mom_pre,

@@ -179,6 +179,80 @@ __device__ __forceinline__ void block_max_part(T v, typename Bits<T>::U* part) {
     }
 }
 
+// A maximum kept in a context slot: n per-block maxima (n = 1: the value
+// itself).  With few partials each wave of the consumer folds them itself (no
+// barrier, the result in scalar registers); a launch that only does that
+// costs about 3 us between two small kernels.
+struct MaxRef {
+    const void* p;
+    int n;
+};
+
+// The maximum behind r, in every lane.  kFold: r.n > 1 (chosen at launch: the
+// large V launches lost 15 % with the choice in the kernel).
+template <class T, bool kFold>
+__device__ __forceinline__ T max_of(const MaxRef& r) {
+    if constexpr (!kFold) return *(const T*)r.p;
+    using U = typename Bits<T>::U;
+    const U* p = (const U*)r.p;
+    const int lane = threadIdx.x & (kWave - 1);
+    U m = *p;
+    if ((int)(blockDim.x - (threadIdx.x - lane)) < kWave) {    // a partial last wave: every lane reads all
+        for (int i = 1; i < r.n; ++i) m = p[i] > m ? p[i] : m;
+    } else {
+        for (int b = lane; b < r.n; b += 8 * kWave) {           // eight loads in flight
+            U v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = b + u * kWave < r.n ? p[b + u * kWave] : U(0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m = v[u] > m ? v[u] : m;
+        }
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) {
+            const U y = __shfl_xor(m, o, kWave);
+            m = y > m ? y : m;
+        }
+    }
+    if constexpr (sizeof(U) == 4) {
+        m = (U)__builtin_amdgcn_readfirstlane((int)m);
+    } else {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)m);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(m >> 32));
+        m = (U)lo | ((U)hi << 32);
+    }
+    return __builtin_bit_cast(T, m);
+}
+
+// Maximum of part[0..n) (unsigned bit patterns) by one 1024-thread block, into
+// *slot; 16-byte loads where part is 16-byte aligned.
+template <class U>
+__device__ __forceinline__ void fold_max_block(const U* part, int n, U* slot) {
+    constexpr int V = 16 / (int)sizeof(U);
+    typedef U Vec __attribute__((ext_vector_type(V)));
+    __shared__ U fold[1024 / kWave];
+    const int tid = threadIdx.x;
+    const int nvec = ((uintptr_t)part & 15u) ? 0 : n / V;
+    U m = 0;
+#pragma unroll 8
+    for (int i = tid; i < nvec; i += 1024) {
+        const Vec v = reinterpret_cast<const Vec*>(part)[i];
+#pragma unroll
+        for (int k = 0; k < V; ++k) m = v[k] > m ? v[k] : m;
+    }
+    for (int i = nvec * V + tid; i < n; i += 1024) m = part[i] > m ? part[i] : m;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const U y = __shfl_xor(m, o, kWave);
+        m = y > m ? y : m;
+    }
+    if ((tid & (kWave - 1)) == 0) fold[tid / kWave] = m;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < 1024 / kWave; ++w) m = fold[w] > m ? fold[w] : m;
+        *slot = m;
+    }
+}
+
 // Sum of N doubles per thread over the block; result in out[] of every thread.
 // red must hold N * (blockDim / 64) doubles of shared memory.
 template <int N>

@@ -17,12 +17,36 @@ struct VGridArgs {
 
 struct V3Params;  // pfc_kernels.hip
 
+// Where a kernel leaves the maximum of its output.  A slot holds kSlotMax
+// entries of 8 bytes: up to `direct` per-block maxima stay in the slot for the
+// consumer's waves to fold (max_of; a launch saved), more go to part and are
+// reduced into the slot's first entry.  kDirectX where the X operator consumes
+// them: its waves are few and walk many cells (1024 partials: two batches of
+// loads).  kDirectV where the velocity operator does: every cell's waves fold
+// them again (1024 partials cost it 20 % at 256x128x16^3, 64 nothing).
+// slot null: no maximum wanted.  *n receives the number of entries the slot holds.
+constexpr int kSlotMax = 1024;
+constexpr int kDirectX = 1024, kDirectV = 64;
+struct MaxSink {
+    void* slot = nullptr;
+    void* part = nullptr;
+    int* n = nullptr;
+    int most = 0;
+    bool direct(long long blocks) const { return blocks <= most; }
+    template <class T>
+    typename Bits<T>::U* target(long long blocks) const {
+        if (!slot) return nullptr;
+        *n = direct(blocks) ? (int)blocks : 1;
+        return (typename Bits<T>::U*)(direct(blocks) ? slot : part);
+    }
+};
+
 template <class T>
 hipError_t launch_pfc_x(const T* fin, T* fout, int rows, int nx, long long Nv, int inner, double vx_lo, double dvx,
-                        double tau_dx, const void* finf, void* max_out, void* part, hipStream_t st);
+                        double tau_dx, MaxRef finf, const MaxSink& sink, hipStream_t st);
 template <class T>
-hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, const double* E, double qm_tau_dv, const void* finf,
-                         void* max_out, void* part, hipStream_t st);
+hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, const double* E, double qm_tau_dv, MaxRef finf,
+                         const MaxSink& sink, hipStream_t st);
 struct V3Params {
     int nvx, nvy, nvz;
     double lo[3], dv[3], inv_dv[3];
@@ -36,15 +60,15 @@ struct V3Params {
 __device__ __forceinline__ int row_of(int e, float inv_n) { return (int)(((float)e + 0.5f) * inv_n); }
 template <class T>
 hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E, const double* B, const V3Params& P,
-                         const void* finf, void* max_out, void* part, hipStream_t st);
+                         MaxRef finf, const MaxSink& sink, hipStream_t st);
 size_t v3_shared_bytes(int nvx, int nvy, int nvz, size_t elem);
 // V(tau) by the backsubstitution split: three affine sweeps with per-face
 // feet (every velocity axis <= 32).
 template <class T>
 hipError_t launch_pfc_v3b(const T* fin, T* fout, long long cells, const double* E, const double* B, const V3Params& P,
-                          const void* finf, void* max_out, void* part, hipStream_t st);
+                          MaxRef finf, const MaxSink& sink, hipStream_t st);
 template <class T>
-hipError_t launch_array_max(const T* f, long long n, void* out, void* part, hipStream_t st);
+hipError_t launch_array_max(const T* f, long long n, const MaxSink& sink, hipStream_t st);
 // Launchers that produce a maximum store per-block partials in `part` (8 bytes
 // per block of their grid) and reduce them into the slot in a second launch;
 // these give the grid sizes, to size `part`.
@@ -54,15 +78,17 @@ long long pfc_xy_blocks(int nx, int ny, int nvx, int nvy, int nvz);
 // per = 0: reflecting y walls, 1: periodic y.
 template <class T>
 hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy, int nvz, double vx_lo, double dvx,
-                         double tau_dx, double vy_lo, double dvy, double tau_dy, int per, const void* finf,
-                         void* max_out, void* part, hipStream_t st);
+                         double tau_dx, double vy_lo, double dvy, double tau_dy, int per, MaxRef finf,
+                         const MaxSink& sink, hipStream_t st);
 constexpr long long kMaxArrayBlocks = 4096;
-// Reductions of per-block partials (maxima, clip counts) run in two launches:
+// Reductions of up to kFoldOne per-block partials (maxima, clip counts) run in
+// one launch of one block, longer ones in two:
 // fin_split(n).blocks <= kFinStage blocks fold ranges of fin_split(n).chunk
 // partials into a stage of kFinStage entries that sits fin_stage(n, size)
 // bytes after the partials' start, then one wave folds the stage.  A partials
 // buffer of n entries of `size` bytes therefore needs kFinSlack bytes beyond
 // its n * size.
+constexpr long long kFoldOne = 65536;
 constexpr int kFinStage = 64;
 constexpr long long kFinRange = 8192;          // partials per first-level block, at least
 constexpr size_t kFinSlack = 128 + kFinStage * 8;
@@ -75,7 +101,7 @@ inline FinSplit fin_split(long long n) {
     g = g < 1 ? 1 : (g > kFinStage ? kFinStage : g);
     return {(int)g, (n + g - 1) / g};
 }
-inline size_t fin_stage(long long n, size_t size) { return ((size_t)n * size + 127) / 128 * 128; }
+__host__ __device__ inline size_t fin_stage(long long n, size_t size) { return ((size_t)n * size + 127) / 128 * 128; }
 template <class T>
 hipError_t launch_max_finalize(const void* part, long long n, void* slot, hipStream_t st);
 
@@ -92,11 +118,17 @@ constexpr int kBigCube = 34;
 constexpr int kFitCellDoubles = 20;
 template <class T>
 hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
-                       long long cells, const VGridArgs& a, void* max_out, void* part, unsigned* clip_part,
+                       long long cells, const VGridArgs& a, const MaxSink& sink, unsigned* clip_part,
                        double* scratch, hipStream_t st);
+// launch_fit3 leaves per-block maxima in the sink and per-cell clip counts in
+// clip_part; launch_fit_fold, after the fits of all ns species, folds them
+// into the sinks' slots and the counters.
+template <class T>
+hipError_t launch_fit_fold(int ns, const MaxSink* sinks, unsigned* const* clips, void* counters, long long cells,
+                           hipStream_t st);
 template <class T>
 hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
-                       long long cells, int nv, double vlo, double dv, double m, void* max_out, void* part,
+                       long long cells, int nv, double vlo, double dv, double m, const MaxSink& sink,
                        hipStream_t st);
 
 hipError_t launch_poisson(const double* mom, int N, double L, double q, double* ab, double* E, hipStream_t st);
