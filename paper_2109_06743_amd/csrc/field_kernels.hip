@@ -2,9 +2,12 @@
 // precision because the energy exchange with the particles depends on it).
 //
 // 1X1V (Sec. 3.1): Gauss's law dE/dx = rho with eps0 = 1 and a uniform static
-// ion background, solved with a direct discrete Fourier transform (the grid
-// is small): E_i = (2/N) sum_{m=1}^{N/2-1} Im(rho_hat_m e^{i th}) / k_m, the mean
-// and Nyquist modes dropped.
+// ion background, solved with a discrete Fourier transform,
+// E_i = (2/N) sum_{m=1}^{N/2-1} Im(rho_hat_m e^{i th}) / k_m, the mean and
+// Nyquist modes dropped.  Written out that is a convolution of the density
+// with g[n] = (2/N) sum_m sin(2 pi m n / N) / k_m, which depends on the grid
+// only: g is tabulated once per context and a solve is N multiply-adds per
+// cell, done by the kernels that need E.
 //
 // 2X3V (Sec. 2.1, Maxwell's equations, FDTD): Yee grid, mu0 = 1, eps0 = 1/c^2,
 // x periodic, conducting walls in y with the tangential E (Ex, Ez) and normal
@@ -15,38 +18,40 @@
 namespace vl {
 
 // --------------------------------------------------------------- Poisson ---
-__global__ void dft_rho_kernel(const double* __restrict__ mom, int N, double q, double* __restrict__ ab) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x + 1;    // 1 .. N/2-1
-    if (m >= (N + 1) / 2) return;
-    double a = 0.0, b = 0.0;
-    for (int i = 0; i < N; ++i) {
-        const double rho = q * mom[(long long)i * 4];
-        double s, c;
-        sincospi(2.0 * (double)(((long long)m * i) % N) / N, &s, &c);
-        a += rho * c;
-        b -= rho * s;
-    }
-    ab[2 * m] = a;
-    ab[2 * m + 1] = b;
-}
-
-__global__ void dft_field_kernel(const double* __restrict__ ab, int N, double L, double* __restrict__ E) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
+// Table of the Green's function, one wave per entry 0 .. N/2 (g is odd).
+__global__ void __launch_bounds__(256) poisson_green_kernel(int N, double L, double* __restrict__ g) {
+    const int n = (int)blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (n > N / 2) return;
     double acc = 0.0;
-    for (int m = 1; m < (N + 1) / 2; ++m) {
-        double s, c;
-        sincospi(2.0 * (double)(((long long)m * i) % N) / N, &s, &c);
-        const double k = 2.0 * M_PI * m / L;
-        acc += (ab[2 * m] * s + ab[2 * m + 1] * c) / k;
+    for (int m = 1 + lane; m < (N + 1) / 2; m += 64)
+        acc += sinpi(2.0 * (double)(((long long)m * n) % N) / N) / (2.0 * M_PI * m / L);
+    acc = 2.0 * wave_sum(acc) / N;
+    if (2 * n == N || n == 0) acc = 0.0;
+    if (lane == 0) {
+        g[n] = acc;
+        if (n > 0) g[N - n] = 2 * n == N ? 0.0 : -acc;
     }
-    E[i] = 2.0 * acc / N;
 }
 
-hipError_t launch_poisson(const double* mom, int N, double L, double q, double* ab, double* E, hipStream_t st) {
-    const int nm = (N + 1) / 2 - 1;
-    if (nm > 0) hipLaunchKernelGGL(dft_rho_kernel, dim3((nm + 63) / 64), dim3(64), 0, st, mom, N, q, ab);
-    hipLaunchKernelGGL(dft_field_kernel, dim3((N + 63) / 64), dim3(64), 0, st, ab, N, L, E);
+// E at the centres from species moments [N][4].  Serial sums of FP64 sine and
+// cosine calls, one thread per mode and then per cell, took 126 us at N = 256
+// and 30 us at N = 64; this takes 5.
+__global__ void __launch_bounds__(256)
+poisson_kernel(const double* __restrict__ mom, int N, double q, const double* __restrict__ g, double* __restrict__ E) {
+    __shared__ PoissonLds<1> L;
+    const double* const src[1] = {mom};
+    poisson_tile<1>(src, N, g, blockIdx.x * 64, q, L);
+    const int i = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x < 64 && i < N) E[i] = L.e[0][threadIdx.x];
+}
+
+hipError_t launch_poisson_green(int N, double L, double* g, hipStream_t st) {
+    hipLaunchKernelGGL(poisson_green_kernel, dim3((N / 2 + 4) / 4), dim3(256), 0, st, N, L, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_poisson(const double* mom, int N, double q, const double* g, double* E, hipStream_t st) {
+    hipLaunchKernelGGL(poisson_kernel, dim3((N + 63) / 64), dim3(256), 0, st, mom, N, q, g, E);
     return hipGetLastError();
 }
 

@@ -354,53 +354,105 @@ __global__ void qcal_q0_kernel(const double* __restrict__ U, long long cells, do
 }
 
 // ------------------------------------------------------------------- 1V ----
-__global__ void flux_x1_kernel(const double* __restrict__ U, const double* __restrict__ QA,
-                               const double* __restrict__ QB, double wa, double wb, int nx, double m,
-                               double* __restrict__ Hx) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nx) return;
-    double c[4][4];
+// One SSP-RK3 step of the 1V fluid in one launch.  A block advances kLineTile
+// cells: it holds them with six halo cells on each side (two per stage), runs
+// the three stages in shared memory on a range that shrinks by two cells per
+// side and stage, and writes its own cells to Uout, which must not be U unless
+// one block covers the grid (another block reads U's halo).  The step is a
+// chain of tiny dependent kernels otherwise: two launches per stage and the
+// stage fields took 12 launches, about 3 us each whatever the grid.
+// G.g set: the stage fields are the Poisson solves of the densities at t and
+// t+1 and their mean, formed here; else they are read from E_t, E_t1, E_th.
+struct LineFluid {
+    const double* U;
+    double* Uout;
+    const double* mom_t;
+    const double* mom_t1;
+    const double* E_t;
+    const double* E_t1;
+    const double* E_th;
+    const double* g;
+    double dt, q, m, dx;
+    int nx;
+};
+constexpr int kLineTile = 56;                 // + 8: the 64 cells whose fields the stages need
+constexpr int kLineCells = kLineTile + 12;
+
+__global__ void __launch_bounds__(256) line_rk3_kernel(LineFluid G) {
+    __shared__ PoissonLds<2> P;
+    __shared__ double cur[4][kLineCells], lo[4][kLineCells], hi[4][kLineCells], F[3][kLineCells];
+    const int c = threadIdx.x;                // cell i0 - 6 + c
+    const int i0 = blockIdx.x * kLineTile;
+    const bool in = c < kLineCells;
+    const int i = (int)((((long long)i0 - 6 + c) % G.nx + G.nx) % G.nx);
+    double un[3] = {0.0, 0.0, 0.0}, qa = 0.0, qb = 0.0;
+    if (in) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int ii = ((i - 1 + t) % nx + nx) % nx;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) c[t][k] = U[(long long)ii * 3 + k];
-        c[t][3] = wa * QA[(long long)ii * 4 + 3] + (wb != 0.0 ? wb * QB[(long long)ii * 4 + 3] : 0.0);
+        for (int k = 0; k < 3; ++k) un[k] = G.U[3ll * i + k];
+        qa = G.mom_t[4ll * i + 3];
+        qb = G.mom_t1[4ll * i + 3];
     }
-    double Um[4], Up[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double l1, r1, l2, r2;
-        cweno(c[0][k], c[1][k], c[2][k], l1, r1);
-        cweno(c[1][k], c[2][k], c[3][k], l2, r2);
-        Um[k] = r1;
-        Up[k] = l2;
+    if (G.g) {
+        const double* const src[2] = {G.mom_t, G.mom_t1};
+        poisson_tile<2>(src, G.nx, G.g, i0 - 4, G.q, P);
     }
+    double us[3] = {un[0], un[1], un[2]};
+    const double m = G.m;
     auto spd = [m](const double* V) {
         const double u = V[1] / V[0];
         const double p = V[2] - m * V[0] * u * u;
         return fabs(u) + sqrt(fmax(3.0 * p / (m * V[0]), 0.0));
     };
-    const double a = fmax(spd(Um), spd(Up));
-    const double Fm[3] = {Um[1], Um[2] / m, Um[3]}, Fp[3] = {Up[1], Up[2] / m, Up[3]};
+#pragma unroll 1
+    for (int s = 0; s < 3; ++s) {
+        const int r = 2 * (s + 1);            // this stage updates cells [r, kLineCells - r)
+        if (in) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) Hx[(long long)i * 3 + k] = 0.5 * (Fp[k] + Fm[k]) - 0.5 * a * (Up[k] - Um[k]);
+            for (int k = 0; k < 3; ++k) cur[k][c] = us[k];
+            cur[3][c] = s == 0 ? qa : (s == 1 ? qb : 0.5 * qa + 0.5 * qb);
+        }
+        __syncthreads();
+        if (c >= r - 1 && c < kLineCells - r + 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) cweno(cur[k][c - 1], cur[k][c], cur[k][c + 1], lo[k][c], hi[k][c]);
+        }
+        __syncthreads();
+        if (c >= r - 1 && c < kLineCells - r) {          // face c + 1/2
+            const double Um[4] = {hi[0][c], hi[1][c], hi[2][c], hi[3][c]};
+            const double Up[4] = {lo[0][c + 1], lo[1][c + 1], lo[2][c + 1], lo[3][c + 1]};
+            const double a = fmax(spd(Um), spd(Up));
+            const double Fm[3] = {Um[1], Um[2] / m, Um[3]}, Fp[3] = {Up[1], Up[2] / m, Up[3]};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) F[k][c] = 0.5 * (Fp[k] + Fm[k]) - 0.5 * a * (Up[k] - Um[k]);
+        }
+        __syncthreads();
+        if (c >= r && c < kLineCells - r) {
+            double e;
+            if (G.g) {
+                const double et = P.e[0][c - 2], et1 = P.e[1][c - 2];
+                e = s == 0 ? et : (s == 1 ? et1 : 0.5 * et + 0.5 * et1);
+            } else {
+                e = (s == 0 ? G.E_t : (s == 1 ? G.E_t1 : G.E_th))[i];
+            }
+            const double a = s == 0 ? 0.0 : (s == 1 ? 0.75 : 1.0 / 3.0), b = s == 0 ? 1.0 : (s == 1 ? 0.25 : 2.0 / 3.0);
+            const double L[3] = {0.0, (G.q / m) * us[0] * e, 2.0 * G.q * us[1] * e};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double v = us[k] + G.dt * (L[k] - (F[k][c] - F[k][c - 1]) / G.dx);
+                us[k] = (a != 0.0 ? a * un[k] : 0.0) + b * v;
+            }
+        }
+        __syncthreads();
+    }
+    if (c >= 6 && c < 6 + kLineTile && i0 + c - 6 < G.nx) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) G.Uout[3ll * i + k] = us[k];
+    }
 }
 
-__global__ void update1_kernel(const double* __restrict__ Us, const double* Un, double* Uout,
-                               const double* __restrict__ Hx, const double* __restrict__ E, double a, double b,
-                               double dt, int nx, double q, double m, double dx) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nx) return;
-    const int im = (i == 0) ? nx - 1 : i - 1;
-    const double n = Us[i * 3], nu = Us[i * 3 + 1];
-    const double e = E[i];
-    const double L[3] = {0.0, (q / m) * n * e, 2.0 * q * nu * e};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double s = Us[i * 3 + k] + dt * (L[k] - (Hx[i * 3 + k] - Hx[im * 3 + k]) / dx);
-        Uout[i * 3 + k] = (a != 0.0 ? a * Un[i * 3 + k] : 0.0) + b * s;
-    }
+__global__ void __launch_bounds__(256) copy_kernel(const double* __restrict__ a, double* __restrict__ b, long long n) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) b[i] = a[i];
 }
 
 // -------------------------------------------------------------- launchers --
@@ -515,25 +567,15 @@ hipError_t launch_qcal_q0(const double* U, long long cells, double m, double* qc
     return hipGetLastError();
 }
 
-hipError_t launch_fluid_rk3_1v(double* U, const double* mom_t, const double* mom_t1, const double* E_t,
-                               const double* E_t1, const double* E_th, double dt, int nx, double q, double m,
-                               double dx, double* work, hipStream_t st) {
-    double* U1 = work;
-    double* U2 = U1 + (long long)nx * 3;
-    double* Hx = U2 + (long long)nx * 3;
-    dim3 blk(64), g((nx + 63) / 64);
-    struct Stage { const double* Us; const double* Un; double* Uo; const double* QA; const double* QB; double wa, wb;
-                   const double* E; double a, b; };
-    const Stage S[3] = {
-        {U, U, U1, mom_t, mom_t, 1.0, 0.0, E_t, 0.0, 1.0},
-        {U1, U, U2, mom_t1, mom_t1, 1.0, 0.0, E_t1, 0.75, 0.25},
-        {U2, U, U, mom_t, mom_t1, 0.5, 0.5, E_th, 1.0 / 3.0, 2.0 / 3.0},
-    };
-    for (int k = 0; k < 3; ++k) {
-        hipLaunchKernelGGL(flux_x1_kernel, g, blk, 0, st, S[k].Us, S[k].QA, S[k].QB, S[k].wa, S[k].wb, nx, m, Hx);
-        hipLaunchKernelGGL(update1_kernel, g, blk, 0, st, S[k].Us, S[k].Un, S[k].Uo, Hx, S[k].E, S[k].a, S[k].b, dt,
-                           nx, q, m, dx);
-    }
+hipError_t launch_fluid_rk3_1v(double* U, double* Uout, const double* mom_t, const double* mom_t1, const double* E_t,
+                               const double* E_t1, const double* E_th, const double* g, double dt, int nx, double q,
+                               double m, double dx, double* work, hipStream_t st) {
+    const int blocks = (nx + kLineTile - 1) / kLineTile;
+    double* to = (Uout != U || blocks == 1) ? Uout : work;
+    LineFluid G{U, to, mom_t, mom_t1, E_t, E_t1, E_th, g, dt, q, m, dx, nx};
+    hipLaunchKernelGGL(line_rk3_kernel, dim3(blocks), dim3(256), 0, st, G);
+    if (to != Uout)
+        hipLaunchKernelGGL(copy_kernel, dim3((3 * nx + 255) / 256), dim3(256), 0, st, work, Uout, 3ll * nx);
     return hipGetLastError();
 }
 

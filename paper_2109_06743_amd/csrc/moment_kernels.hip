@@ -830,7 +830,7 @@ fit3_stream_kernel(const T* fin, T* fout, const FitCell* __restrict__ P, double*
 
 template <class T>
 __global__ void __launch_bounds__(256)
-fit1_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, double* __restrict__ U,
+fit1_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, const double* Uin, double* U,
             double* __restrict__ mom_post, unsigned long long* __restrict__ counters, int nv, double vlo,
             double dv, double mass, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
@@ -840,7 +840,7 @@ fit1_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, double* _
     const T* src = fin + cell * nv;
     T* dst = fout + cell * nv;
     const double nV = mom_pre[cell * 4 + 0];
-    const double Un = U[cell * 3 + 0], Unu = U[cell * 3 + 1], UP = U[cell * 3 + 2];
+    const double Un = Uin[cell * 3 + 0], Unu = Uin[cell * 3 + 1], UP = Uin[cell * 3 + 2];
     bool ok = nV > 1e-12 && Un > 1e-12;
     double uV = 0, TV = 0, uF = 0, TF = 0;
     if (ok) {
@@ -897,8 +897,8 @@ fit1_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, double* _
             mom_post[cell * 4 + 2] = mass * acc[2] * dv * scale;
             mom_post[cell * 4 + 3] = mass * acc[3] * dv * scale;
         }
-        if (ok) {
-            const double r = nV / Un;
+        if (ok || Uin != U) {
+            const double r = ok ? nV / Un : 1.0;
             U[cell * 3 + 0] = Un * r;
             U[cell * 3 + 1] = Unu * r;
             U[cell * 3 + 2] = UP * r;
@@ -1160,11 +1160,11 @@ hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, 
 }
 
 template <class T>
-hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
+hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, const double* Uin, double* U, double* mom_post, void* counters,
                        long long cells, int nv, double vlo, double dv, double m, const MaxSink& sink,
                        hipStream_t st) {
     hipLaunchKernelGGL((fit1_kernel<T>), dim3((unsigned)cells), dim3(threads_for(nv)), sizeof(T) * (size_t)nv, st,
-                       fin, fout, mom_pre, U, mom_post, (unsigned long long*)counters, nv, vlo, dv, m,
+                       fin, fout, mom_pre, Uin, U, mom_post, (unsigned long long*)counters, nv, vlo, dv, m,
                        sink.target<T>(cells));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !sink.slot || sink.direct(cells)) return e;
@@ -1179,8 +1179,8 @@ hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, double* U, 
                                        const VGridArgs&, const MaxSink&, unsigned*, double*, hipStream_t);      \
     template hipError_t launch_fit_fold<T>(int, const MaxSink*, unsigned* const*, void*, long long,             \
                                            hipStream_t);                                                       \
-    template hipError_t launch_fit1<T>(const T*, T*, const double*, double*, double*, void*, long long, int,    \
-                                       double, double, double, const MaxSink&, hipStream_t);
+    template hipError_t launch_fit1<T>(const T*, T*, const double*, const double*, double*, double*, void*,     \
+                                       long long, int, double, double, double, const MaxSink&, hipStream_t);
 VL_INST(float)
 VL_INST(double)
 #undef VL_INST

@@ -521,15 +521,37 @@ __device__ __forceinline__ T zeroflux_out(const T* g, int n, int p, long long K,
 }
 
 // 1V velocity sweep: one block per spatial cell, the pencil staged in shared
-// memory (nv + 4 values).  s = (q/m) E_i tau / dv.  In place is allowed.
+// memory (nv + 4 values).  s = (q/m) E_i tau / dv.  In place is allowed.  E
+// from S.E, or (S.g set) from the densities of the moments S.mom [nx][4] by
+// the Poisson convolution (see poisson_tile), stored to S.E as well: the
+// solve costs each block nx multiply-adds and the step two launches less.
+struct LineField {
+    double* E;
+    const double* mom;
+    const double* g;
+    double q;
+};
 template <class T, bool kFold>
 __global__ void __launch_bounds__(256)
-pfc_v1_kernel(const T* fin, T* fout, int nv, const double* __restrict__ E, double qm_tau_dv,
+pfc_v1_kernel(const T* fin, T* fout, int nx, int nv, LineField S, double qm_tau_dv,
               MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
+    __shared__ double red[4];
     T* g = reinterpret_cast<T*>(smem_raw);
     const int ix = blockIdx.x;
-    const double s = qm_tau_dv * E[ix];
+    double e;
+    if (S.g) {
+        const double own = S.mom[4ll * ix];
+        double acc[1] = {0.0};
+        for (int j = threadIdx.x; j < nx; j += blockDim.x)
+            acc[0] = fma(S.mom[4ll * j] - own, S.g[ix >= j ? ix - j : ix - j + nx], acc[0]);
+        block_sum<1>(acc, red);
+        e = S.q * acc[0];
+        if (threadIdx.x == 0) S.E[ix] = e;
+    } else {
+        e = S.E[ix];
+    }
+    const double s = qm_tau_dv * e;
     const bool pos = s >= 0.0;
     const Shift<T> sh(fabs(s));
     const T finf = max_of<T, kFold>(finf_r);
@@ -1449,12 +1471,13 @@ hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy
 }
 
 template <class T>
-hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, const double* E, double qm_tau_dv,
-                         MaxRef finf, const MaxSink& sink, hipStream_t st) {
+hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, double* E, const double* mom, const double* g,
+                         double q, double qm_tau_dv, MaxRef finf, const MaxSink& sink, hipStream_t st) {
     const int threads = nv >= 256 ? 256 : ((nv + 63) / 64) * 64;
     const size_t shm = sizeof(T) * (size_t)(nv + 4);
-    hipLaunchKernelGGL((finf.n > 1 ? pfc_v1_kernel<T, true> : pfc_v1_kernel<T, false>), dim3(nx), dim3(threads), shm, st, fin, fout, nv, E, qm_tau_dv,
-                       finf, sink.target<T>(nx));
+    const LineField S{E, mom, g, q};
+    hipLaunchKernelGGL((finf.n > 1 ? pfc_v1_kernel<T, true> : pfc_v1_kernel<T, false>), dim3(nx), dim3(threads), shm,
+                       st, fin, fout, nx, nv, S, qm_tau_dv, finf, sink.target<T>(nx));
     return finish_max<T>(sink, nx, st);
 }
 
@@ -1550,8 +1573,8 @@ hipError_t launch_array_max(const T* f, long long n, const MaxSink& sink, hipStr
 #define VL_INST(T)                                                                                         \
     template hipError_t launch_pfc_x<T>(const T*, T*, int, int, long long, int, double, double, double,     \
                                         MaxRef, const MaxSink&, hipStream_t);                              \
-    template hipError_t launch_pfc_v1<T>(const T*, T*, int, int, const double*, double, MaxRef,             \
-                                         const MaxSink&, hipStream_t);                                     \
+    template hipError_t launch_pfc_v1<T>(const T*, T*, int, int, double*, const double*, const double*,      \
+                                         double, double, MaxRef, const MaxSink&, hipStream_t);             \
     template hipError_t launch_pfc_v3<T>(const T*, T*, long long, const double*, const double*,             \
                                          const V3Params&, MaxRef, const MaxSink&, hipStream_t);            \
     template hipError_t launch_pfc_v3b<T>(const T*, T*, long long, const double*, const double*,            \

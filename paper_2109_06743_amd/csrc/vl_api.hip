@@ -27,11 +27,11 @@ struct vl_ctx {
     double t_ms[VL_T_COUNT] = {0};
     int64_t t_cnt[VL_T_COUNT] = {0};
     // device scratch: kSlots slots of kSlotMax maxima per species (slot_n: the
-    // entries each holds), then the DFT coefficients, then the diagnostics
+    // entries each holds), then the Poisson table (1X1V), then the diagnostics
     // partials
     unsigned long long* slots = nullptr;
     int slot_n[4][VL_MAX_SPECIES] = {{1, 1}, {1, 1}, {1, 1}, {1, 1}};
-    double* dft = nullptr;
+    double* green = nullptr;
     double* part = nullptr;
     long long cells = 0;
     long long nv[VL_MAX_SPECIES] = {0, 0};
@@ -126,24 +126,28 @@ vl_status ensure_device(vl_ctx* ctx) {
     if (ctx->slots && ctx->device == dev) return VL_OK;
     if (ctx->slots && ctx->device != dev)
         return fail(ctx, VL_EDEVICE, "context was first used on device %d, current device is %d", ctx->device, dev);
-    const size_t bytes = sizeof(unsigned long long) * kSlots * VL_MAX_SPECIES * vl::kSlotMax +
-                         sizeof(double) * (2 * (size_t)ctx->cfg.nx + 2 + kPartials);
-    void* p = nullptr;
-    VL_HIP(hipMalloc(&p, bytes));
-    VL_HIP(hipMemset(p, 0, bytes));
-    void* q = nullptr;
-    // per-block maxima (8 bytes a block), then the clip counts (4 bytes), each
-    // followed by the stage of its two-level reduction
+    // one allocation: slots, Poisson table, diagnostics partials, then per
+    // species the per-block maxima (8 bytes a block) and the clip counts (4
+    // bytes), each followed by the stage of its two-level reduction
+    const size_t slot_bytes = sizeof(unsigned long long) * kSlots * VL_MAX_SPECIES * vl::kSlotMax;
+    const size_t bytes = (slot_bytes + sizeof(double) * ((size_t)ctx->cfg.nx + kPartials) + 255) / 256 * 256;
     const size_t part_bytes = (8 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
     const size_t clip_bytes = (4 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
-    VL_HIP(hipMalloc(&q, (part_bytes + clip_bytes) * ctx->cfg.nspecies));
+    void* p = nullptr;
+    VL_HIP(hipMalloc(&p, bytes + (part_bytes + clip_bytes) * ctx->cfg.nspecies));
+    VL_HIP(hipMemset(p, 0, slot_bytes));
     for (int s = 0; s < ctx->cfg.nspecies; ++s) {
-        ctx->bpart[s] = (char*)q + s * (part_bytes + clip_bytes);
+        ctx->bpart[s] = (char*)p + bytes + s * (part_bytes + clip_bytes);
         ctx->bclip[s] = (unsigned*)((char*)ctx->bpart[s] + part_bytes);
     }
     ctx->slots = (unsigned long long*)p;
-    ctx->dft = (double*)(ctx->slots + (size_t)kSlots * VL_MAX_SPECIES * vl::kSlotMax);
-    ctx->part = ctx->dft + 2 * (size_t)ctx->cfg.nx + 2;
+    ctx->green = (double*)(ctx->slots + (size_t)kSlots * VL_MAX_SPECIES * vl::kSlotMax);
+    ctx->part = ctx->green + (size_t)ctx->cfg.nx;
+    if (ctx->cfg.dim_x == 1) {
+        // once per context; finished before any stream can use it
+        VL_HIP(vl::launch_poisson_green(ctx->cfg.nx, ctx->cfg.x_hi - ctx->cfg.x_lo, ctx->green, nullptr));
+        VL_HIP(hipStreamSynchronize(nullptr));
+    }
     ctx->device = dev;
     return VL_OK;
 }
@@ -216,7 +220,8 @@ vl_status advect_v_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double
     const vl_species& sp = c.sp[s];
     Timed tm(ctx, VL_T_PFC_V, st);
     if (c.dim_v == 1) {
-        VL_HIP((vl::launch_pfc_v1<T>(fin, fout, c.nx, sp.nv[0], E, sp.q / sp.m * tau / dv_of(sp, 0), finf, sink, st)));
+        VL_HIP((vl::launch_pfc_v1<T>(fin, fout, c.nx, sp.nv[0], const_cast<double*>(E), nullptr, nullptr, 0.0,
+                                     sp.q / sp.m * tau / dv_of(sp, 0), finf, sink, st)));
         return VL_OK;
     }
     vl::V3Params P;
@@ -268,7 +273,7 @@ vl_status fit_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* mom
     const vl_species& sp = c.sp[s];
     Timed tm(ctx, VL_T_FIT, st);
     if (c.dim_v == 1)
-        VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, sp.nv[0], sp.v_lo[0],
+        VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, U, mom_post, counters, ctx->cells, sp.nv[0], sp.v_lo[0],
                                    dv_of(sp, 0), sp.m, sink, st)));
     else {
         if (!ctx->fit_scratch) {
@@ -310,7 +315,8 @@ vl_status fluid_step_impl(vl_ctx* ctx, int s, double* U, const double* mom_t, co
         VL_HIP(vl::launch_fluid_rk3_3v(U, mom_t, mom_t1, E_t, B_t, E_t1, B_t1, E_th, B_th, dt, c.nx, c.ny, sp.q, sp.m,
                                        dx_of(c), dy_of(c), work, st, per_y(c)));
     else
-        VL_HIP(vl::launch_fluid_rk3_1v(U, mom_t, mom_t1, E_t, E_t1, E_th, dt, c.nx, sp.q, sp.m, dx_of(c), work, st));
+        VL_HIP(vl::launch_fluid_rk3_1v(U, U, mom_t, mom_t1, E_t, E_t1, E_th, nullptr, dt, c.nx, sp.q, sp.m, dx_of(c),
+                                       work, st));
     return VL_OK;
 }
 
@@ -538,41 +544,34 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
     } else {
         const int nx = c.nx;
         double* mom_half = S->work;
-        double* E_t = mom_half + 4 * nx;
-        double* E_t1 = E_t + nx;
-        double* E_th = E_t1 + nx;
-        double* fwork = E_th + nx;
+        double* Unew = mom_half + 4 * nx;
         const int s = 0;
+        const vl_species& sp = c.sp[0];
         T* f = (T*)S->f[s];
         T* tmp = (T*)S->f_tmp[s];
-        const double L = c.x_hi - c.x_lo;
         if ((r = advect_x_typed<T>(ctx, s, f, tmp, 0.5 * dt, max_in(ctx, 0, s), max_to(ctx, 1, s), st)) != VL_OK)
             return r;
         if ((r = moments_typed<T>(ctx, s, tmp, mom_half, st)) != VL_OK) return r;
         {
-            Timed tm(ctx, VL_T_FIELDS, st);
-            VL_HIP(vl::launch_poisson(mom_half, nx, L, c.sp[0].q, ctx->dft, S->fields, st));
+            // the field at t+1/2 is solved for inside the velocity sweep
+            Timed tm(ctx, VL_T_PFC_V, st);
+            VL_HIP((vl::launch_pfc_v1<T>(tmp, tmp, nx, sp.nv[0], S->fields, mom_half, ctx->green, sp.q,
+                                         sp.q / sp.m * dt / dv_of(sp, 0), max_in(ctx, 1, s), max_to(ctx, 2, s), st)));
         }
-        if ((r = advect_v_typed<T>(ctx, s, tmp, tmp, S->fields, nullptr, dt, max_in(ctx, 1, s), max_to(ctx, 2, s),
-                                   st)) != VL_OK)
-            return r;
         if ((r = advect_x_typed<T>(ctx, s, tmp, f, 0.5 * dt, max_in(ctx, 2, s), c.fit ? kNoMax : max_to(ctx, 0, s),
                                    st)) != VL_OK)
             return r;
         if ((r = moments_typed<T>(ctx, s, f, S->mom_pre[s], st)) != VL_OK) return r;
         if (c.fit) {
             {
-                Timed tm(ctx, VL_T_FIELDS, st);
-                VL_HIP(vl::launch_poisson(S->mom_post[s], nx, L, c.sp[0].q, ctx->dft, E_t, st));
-                VL_HIP(vl::launch_poisson(S->mom_pre[s], nx, L, c.sp[0].q, ctx->dft, E_t1, st));
-                VL_HIP(vl::launch_axpby(E_t, E_t1, 0.5, 0.5, E_th, nx, st));
+                // the stage fields are solved for inside the fluid step
+                Timed tm(ctx, VL_T_FLUID, st);
+                VL_HIP(vl::launch_fluid_rk3_1v(S->U[s], Unew, S->mom_post[s], S->mom_pre[s], nullptr, nullptr, nullptr,
+                                               ctx->green, dt, nx, sp.q, sp.m, dx_of(c), nullptr, st));
             }
-            if ((r = fluid_step_impl(ctx, s, S->U[s], S->mom_post[s], S->mom_pre[s], E_t, nullptr, E_t1, nullptr, E_th,
-                                     nullptr, dt, fwork, st)) != VL_OK)
-                return r;
-            if ((r = fit_typed<T>(ctx, s, f, f, S->mom_pre[s], S->U[s], S->mom_post[s], S->counters, max_to(ctx, 0, s),
-                                  st)) != VL_OK)
-                return r;
+            Timed tm(ctx, VL_T_FIT, st);
+            VL_HIP((vl::launch_fit1<T>(f, f, S->mom_pre[s], Unew, S->U[s], S->mom_post[s], S->counters, ctx->cells,
+                                       sp.nv[0], sp.v_lo[0], dv_of(sp, 0), sp.m, max_to(ctx, 0, s), st)));
         } else {
             Timed tm(ctx, VL_T_COPY, st);
             VL_HIP(hipMemcpyAsync(S->mom_post[s], S->mom_pre[s], (size_t)nx * 4 * sizeof(double),
@@ -628,7 +627,7 @@ vl_status fit_noalloc_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const dou
     const vl_config& c = ctx->cfg;
     const vl_species& sc = c.sp[s];
     if (c.dim_v == 1) {
-        VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, sc.nv[0], sc.v_lo[0],
+        VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, U, mom_post, counters, ctx->cells, sc.nv[0], sc.v_lo[0],
                                    dv_of(sc, 0), sc.m, kNoMax, st)));
         return VL_OK;
     }
@@ -753,7 +752,6 @@ vl_status vl_destroy(vl_ctx* ctx) {
     for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
     if (ctx->slots) (void)hipFree(ctx->slots);
     if (ctx->fit_scratch) (void)hipFree(ctx->fit_scratch);
-    if (ctx->bpart[0]) (void)hipFree(ctx->bpart[0]);
     delete ctx;
     return VL_OK;
 }
@@ -842,8 +840,7 @@ vl_status vl_poisson(vl_ctx* ctx, const double* mom, double* E, vl_stream stream
     if (!mom || !E) return fail(ctx, VL_EINVAL, "null argument");
     vl_status r;
     if ((r = ensure_device(ctx)) != VL_OK) return r;
-    VL_HIP(vl::launch_poisson(mom, ctx->cfg.nx, ctx->cfg.x_hi - ctx->cfg.x_lo, ctx->cfg.sp[0].q, ctx->dft, E,
-                              (hipStream_t)stream));
+    VL_HIP(vl::launch_poisson(mom, ctx->cfg.nx, ctx->cfg.sp[0].q, ctx->green, E, (hipStream_t)stream));
     return VL_OK;
 }
 

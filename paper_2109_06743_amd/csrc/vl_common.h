@@ -275,6 +275,63 @@ __device__ __forceinline__ void block_sum(double (&v)[N], double* red) {
     __syncthreads();
 }
 
+// 1X1V Poisson solve by convolution with the solver's Green's function
+// (poisson_green): E_i = q sum_j (n_j - n_i) g[(i - j) mod N].  g is odd with
+// zero sum, so taking n_i off changes nothing but the rounding.  A 256-thread
+// block gives E at the 64 cells first .. first + 63 (mod N) for NF density
+// arrays mom[f][4 j]: lane = cell, wave = every fourth j; densities and the
+// window of g go through shared memory kPoisChunk sources at a time.  Result
+// in L.e[f][lane], visible to the block.
+constexpr int kPoisChunk = 256;
+template <int NF>
+struct PoissonLds {
+    double n[NF][kPoisChunk];
+    double g[kPoisChunk + 64];
+    double red[4][NF][64];
+    double e[NF][64];
+};
+template <int NF>
+__device__ __forceinline__ void poisson_tile(const double* const (&mom)[NF], int N, const double* __restrict__ g,
+                                             int first, double q, PoissonLds<NF>& L) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int i = (int)((((long long)first + lane) % N + N) % N);
+    const int base = (first % N + N) % N;
+    double own[NF], acc[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        own[f] = mom[f][4ll * i];
+        acc[f] = 0.0;
+    }
+    for (int j0 = 0; j0 < N; j0 += kPoisChunk) {
+        const int cnt = N - j0 < kPoisChunk ? N - j0 : kPoisChunk;
+        __syncthreads();
+        if (tid < cnt) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) L.n[f][tid] = mom[f][4ll * (j0 + tid)];
+        }
+        // L.g[k] = g[(first - j0 - (kPoisChunk - 1) + k) mod N]
+        for (int k = tid; k < kPoisChunk + 64; k += 256)
+            L.g[k] = g[(((long long)base - j0 - (kPoisChunk - 1) + k) % N + N) % N];
+        __syncthreads();
+#pragma unroll 4
+        for (int j = w; j < cnt; j += 4) {
+            const double gg = L.g[lane - j + kPoisChunk - 1];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) acc[f] = fma(L.n[f][j] - own[f], gg, acc[f]);
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) L.red[w][f][lane] = acc[f];
+    __syncthreads();
+    if (w < NF) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s += L.red[k][w][lane];
+        L.e[w][lane] = q * s;
+    }
+    __syncthreads();
+}
+
 // PFC partial flux phi(j, a) of the limited parabola of cell j within a cell
 // widths of its downwind face.  fm, f0, fp: upwind neighbour, cell, downwind
 // neighbour.  c1 = (1-a)(2-a)/6, c2 = (1-a)(1+a)/6.  The limiter is the

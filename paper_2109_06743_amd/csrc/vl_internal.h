@@ -44,9 +44,11 @@ struct MaxSink {
 template <class T>
 hipError_t launch_pfc_x(const T* fin, T* fout, int rows, int nx, long long Nv, int inner, double vx_lo, double dvx,
                         double tau_dx, MaxRef finf, const MaxSink& sink, hipStream_t st);
+// g (the Poisson table) set: E is formed from the densities of mom and stored
+// to E; null: E is read.
 template <class T>
-hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, const double* E, double qm_tau_dv, MaxRef finf,
-                         const MaxSink& sink, hipStream_t st);
+hipError_t launch_pfc_v1(const T* fin, T* fout, int nx, int nv, double* E, const double* mom, const double* g,
+                         double q, double qm_tau_dv, MaxRef finf, const MaxSink& sink, hipStream_t st);
 struct V3Params {
     int nvx, nvy, nvz;
     double lo[3], dv[3], inv_dv[3];
@@ -127,11 +129,13 @@ template <class T>
 hipError_t launch_fit_fold(int ns, const MaxSink* sinks, unsigned* const* clips, void* counters, long long cells,
                            hipStream_t st);
 template <class T>
-hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
+hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, const double* Uin, double* U, double* mom_post, void* counters,
                        long long cells, int nv, double vlo, double dv, double m, const MaxSink& sink,
                        hipStream_t st);
 
-hipError_t launch_poisson(const double* mom, int N, double L, double q, double* ab, double* E, hipStream_t st);
+// Green's function of the 1X1V Poisson solver, g[N], and the solve with it.
+hipError_t launch_poisson_green(int N, double L, double* g, hipStream_t st);
+hipError_t launch_poisson(const double* mom, int N, double q, const double* g, double* E, hipStream_t st);
 // mom[s]: per-cell records of mstride doubles holding n u at offsets 1..3
 // (raw moments: 20; fluid state: 10).
 hipError_t launch_maxwell_half(double* yee, int nx, int ny, const double* const* mom, const double* q, int ns,
@@ -172,9 +176,11 @@ hipError_t launch_fluid_rk3_3v(double* U, const double* mom_t, const double* mom
                                const double* B_t, const double* E_t1, const double* B_t1, const double* E_th,
                                const double* B_th, double dt, int nx, int ny, double q, double m, double dx,
                                double dy, double* work, hipStream_t st, int per = 0);
-hipError_t launch_fluid_rk3_1v(double* U, const double* mom_t, const double* mom_t1, const double* E_t,
-                               const double* E_t1, const double* E_th, double dt, int nx, double q, double m,
-                               double dx, double* work, hipStream_t st);
+// U -> Uout (which may be U; work: 3 nx doubles, used then).  g set: the stage
+// fields are the Poisson solves of mom_t, mom_t1 and their mean.
+hipError_t launch_fluid_rk3_1v(double* U, double* Uout, const double* mom_t, const double* mom_t1, const double* E_t,
+                               const double* E_t1, const double* E_th, const double* g, double dt, int nx, double q,
+                               double m, double dx, double* work, hipStream_t st);
 
 // One SSP-RK3 stage of the 3V fluid: Uo = a Un + b (Us + dt L(Us)), third
 // moment wa QA + wb QB (raw-moment layout, entries 10..19 of 20 per cell).
