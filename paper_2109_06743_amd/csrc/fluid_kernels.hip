@@ -4,15 +4,20 @@
 // point values at the faces, local Lax-Friedrichs flux with speed
 // |u_d| + sqrt(3 p_dd / (m n)), and SSP-RK3 (Shu-Osher) in time.
 //
-// Face fluxes are computed once per face (both directions in one launch, one
-// thread per face and component), then a per-cell kernel forms
-// L(U) = -div H + S(U, E, B) and the RK stage combination
+// One launch per RK stage does all of it for every species: third moment (from
+// f, or a closure of the stage state), face fluxes of both directions,
+// L(U) = -div H + S(U, E, B) and the stage combination
 // U_out = a U_n + b (U_s + dt L).
 //
 // Component orders: U = (n, nu_x, nu_y, nu_z, Pxx, Pxy, Pxz, Pyy, Pyz, Pzz);
 // Qcal (from the raw moment vector, offset 10) = (xxx, xxy, xxz, xyy, xyz,
 // xzz, yyy, yyz, yzz, zzz).  1V: U = (n, nu, P), Qcal = raw moment 3.
 #include "vl_internal.h"
+
+// Fuse multiply-adds as the expressions are written, not as each instantiation
+// happens to be optimised: a network closure that falls back gives the kinetic
+// step bit for bit.
+#pragma clang fp contract(on)
 
 namespace vl {
 
@@ -23,43 +28,29 @@ constexpr double kCwenoEps = 1e-6;
 // and centred polynomials evaluated at +-h/2 are
 //   P_L = b -+ (b - a)/2,  P_R = b -+ (c - b)/2,  P_C = b + d2/6 -+ (c - a)/4,
 // d2 = c - 2b + a, weighted with (1/4, 1/2, 1/4) / (eps + IS)^2, normalised.
-// With D = (eps + IS)^2 the normalised weights are
-//   w_L = Dc Dr / S, w_C = 2 Dl Dr / S, w_R = Dl Dc / S,
-//   S = Dc Dr + 2 Dl Dr + Dl Dc
-// (one division), and since they sum to one the point values are b plus the
-// weighted corrections (a constant state reconstructs to itself exactly).
+// With e = eps + IS the weights are, times a common factor, tl = (ec er)^2,
+// 2 tc = 2 (el er)^2 and tr = (el ec)^2, their sum S = tl + 2 tc + tr (one
+// reciprocal); since they sum to one the point values are b plus the weighted
+// corrections (a constant state reconstructs to itself exactly):
+//   b + h (2/3 tc d2 +- (tl dl + tc dc + tr dr)),  h = 1 / (2 S).
+// 31 operations and the hardware's estimate of 1/S, refined once to third
+// order; the reconstructions are two thirds of the stage kernel's arithmetic.
 __device__ __forceinline__ void cweno(double a, double b, double c, double& left, double& right) {
-    const double dl = b - a, dr = c - b, d2 = c - 2.0 * b + a, dc = c - a;
-    const double el = kCwenoEps + dl * dl, er = kCwenoEps + dr * dr;
-    const double ec = kCwenoEps + (13.0 / 3.0) * d2 * d2 + 0.25 * dc * dc;
-    const double Dl = el * el, Dc = ec * ec, Dr = er * er;
-    const double tl = Dc * Dr, tc = 2.0 * Dl * Dr, tr = Dl * Dc;
-    const double inv = 1.0 / (tl + tc + tr);
-    const double wl = tl * inv, wc = tc * inv, wr = tr * inv;
-    const double side = 0.5 * (wl * dl + wr * dr) + 0.25 * wc * dc;   // odd part
-    const double even = wc * (d2 * (1.0 / 6.0));                         // even part
-    right = b + (even + side);
-    left = b + (even - side);
-}
-
-// index helpers for the symmetric second and third moments
-__device__ __forceinline__ int p_index(int a, int b) {
-    if (a > b) { int t = a; a = b; b = t; }
-    return a == 0 ? b : (a == 1 ? 2 + b : 5);
-}
-__device__ __forceinline__ int q_index(int a, int b, int c) {
-    // sort a <= b <= c
-    if (a > b) { int t = a; a = b; b = t; }
-    if (b > c) { int t = b; b = c; c = t; }
-    if (a > b) { int t = a; a = b; b = t; }
-    // (0,0,0)0 (0,0,1)1 (0,0,2)2 (0,1,1)3 (0,1,2)4 (0,2,2)5 (1,1,1)6 (1,1,2)7 (1,2,2)8 (2,2,2)9
-    if (a == 0) {
-        if (b == 0) return c;
-        if (b == 1) return 2 + c;
-        return 5;
-    }
-    if (a == 1) return b == 1 ? 5 + c : 8;
-    return 9;
+    const double dl = b - a, dr = c - b, d2 = dr - dl, dc = dr + dl;
+    const double el = fma(dl, dl, kCwenoEps), er = fma(dr, dr, kCwenoEps);
+    const double ec = fma(13.0 / 3.0, d2 * d2, fma(0.25, dc * dc, kCwenoEps));
+    double tl = ec * er, tc = el * er, tr = el * ec;
+    tl *= tl;
+    tc *= tc;
+    tr *= tr;
+    const double sum = fma(2.0, tc, tl + tr);
+    const double r = __builtin_amdgcn_rcp(sum);
+    const double e = fma(-sum, r, 1.0);
+    const double h = 0.5 * fma(r, fma(e, e, e), r);
+    const double side = h * fma(tl, dl, fma(tc, dc, tr * dr));       // odd part
+    const double even = fma(h, ((2.0 / 3.0) * tc) * d2, b);          // even part
+    right = even + side;
+    left = even - side;
 }
 
 // y-parity (+1/-1) of U and Qcal components under y -> -y
@@ -70,286 +61,379 @@ __device__ __forceinline__ double par_q(int k) {
     return (k == 1 || k == 4 || k == 6 || k == 8) ? -1.0 : 1.0;  // xxy, xyz, yyy, yzz
 }
 
-struct FluidArgs {
-    int nx, ny;
-    double m, q;
-    double idx, idy;      // 1/dx, 1/dy
-    int per;              // 1: periodic y, 0: reflecting walls
-};
-
-// Both face directions in one launch.  An x tile is kXTile consecutive faces
-// i+1/2 of one cell row; a y tile is kYRows consecutive face rows jh-1/2 of
-// kYCols adjacent columns.  A block stages the cell values (U and Qcal,
-// wrapped in x, mirrored at the y walls) that its faces need in shared
-// memory, forms the CWENO-3 point values once per cell and component, the two
-// wave speeds once per face, then the 10 flux components of each face.
-// Blocks [0, nbx) are x tiles, the rest y tiles.
-constexpr int kXTile = 32;
-constexpr int kYRows = 8, kYCols = 4;
-constexpr int kFaceThreads = 256;   // eight blocks per CU: a launch is about one round
-constexpr int kStageCells = (kYRows + 3) * kYCols;   // >= kXTile + 3
-constexpr int kRecCells = (kYRows + 1) * kYCols;     // >= kXTile + 1
-static_assert(kXTile + 3 <= kStageCells && kXTile + 1 <= kRecCells, "x tile must fit the staging arrays");
-static_assert(kYRows * kYCols == kXTile, "both tiles hold the same number of faces");
-
-__device__ __forceinline__ double stage_comp(const double* U, const double* QA, const double* QB, double wa,
-                                             double wb, int j, int i, int k, const FluidArgs& A) {
-    bool mir = false;
-    if (A.per) {
-        while (j < 0) j += A.ny;
-        while (j >= A.ny) j -= A.ny;
-    } else {
-        if (j < 0) { j = -1 - j; mir = true; }
-        if (j >= A.ny) { j = 2 * A.ny - 1 - j; mir = true; }
-    }
-    while (i < 0) i += A.nx;
-    while (i >= A.nx) i -= A.nx;
-    const long long c = (long long)j * A.nx + i;
-    double v;
-    if (k < 10) {
-        v = U[c * 10 + k];
-        if (mir) v *= par_u(k);
-    } else {
-        v = wa * QA[c * 20 + k] + (wb != 0.0 ? wb * QB[c * 20 + k] : 0.0);
-        if (mir) v *= par_q(k - 10);
-    }
-    return v;
+// Value of lane + 1 (kUp) or lane - 1 of the same 16-lane row.
+template <bool kUp>
+__device__ __forceinline__ double row_next(double v) {
+    constexpr int ctrl = kUp ? 0x101 : 0x111;               // row_shl:1, row_shr:1
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, ctrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Species sp = blockIdx.y of the set.
-__global__ void __launch_bounds__(kFaceThreads)
-faces3_kernel(FluidSet S, double wa, double wb, FluidArgs A, int nbx_row, int nbx, int nby_col) {
-    const int sp = blockIdx.y;
-    const double* __restrict__ U = S.Us[sp];
-    const double* __restrict__ QA = S.QA[sp];
-    const double* __restrict__ QB = S.QB[sp];
-    double* __restrict__ Hx = S.Hx[sp];
-    double* __restrict__ Hy = S.Hy[sp];
-    A.m = S.m[sp];
-    __shared__ double raw[kStageCells][20];
-    __shared__ double lo[kRecCells][20], hi[kRecCells][20];   // point values at a cell's lower / upper face
-    __shared__ double spd[2][kXTile];
-    const bool yface = (int)blockIdx.x >= nbx;
-    const int b = yface ? (int)blockIdx.x - nbx : (int)blockIdx.x;
-    const int row0 = yface ? (b / nby_col) * kYRows : b / nbx_row;
-    const int col0 = yface ? (b % nby_col) * kYCols : (b % nbx_row) * kXTile;
-    const int nstage = yface ? kStageCells : kXTile + 3;
-    const int nrec = yface ? kRecCells : kXTile + 1;
-    // Thread t < 240 handles component k = t % 20 of cells t / 20, + 12, + 24, ...
-    // in the staging and reconstruction loops (no index division per element).
-    constexpr int kCellsPerPass = kFaceThreads / 20;
-    const int kc = (int)threadIdx.x % 20, c0 = (int)threadIdx.x / 20;
-    // staged cell l: x tile (row0, col0 - 1 + l); y tile (row0 - 2 + l / kYCols, col0 + l % kYCols)
-    for (int l = c0 < kCellsPerPass ? c0 : nstage; l < nstage; l += kCellsPerPass) {
-        const int k = kc;
-        const int j = yface ? row0 - 2 + l / kYCols : row0;
-        const int i = yface ? col0 + l % kYCols : col0 - 1 + l;
-        // y tiles: rows past ny + 1 and columns past nx feed no valid face
-        const bool need = !yface || (j <= A.ny + 1 && i < A.nx);
-        raw[l][k] = need ? stage_comp(U, QA, QB, wa, wb, j, i, k, A) : 0.0;
-    }
-    __syncthreads();
-    // reconstructed cell r: x tile (row0, col0 + r); y tile (row0 - 1 + r / kYCols, col0 + r % kYCols)
-    const int sstep = yface ? kYCols : 1;
-    for (int r = c0 < kCellsPerPass ? c0 : nrec; r < nrec; r += kCellsPerPass) {
-        const int k = kc;
-        double l, h;
-        cweno(raw[r][k], raw[r + sstep][k], raw[r + 2 * sstep][k], l, h);
-        lo[r][k] = l;
-        hi[r][k] = h;
-    }
-    __syncthreads();
-    // face f: x tile i+1/2 with i = col0 + f of row0; y tile face row jh = row0 + f / kYCols at column
-    // col0 + f % kYCols.  Minus side (cell i, or row jh - 1): r = f; plus side: r = f + sstep.
-    const int d = yface ? 1 : 0;
-    auto face_ok = [&](int f) {
-        return yface ? (row0 + f / kYCols <= A.ny && col0 + f % kYCols < A.nx) : (col0 + f < A.nx);
-    };
-    for (int t = threadIdx.x; t < 2 * kXTile; t += kFaceThreads) {
-        const int f = t % kXTile, side = t / kXTile;
-        if (face_ok(f)) {
-            const double* V = side ? lo[f + sstep] : hi[f];
-            const double n = V[0];
-            const double u = V[1 + d] / n;
-            const double p = V[4 + p_index(d, d)] - A.m * n * u * u;
-            spd[side][f] = fabs(u) + sqrt(fmax(3.0 * p / (A.m * n), 0.0));
-        }
-    }
-    __syncthreads();
-    // thread t < 250: flux component k = t % 10 of faces t / 10 and t / 10 + 25
-    const int k = (int)threadIdx.x % 10;
-    // flux component k: n -> nu_d, nu_i -> P_id / m, P_ab -> Qcal_abd
-    int src;
-    double sc = 1.0;
-    if (k == 0) {
-        src = 1 + d;
-    } else if (k < 4) {
-        src = 4 + p_index(k - 1, d);
-        sc = 1.0 / A.m;
-    } else {
-        const int ia[6] = {0, 0, 0, 1, 1, 2}, ib[6] = {0, 1, 2, 1, 2, 2};
-        src = 10 + q_index(ia[k - 4], ib[k - 4], d);
-    }
-    constexpr int kFacesPerPass = kFaceThreads / 10;
-    for (int f = (int)threadIdx.x < 10 * kFacesPerPass ? (int)threadIdx.x / 10 : kXTile; f < kXTile;
-         f += kFacesPerPass) {
-        if (!face_ok(f)) continue;
-        const double* Lm = hi[f];
-        const double* Lp = lo[f + sstep];
-        const double a = fmax(spd[0][f], spd[1][f]);
-        const double Fm = Lm[src] * sc, Fp = Lp[src] * sc;
-        long long h;
-        if (yface) h = (long long)(row0 + f / kYCols) * A.nx + col0 + f % kYCols;
-        else h = (long long)row0 * A.nx + col0 + f;
-        (yface ? Hy : Hx)[h * 10 + k] = 0.5 * (Fp + Fm) - 0.5 * a * (Lp[k] - Lm[k]);
+// One RK stage of the ten-moment fluid.  A 512-thread block updates kRows x
+// kCols cells; its first half takes the x direction and the sources, its
+// second half the y direction:
+// 1. U (first half) and the kinetic third moment (second half) of the cells
+//    and two more on each side go to shared memory, one array per component,
+//    in runs of 180 consecutive doubles per row (wrapped in x, mirrored or
+//    wrapped in y); with a closure the block forms the third moments there.
+// 2. x: 16 lanes per row, the outer two for the neighbour cells; each lane
+//    reconstructs its cell (16 components: U and the six third moments with an
+//    x index), takes the next cell's lower point values from the next lane and
+//    forms the flux through its upper face; the flux through its lower face is
+//    the previous lane's.
+// 3. y: the same for kRows + 2 rows, through shared memory (which no longer
+//    holds the cells).
+// 4. The second half adds both and the block writes rows of 140 doubles.
+// The kernel is bound by its FP64 instructions (two thirds of them in cweno).
+// Two kernels per stage used to store the fluxes (160 B a cell) and read them
+// back from 80-byte records, reconstruct all 20 components per direction and,
+// with a closure, read and write a third moment (2 x 160 B) and an Eq. 5
+// source first: 125 + 63 + 25 + 22 us a stage at 1024 x 512, one species; this
+// takes 65 (Eq. 5), and 10.9 us instead of 6.6 + 4.1 on 32 x 16 cells (both
+// species).  One thread per cell of a 16 x 16 square for both directions took
+// 71 us there and 15.5 us on 32 x 16 cells (the length of its chain).
+enum { kThirdKinetic = 0, kThirdZero = 1, kThirdNet = 2 };
+constexpr int kRows = 16, kCols = 14;
+constexpr int kHaloR = kRows + 4, kHaloC = kCols + 4;
+constexpr int kHaloCells = kHaloR * kHaloC;
+constexpr int kStageComps = 19;               // U and Qcal without zzz, which no flux takes
+constexpr int kXLanes = kRows * (kCols + 2), kYLanes = (kRows + 2) * kCols;
+constexpr int kHalf = 256;                    // threads per direction
+constexpr int kTempCells = (kRows + 2) * (kCols + 2);
+constexpr int kXStride = kXLanes + 1, kYStride = kYLanes + 1;    // of the exchange arrays
+static_assert(kXLanes <= kHalf && kYLanes <= kHalf && kHaloC * 10 <= kHalf, "one pass each");
+static_assert(17 * kYStride <= kStageComps * kHaloCells, "the y exchange fits the cells' memory");
+static_assert(kRows * kCols * 10 <= 10 * kYStride, "the results fit the y fluxes' memory");
+static_assert(10 * (kXStride + kYStride) <= kStageComps * kHaloCells, "fluxes and sums fit the cells' memory");
+
+struct FluidArgs {
+    int nx, ny;
+    double idx, idy;      // 1/dx, 1/dy
+    double a, b, dt;      // stage: Uo = a Un + b (Us + dt L)
+    double wa, wb;        // kinetic third moment wa QA + wb QB
+    const double* E;      // [cells][3]
+    const double* B;
+    int per;              // 1: periodic y, 0: reflecting walls
+    int tx, ty;           // tiles along x, y
+};
+
+// Third moment with heat flux q (Qcal of the zero-heat-flux state plus q):
+// u_a P_bc + u_b P_ac + u_c P_ab - 2 m n u_a u_b u_c, component k of nine.
+__device__ __forceinline__ void third_moment(const double (&U)[10], double m, double (&Q)[9]) {
+    const double in = 1.0 / U[0];
+    const double u[3] = {U[1] * in, U[2] * in, U[3] * in};
+    const double mn2 = 2.0 * m * U[0];
+    const double P[3][3] = {{U[4], U[5], U[6]}, {U[5], U[7], U[8]}, {U[6], U[8], U[9]}};
+    const int ta[9] = {0, 0, 0, 0, 0, 0, 1, 1, 1}, tb[9] = {0, 0, 0, 1, 1, 2, 1, 1, 2}, tc[9] = {0, 1, 2, 1, 2, 2, 1, 2, 2};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const int x = ta[k], y = tb[k], z = tc[k];
+        Q[k] = (u[x] * P[y][z] + u[y] * P[x][z] + u[z] * P[x][y]) - mn2 * u[x] * u[y] * u[z];
     }
 }
 
 // Temperature tensor T = (P - m n u u) / n of a fluid record (PAIRS order).
-__device__ __forceinline__ void temperature6(const double* V, double m, double* T) {
-    const double n = V[0];
-    const double u[3] = {V[1] / n, V[2] / n, V[3] / n};
+__device__ __forceinline__ void temperature6(const double (&V)[10], double m, double (&T)[6]) {
+    const double in = 1.0 / V[0];
+    const double u[3] = {V[1] * in, V[2] * in, V[3] * in};
     const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 2};
 #pragma unroll
-    for (int k = 0; k < 6; ++k) T[k] = (V[4 + k] - m * n * u[pa[k]] * u[pb[k]]) / n;
+    for (int k = 0; k < 6; ++k) T[k] = V[4 + k] * in - m * u[pa[k]] * u[pb[k]];
 }
 
-// Temperature of cell (j, i) with x periodic and the y walls mirrored (the
-// mirrored record has n u_y, P_xy, P_yz negated, so T_xy and T_yz flip).
-__device__ __forceinline__ void temperature_at(const double* __restrict__ U, int j, int i, const FluidArgs& A,
-                                               double* T) {
-    bool mir = false;
-    if (A.per) {
-        if (j < 0) j += A.ny;
-        if (j >= A.ny) j -= A.ny;
-    } else {
-        if (j < 0) { j = -1 - j; mir = true; }
-        if (j >= A.ny) { j = 2 * A.ny - 1 - j; mir = true; }
+// Face fluxes of one direction: W components 0..9 are U, 10..15 the third
+// moments of the second-moment fluxes in PAIRS order; src[k] the component
+// whose value is flux k (n -> nu_d, nu_i -> P_id / m, P_ab -> Qcal_abd).
+template <int D>
+struct FluxMap {
+    // raw component of W[10 + k]: Qcal_abd of the pair ab
+    static __device__ __forceinline__ constexpr int third(int k) {
+        constexpr int x[6] = {0, 1, 2, 3, 4, 5}, y[6] = {1, 3, 4, 6, 7, 8};
+        return 10 + (D == 0 ? x[k] : y[k]);
     }
-    if (i < 0) i += A.nx;
-    if (i >= A.nx) i -= A.nx;
-    const long long c = (long long)j * A.nx + i;
-    double V[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) V[k] = U[c * 10 + k] * (mir ? par_u(k) : 1.0);
-    temperature6(V, A.m, T);
+    static __device__ __forceinline__ constexpr int src(int k) {
+        constexpr int x[10] = {1, 4, 5, 6, 10, 11, 12, 13, 14, 15};
+        constexpr int y[10] = {2, 5, 7, 8, 10, 11, 12, 13, 14, 15};
+        return D == 0 ? x[k] : y[k];
+    }
+    static constexpr int nu = 1 + D, pdd = D == 0 ? 4 : 7;
+};
+
+template <int D>
+__device__ __forceinline__ double wave_speed(const double (&W)[16], double m) {
+    const double in = 1.0 / W[0];
+    const double u = W[FluxMap<D>::nu] * in;
+    const double p = W[FluxMap<D>::pdd] - m * W[FluxMap<D>::nu] * u;
+    return fabs(u) + sqrt(fmax(3.0 * p * in / m, 0.0));
 }
 
-// Temperature-gradient closure of Eq. 5 as a source of the second moment:
-// S = -div Q = gchi n v_t lap T (gchi = chi / k0), lap by central second
-// differences, x periodic, y walls mirrored; S[cells][6] in PAIRS order.
-// Species blockIdx.z of the set; species without the closure are skipped.
-__global__ void closure_source3_kernel(FluidSet Set, FluidArgs A) {
-    const int sp = blockIdx.z;
-    const double gchi = Set.gchi[sp];
-    const double* __restrict__ Us = Set.Us[sp];
-    double* __restrict__ S = Set.Sg[sp];
-    A.m = Set.m[sp];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y;
-    if (i >= A.nx || gchi == 0.0) return;
-    double Tc[6], T1[6], T2[6], lx[6];
-    temperature_at(Us, j, i, A, Tc);
-    temperature_at(Us, j, i + 1, A, T1);
-    temperature_at(Us, j, i - 1, A, T2);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) lx[k] = (T1[k] - 2.0 * Tc[k]) + T2[k];
-    temperature_at(Us, j + 1, i, A, T1);
-    temperature_at(Us, j - 1, i, A, T2);
-    const long long c = (long long)j * A.nx + i;
-    const double vt = sqrt((Tc[0] + Tc[3] + Tc[5]) / (3.0 * A.m));
-    const double w = gchi * (Us[c * 10] * vt);
-    const double ix2 = A.idx * A.idx, iy2 = A.idy * A.idy;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) S[c * 6 + k] = w * (lx[k] * ix2 + ((T1[k] - 2.0 * Tc[k]) + T2[k]) * iy2);
+// Local Lax-Friedrichs flux k between the point values Wm (below) and Wp.
+template <int D>
+__device__ __forceinline__ double face_flux(const double (&Wm)[16], const double (&Wp)[16], int k, double a, double im) {
+    const double sum = Wp[FluxMap<D>::src(k)] + Wm[FluxMap<D>::src(k)];
+    return (k >= 1 && k < 4 ? 0.5 * im : 0.5) * sum - 0.5 * a * (Wp[k] - Wm[k]);
 }
 
-// U_out = a U_n + b (U_s + dt L(U_s)); U_out may alias U_n (each cell reads
-// only its own U_n entry) but not U_s.  Where the species has the Eq. 5
-// closure, Sg is an extra source of the second moment, [cells][6].  Species
-// blockIdx.z of the set.
-__global__ void update3_kernel(FluidSet S, const double* __restrict__ E, const double* __restrict__ B, double a,
-                               double b, double dt, FluidArgs A) {
-    const int sp = blockIdx.z;
+template <int THIRD>
+__global__ void __launch_bounds__(2 * kHalf) __attribute__((amdgpu_waves_per_eu(4)))
+fluid3_stage_kernel(FluidSet S, FluidArgs A) {
+    __shared__ double raw[kStageComps][kHaloCells];
+    double* const pool = &raw[0][0];
+    double* const part = pool + 10 * kYStride;   // x half's sums, next to the y fluxes
+    __shared__ double temp[THIRD == kThirdZero ? 6 * kTempCells : 1];
+    const unsigned per_sp = (unsigned)(A.tx * A.ty);
+    const unsigned w = xcd_work_index(blockIdx.x, gridDim.x);
+    const int sp = (int)(w / per_sp);
+    const int i0 = (int)(w % per_sp % (unsigned)A.tx) * kCols, j0 = (int)(w % per_sp / (unsigned)A.tx) * kRows;
     const double* __restrict__ Us = S.Us[sp];
-    const double* Un = S.Un[sp];
-    double* Uout = S.Uo[sp];
-    const double* __restrict__ Hx = S.Hx[sp];
-    const double* __restrict__ Hy = S.Hy[sp];
-    const double* __restrict__ Sg = S.gchi[sp] != 0.0 ? S.Sg[sp] : nullptr;
-    A.m = S.m[sp];
-    A.q = S.q[sp];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y;
-    if (i >= A.nx) return;
-    const int im = (i == 0) ? A.nx - 1 : i - 1;
-    const long long c = (long long)j * A.nx + i;
-    double u[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) u[k] = Us[c * 10 + k];
-    const double ex = E[c * 3], ey = E[c * 3 + 1], ez = E[c * 3 + 2];
-    const double bx = B[c * 3], by = B[c * 3 + 1], bz = B[c * 3 + 2];
-    const double qm = A.q / A.m;
-    double L[10];
-    // sources: momentum (q/m)(n E + nu x B)
-    L[0] = 0.0;
-    L[1] = qm * (u[0] * ex + u[2] * bz - u[3] * by);
-    L[2] = qm * (u[0] * ey + u[3] * bx - u[1] * bz);
-    L[3] = qm * (u[0] * ez + u[1] * by - u[2] * bx);
-    // second moment: q (nu_i E_j + nu_j E_i) + (q/m)(eps_jkl P_ik B_l + eps_ikl P_jk B_l)
-    double P[3][3];
-    P[0][0] = u[4]; P[0][1] = P[1][0] = u[5]; P[0][2] = P[2][0] = u[6];
-    P[1][1] = u[7]; P[1][2] = P[2][1] = u[8]; P[2][2] = u[9];
-    const double Ev[3] = {ex, ey, ez}, Bv[3] = {bx, by, bz}, nu[3] = {u[1], u[2], u[3]};
-    // (P x B)_{ij} = eps_jkl P_ik B_l: row i of P crossed with B
-    double PxB[3][3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        PxB[r][0] = P[r][1] * Bv[2] - P[r][2] * Bv[1];
-        PxB[r][1] = P[r][2] * Bv[0] - P[r][0] * Bv[2];
-        PxB[r][2] = P[r][0] * Bv[1] - P[r][1] * Bv[0];
-    }
-    const int ia[6] = {0, 0, 0, 1, 1, 2}, ib[6] = {0, 1, 2, 1, 2, 2};
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const int p = ia[k], r = ib[k];
-        L[4 + k] = A.q * (nu[p] * Ev[r] + nu[r] * Ev[p]) + qm * (PxB[p][r] + PxB[r][p]);
-    }
-    const double* hxr = Hx + c * 10;
-    const double* hxl = Hx + ((long long)j * A.nx + im) * 10;
-    const double* hyt = Hy + ((long long)(j + 1) * A.nx + i) * 10;
-    const double* hyb = Hy + ((long long)j * A.nx + i) * 10;
-#pragma unroll
-    for (int k = 0; k < 10; ++k) L[k] -= (hxr[k] - hxl[k]) * A.idx + (hyt[k] - hyb[k]) * A.idy;
-    if (Sg) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) L[4 + k] += Sg[c * 6 + k];
-    }
-#pragma unroll
-    for (int k = 0; k < 10; ++k) {
-        const double s = u[k] + dt * L[k];
-        Uout[c * 10 + k] = (a != 0.0 ? a * Un[c * 10 + k] : 0.0) + b * s;
-    }
-}
+    const double m = S.m[sp], q = S.q[sp];
+    const int nx = A.nx, ny = A.ny;
+    const bool xhalf = threadIdx.x < kHalf;                 // wave-uniform
+    const int tid = threadIdx.x & (kHalf - 1);
 
-// Third moment of a fluid record with zero heat flux:
-// Qcal_abc = u_a P_bc + u_b P_ac + u_c P_ab - 2 m n u_a u_b u_c, written at
-// offsets 10..19 of 20-double records (the layout the face kernel reads).
-__global__ void qcal_q0_kernel(const double* __restrict__ U, long long cells, double m, double* __restrict__ qc) {
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells) return;
-    const double n = U[c * 10];
-    const double u[3] = {U[c * 10 + 1] / n, U[c * 10 + 2] / n, U[c * 10 + 3] / n};
-    double P[3][3];
-    const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 2};
+    // row of a halo row: itself, ~row where mirrored, kNoRow where no flux
+    // needs it (lane = halo row; the loops read it back per row)
+    constexpr int kNoRow = -0x7fffffff;
+    auto map_row = [&](int j) {
+        if (A.per) {
+            j %= ny;
+            return j < 0 ? j + ny : j;
+        }
+        if (j < 0) return ~(-1 - j);
+        if (j < ny) return j;
+        return j <= ny + 1 ? ~(2 * ny - 1 - j) : kNoRow;
+    };
+    auto source_of = [](int row) { return row == kNoRow ? 0 : (row < 0 ? ~row : row); };
+    auto col_of_i = [&](int i) {
+        i %= nx;
+        return i < 0 ? i + nx : i;
+    };
+    const int rows_v = map_row(j0 - 2 + (tid & 31));
+    const bool mirrored = !A.per && (j0 < 2 || j0 + kRows + 2 > ny);
+    // 1. cells and ring: all the loads of a thread in flight together
+    const bool kinetic = THIRD == kThirdKinetic || (THIRD == kThirdNet && S.fallback[sp] && *S.fallback[sp]);
+    if (tid < kHaloC * 10 && (xhalf || kinetic)) {
+        const int l = tid / 10, k = tid % 10;
+        const unsigned i = (unsigned)col_of_i(i0 - 2 + l);
+        double v[kHaloR];
+        if (xhalf) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) P[pa[k]][pb[k]] = P[pb[k]][pa[k]] = U[c * 10 + 4 + k];
-    const int ta[10] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 2}, tb[10] = {0, 0, 0, 1, 1, 2, 1, 1, 2, 2},
-              tc[10] = {0, 1, 2, 1, 2, 2, 1, 2, 2, 2};
+            for (int jj = 0; jj < kHaloR; ++jj) {
+                const double* row = Us + (size_t)source_of(__builtin_amdgcn_readlane(rows_v, jj)) * nx * 10;
+                v[jj] = row[i * 10u + (unsigned)k];
+            }
+            if (mirrored) {
+                const double su = par_u(k);
 #pragma unroll
-    for (int k = 0; k < 10; ++k) {
-        const int x = ta[k], y = tb[k], z = tc[k];
-        qc[c * 20 + 10 + k] = (u[x] * P[y][z] + u[y] * P[x][z] + u[z] * P[x][y]) - 2.0 * m * n * u[x] * u[y] * u[z];
+                for (int jj = 0; jj < kHaloR; ++jj)
+                    if (__builtin_amdgcn_readlane(rows_v, jj) < 0) v[jj] *= su;
+            }
+#pragma unroll
+            for (int jj = 0; jj < kHaloR; ++jj) raw[k][jj * kHaloC + l] = v[jj];
+        } else if (k < 9) {
+            const double* __restrict__ QA = S.QA[sp];
+            const double* __restrict__ QB = S.QB[sp];
+#pragma unroll
+            for (int jj = 0; jj < kHaloR; ++jj) {
+                const double* row = QA + (size_t)source_of(__builtin_amdgcn_readlane(rows_v, jj)) * nx * 20;
+                v[jj] = A.wa * row[i * 20u + 10u + (unsigned)k];
+            }
+            if (A.wb != 0.0) {
+#pragma unroll
+                for (int jj = 0; jj < kHaloR; ++jj) {
+                    const double* row = QB + (size_t)source_of(__builtin_amdgcn_readlane(rows_v, jj)) * nx * 20;
+                    v[jj] = fma(A.wb, row[i * 20u + 10u + (unsigned)k], v[jj]);
+                }
+            }
+            if (mirrored) {
+                const double sq = par_q(k);
+#pragma unroll
+                for (int jj = 0; jj < kHaloR; ++jj)
+                    if (__builtin_amdgcn_readlane(rows_v, jj) < 0) v[jj] *= sq;
+            }
+#pragma unroll
+            for (int jj = 0; jj < kHaloR; ++jj) raw[10 + k][jj * kHaloC + l] = v[jj];
+        }
+    }
+    __syncthreads();
+    if (THIRD != kThirdKinetic && !kinetic) {
+        // third moments of the cross of cells that fluxes need: kRows full rows,
+        // and two rows above and below without the outer columns
+        const int e = (int)threadIdx.x, f = e - kRows * kHaloC;
+        if (f < 4 * kCols) {
+            const int jj = f < 0 ? e / kHaloC + 2 : (f / kCols < 2 ? f / kCols : f / kCols + kRows);
+            const int l = f < 0 ? e % kHaloC : f % kCols + 2;
+            const int c = jj * kHaloC + l;
+            double V[10], Q[9];
+#pragma unroll
+            for (int k = 0; k < 10; ++k) V[k] = raw[k][c];
+            third_moment(V, m, Q);
+            if (THIRD == kThirdNet) {
+                const int row = map_row(j0 - 2 + jj);
+                const long long g = (long long)source_of(row) * nx + col_of_i(i0 - 2 + l);
+                const double sc = S.scale[sp][g];
+                const float* __restrict__ y = S.y[sp] + g * 16;
+#pragma unroll
+                for (int k = 0; k < 9; ++k) Q[k] += (row < 0 ? sc * par_q(k) : sc) * (double)y[k];
+            }
+#pragma unroll
+            for (int k = 0; k < 9; ++k) raw[10 + k][c] = Q[k];
+            if (THIRD == kThirdZero && l >= 1 && l <= kCols + 2 && jj >= 1 && jj <= kRows + 2) {
+                double T[6];
+                temperature6(V, m, T);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) temp[k * kTempCells + (jj - 1) * (kCols + 2) + l - 1] = T[k];
+            }
+        }
+        __syncthreads();
+    }
+    // reconstructions the scheduler may interleave (all 16 spill)
+    constexpr int kBatch = 4;
+    const double im = 1.0 / m;
+    if (xhalf) {
+        // 2. x
+        const int tx = tid & (kCols + 1), ty = tid / (kCols + 2);
+        const int r = (ty + 2) * kHaloC + tx + 1;
+        const int i = i0 - 1 + tx, j = j0 + ty;
+        const bool own = tx > 0 && tx <= kCols && i < nx && j < ny;
+        double u[10], L[10];
+        {
+            double lo[16], hi[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int c = k < 10 ? k : FluxMap<0>::third(k - 10);
+                cweno(raw[c][r - 1], raw[c][r], raw[c][r + 1], lo[k], hi[k]);
+                if (k % kBatch == kBatch - 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            const double slo = wave_speed<0>(lo, m), shi = wave_speed<0>(hi, m);
+            const double a = fmax(shi, row_next<true>(slo));
+#pragma unroll
+            for (int k = 0; k < 16; ++k) lo[k] = row_next<true>(lo[k]);
+#pragma unroll
+            for (int k = 0; k < 10; ++k) {
+                const double H = face_flux<0>(hi, lo, k, a, im);
+                L[k] = (row_next<false>(H) - H) * A.idx;
+            }
+        }
+        double Ev[3] = {0.0, 0.0, 0.0}, Bv[3] = {0.0, 0.0, 0.0};
+        if (own) {
+            const size_t c = ((size_t)j * nx + i) * 3;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                Ev[d] = A.E[c + d];
+                Bv[d] = A.B[c + d];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 10; ++k) u[k] = raw[k][r];
+        __syncthreads();                      // every read of the cells is done
+        // sources: momentum (q/m)(n E + nu x B)
+        const double qm = q / m;
+        L[1] += qm * (u[0] * Ev[0] + u[2] * Bv[2] - u[3] * Bv[1]);
+        L[2] += qm * (u[0] * Ev[1] + u[3] * Bv[0] - u[1] * Bv[2]);
+        L[3] += qm * (u[0] * Ev[2] + u[1] * Bv[1] - u[2] * Bv[0]);
+        // second moment: q (nu_i E_j + nu_j E_i) + (q/m)(eps_jkl P_ik B_l + eps_ikl P_jk B_l)
+        const double P[3][3] = {{u[4], u[5], u[6]}, {u[5], u[7], u[8]}, {u[6], u[8], u[9]}};
+        double PxB[3][3];                     // row i of P crossed with B
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            PxB[d][0] = P[d][1] * Bv[2] - P[d][2] * Bv[1];
+            PxB[d][1] = P[d][2] * Bv[0] - P[d][0] * Bv[2];
+            PxB[d][2] = P[d][0] * Bv[1] - P[d][1] * Bv[0];
+        }
+        const int ia[6] = {0, 0, 0, 1, 1, 2}, ib[6] = {0, 1, 2, 1, 2, 2};
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int x = ia[k], y = ib[k];
+            L[4 + k] += q * (u[1 + x] * Ev[y] + u[1 + y] * Ev[x]) + qm * (PxB[x][y] + PxB[y][x]);
+        }
+        __syncthreads();                      // the y exchange is stored
+        if constexpr (THIRD == kThirdZero) {
+            // Eq. 5 as a source of P: -div Q = gchi n v_t lap T (gchi = chi / k0)
+            if (own) {
+                const double* t = temp + (ty + 1) * (kCols + 2) + tx;
+                const double tr = t[0] + t[3 * kTempCells] + t[5 * kTempCells];
+                const double g = S.gchi[sp] * (u[0] * sqrt(tr / (3.0 * m)));
+                const double ix2 = A.idx * A.idx, iy2 = A.idy * A.idy;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    const double* tk = t + k * kTempCells;
+                    const double lx = (tk[1] - 2.0 * tk[0]) + tk[-1];
+                    const double ly = (tk[kCols + 2] - 2.0 * tk[0]) + tk[-(kCols + 2)];
+                    L[4 + k] += g * (lx * ix2 + ly * iy2);
+                }
+            }
+        }
+        __syncthreads();                      // the y exchange has been read
+        // the half writes the block's results and loads U_n meanwhile
+        const int cols = nx - i0 < kCols ? nx - i0 : kCols, rows = ny - j0 < kRows ? ny - j0 : kRows;
+        const size_t g0 = ((size_t)j0 * nx + i0) * 10, stride = (size_t)nx * 10;
+        const double* Un = (A.a != 0.0 ? S.Un[sp] : Us) + g0;    // first stage: weight 0
+        const unsigned o = tid < cols * 10 ? (unsigned)tid : 0u;
+        double un[kRows];
+#pragma unroll
+        for (int jj = 0; jj < kRows; ++jj) un[jj] = (Un + (jj < rows ? jj : 0) * stride)[o];
+        __syncthreads();                      // the y fluxes are stored
+#pragma unroll
+        for (int k = 0; k < 10; ++k) part[k * kXStride + tid] = fma(A.dt, L[k], u[k]);
+        __syncthreads();                      // the sums are stored
+        __syncthreads();                      // the results are stored
+        if (tid < cols * 10) {
+            double* Uo = S.Uo[sp] + g0;
+            const bool first = A.a == 0.0;
+#pragma unroll
+            for (int jj = 0; jj < kRows; ++jj) {
+                const double v = A.b * pool[jj * kCols * 10 + tid];
+                if (jj < rows) (Uo + jj * stride)[(unsigned)tid] = first ? v : fma(A.a, un[jj], v);
+            }
+        }
+    } else {
+        // 3. y
+        const bool lane = tid < kYLanes;
+        const int t = lane ? tid : 0;
+        const int tx = t % kCols, ty = t / kCols;
+        const int r = (ty + 1) * kHaloC + tx + 2;
+        double lo[16], hi[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int c = k < 10 ? k : FluxMap<1>::third(k - 10);
+            cweno(raw[c][r - kHaloC], raw[c][r], raw[c][r + kHaloC], lo[k], hi[k]);
+            if (k % kBatch == kBatch - 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        const double slo = wave_speed<1>(lo, m), shi = wave_speed<1>(hi, m);
+        __syncthreads();                      // every read of the cells is done
+        if (lane) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) pool[k * kYStride + t] = lo[k];
+            pool[16 * kYStride + t] = slo;
+        }
+        __syncthreads();                      // the y exchange is stored
+        const int up = ty <= kRows ? t + kCols : t;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) lo[k] = pool[k * kYStride + up];
+        const double a = fmax(shi, pool[16 * kYStride + up]);
+        __syncthreads();                      // the y exchange has been read
+        double H[10];
+#pragma unroll
+        for (int k = 0; k < 10; ++k) {
+            H[k] = face_flux<1>(hi, lo, k, a, im);
+            if (lane) pool[k * kYStride + t] = H[k];
+        }
+        __syncthreads();                      // the y fluxes are stored
+        const int dn = ty > 0 ? t - kCols : t;
+#pragma unroll
+        for (int k = 0; k < 10; ++k) H[k] = (pool[k * kYStride + dn] - H[k]) * A.idy;
+        __syncthreads();                      // the sums are stored
+        // 4. both directions
+        if (lane && ty >= 1 && ty <= kRows) {
+            const double* sum = part + (ty - 1) * (kCols + 2) + tx + 1;
+            double* out = pool + ((ty - 1) * kCols + tx) * 10;
+#pragma unroll
+            for (int k = 0; k < 10; ++k) out[k] = fma(A.dt, H[k], sum[k * kXStride]);
+        }
+        __syncthreads();                      // the results are stored
     }
 }
 
@@ -456,114 +540,48 @@ __global__ void __launch_bounds__(256) copy_kernel(const double* __restrict__ a,
 }
 
 // -------------------------------------------------------------- launchers --
-// One SSP-RK3 step of ns species (one launch per kernel for all of them).
-// work: per species U1, U2 (10 doubles per cell each), Hx (10 per cell), Hy
-// (10 per face of ny + 1 rows), fluid_rk3_3v_doubles(nx, ny) in all.
+// One SSP-RK3 step of ns species with the kinetic third moment (one launch per
+// stage).  work: per species U1, U2 (10 doubles per cell each) at a stride of
+// fluid_rk3_3v_doubles(nx, ny).
 hipError_t launch_fluid_rk3_3v_set(int ns, double* const* U, const double* const* mom_t, const double* const* mom_t1,
                                    const double* E_t, const double* B_t, const double* E_t1, const double* B_t1,
                                    const double* E_th, const double* B_th, double dt, int nx, int ny, const double* q,
                                    const double* m, double dx, double dy, double* work, hipStream_t st, int per) {
     if (ns < 1 || ns > 2) return hipErrorInvalidValue;
-    const long long cells = (long long)nx * ny;
-    FluidSet S[3] = {};
-    for (int s = 0; s < ns; ++s) {
-        double* w = work + (size_t)s * fluid_rk3_3v_doubles(nx, ny);
-        double* U1 = w;
-        double* U2 = U1 + cells * 10;
-        double* Hx = U2 + cells * 10;
-        double* Hy = Hx + cells * 10;
-        const double* Us[3] = {U[s], U1, U2};
-        double* Uo[3] = {U1, U2, U[s]};
-        const double* QA[3] = {mom_t[s], mom_t1[s], mom_t[s]};
-        const double* QB[3] = {mom_t[s], mom_t1[s], mom_t1[s]};
-        for (int k = 0; k < 3; ++k) {
-            S[k].Us[s] = Us[k];
-            S[k].Un[s] = U[s];
-            S[k].Uo[s] = Uo[k];
-            S[k].QA[s] = QA[k];
-            S[k].QB[s] = QB[k];
-            S[k].Hx[s] = Hx;
-            S[k].Hy[s] = Hy;
-            S[k].Sg[s] = nullptr;
-            S[k].m[s] = m[s];
-            S[k].q[s] = q[s];
-            S[k].gchi[s] = 0.0;
-        }
-    }
-    const double wa[3] = {1.0, 1.0, 0.5}, wb[3] = {0.0, 0.0, 0.5};
     const double* E[3] = {E_t, E_t1, E_th};
     const double* B[3] = {B_t, B_t1, B_th};
-    const double a[3] = {0.0, 0.75, 1.0 / 3.0}, b[3] = {1.0, 0.25, 2.0 / 3.0};
+    const double wa[3] = {1.0, 1.0, 0.5}, wb[3] = {0.0, 0.0, 0.5};
     for (int k = 0; k < 3; ++k) {
-        const hipError_t e = launch_fluid_stage_3v_set(S[k], ns, wa[k], wb[k], E[k], B[k], a[k], b[k], dt, nx, ny,
-                                                       dx, dy, st, per);
+        FluidSet S{};
+        for (int s = 0; s < ns; ++s) {
+            rk3_buffers(S, s, k, U[s], work + (size_t)s * fluid_rk3_3v_doubles(nx, ny), (long long)nx * ny);
+            S.QA[s] = k == 1 ? mom_t1[s] : mom_t[s];
+            S.QB[s] = mom_t1[s];
+            S.m[s] = m[s];
+            S.q[s] = q[s];
+        }
+        const hipError_t e = launch_fluid_stage_3v_set(S, ns, kThirdFromF, k, wa[k], wb[k], E[k], B[k], dt, nx, ny, dx,
+                                                       dy, st, per);
         if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
-hipError_t launch_fluid_rk3_3v(double* U, const double* mom_t, const double* mom_t1, const double* E_t,
-                               const double* B_t, const double* E_t1, const double* B_t1, const double* E_th,
-                               const double* B_th, double dt, int nx, int ny, double q, double m, double dx,
-                               double dy, double* work, hipStream_t st, int per) {
-    double* Ul[1] = {U};
-    const double* mt[1] = {mom_t};
-    const double* mt1[1] = {mom_t1};
-    return launch_fluid_rk3_3v_set(1, Ul, mt, mt1, E_t, B_t, E_t1, B_t1, E_th, B_th, dt, nx, ny, &q, &m, dx, dy, work,
-                                   st, per);
-}
-
-// The update kernel reads each cell's 10-double records with 8-byte lane
-// accesses 80 bytes apart, so a wave's ten loads share the same lines; with
-// many waves per CU those lines are evicted between the loads and fetched
-// again.  Dynamic LDS that the kernel does not use caps it at four one-wave
-// blocks per CU (one wave per SIMD): 2048 x 1024 cells x 2 species, 7.35 ->
-// 6.89 ms per fluid-only step (two waves per SIMD: 7.08, five: 7.86).  The
-// faces kernel goes the other way (capped at four blocks per CU: 9.03 ms).
-constexpr unsigned kUpdateLdsCap = 40960;
-
-hipError_t launch_fluid_stage_3v_set(const FluidSet& S, int ns, double wa, double wb, const double* E,
-                                     const double* B, double a, double b, double dt, int nx, int ny, double dx,
+hipError_t launch_fluid_stage_3v_set(const FluidSet& S, int ns, int third, int stage, double wa, double wb,
+                                     const double* E, const double* B, double dt, int nx, int ny, double dx,
                                      double dy, hipStream_t st, int per) {
-    if (ns < 1 || ns > 2) return hipErrorInvalidValue;
-    FluidArgs A{nx, ny, 0.0, 0.0, 1.0 / dx, 1.0 / dy, per};
-    dim3 blk(64), gc((nx + 63) / 64, ny, ns);
-    const int nbx_row = (nx + kXTile - 1) / kXTile;
-    const int nby_col = (nx + kYCols - 1) / kYCols;
-    const int nbx = nbx_row * ny, nby = nby_col * ((ny + 1 + kYRows - 1) / kYRows);
-    hipLaunchKernelGGL(faces3_kernel, dim3(nbx + nby, ns), dim3(kFaceThreads), 0, st, S, wa, wb, A, nbx_row, nbx,
-                       nby_col);
-    bool grad = false;
-    for (int s = 0; s < ns; ++s) {
-        if (S.gchi[s] != 0.0 && !S.Sg[s]) return hipErrorInvalidValue;
-        grad = grad || S.gchi[s] != 0.0;
-    }
-    if (grad) hipLaunchKernelGGL(closure_source3_kernel, gc, blk, 0, st, S, A);
-    hipLaunchKernelGGL(update3_kernel, gc, blk, kUpdateLdsCap, st, S, E, B, a, b, dt, A);
-    return hipGetLastError();
-}
-
-hipError_t launch_fluid_stage_3v(const double* Us, const double* Un, double* Uo, const double* QA, const double* QB,
-                                 double wa, double wb, const double* E, const double* B, double a, double b, double dt,
-                                 int nx, int ny, double q, double m, double dx, double dy, double* Hx, double* Hy,
-                                 hipStream_t st, double gchi, double* Sg, int per) {
-    FluidSet S{};
-    S.Us[0] = Us;
-    S.Un[0] = Un;
-    S.Uo[0] = Uo;
-    S.QA[0] = QA;
-    S.QB[0] = QB;
-    S.Hx[0] = Hx;
-    S.Hy[0] = Hy;
-    S.Sg[0] = Sg;
-    S.m[0] = m;
-    S.q[0] = q;
-    S.gchi[0] = gchi;
-    return launch_fluid_stage_3v_set(S, 1, wa, wb, E, B, a, b, dt, nx, ny, dx, dy, st, per);
-}
-
-hipError_t launch_qcal_q0(const double* U, long long cells, double m, double* qc, hipStream_t st) {
-    hipLaunchKernelGGL(qcal_q0_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, U, cells, m, qc);
+    if (ns < 1 || ns > 2 || stage < 0 || stage > 2) return hipErrorInvalidValue;
+    const double a[3] = {0.0, 0.75, 1.0 / 3.0}, b[3] = {1.0, 0.25, 2.0 / 3.0};
+    const int tx = (nx + kCols - 1) / kCols, ty = (ny + kRows - 1) / kRows;
+    if ((long long)tx * ty * ns > 0x7fffffffll) return hipErrorInvalidValue;
+    const FluidArgs A{nx, ny, 1.0 / dx, 1.0 / dy, a[stage], b[stage], dt, wa, wb, E, B, per, tx, ty};
+    const dim3 grid((unsigned)((long long)tx * ty * ns)), blk(2 * kHalf);
+    if (third == kThirdFromF)
+        hipLaunchKernelGGL(fluid3_stage_kernel<kThirdKinetic>, grid, blk, 0, st, S, A);
+    else if (third == kThirdGradient)
+        hipLaunchKernelGGL(fluid3_stage_kernel<kThirdZero>, grid, blk, 0, st, S, A);
+    else
+        hipLaunchKernelGGL(fluid3_stage_kernel<kThirdNet>, grid, blk, 0, st, S, A);
     return hipGetLastError();
 }
 

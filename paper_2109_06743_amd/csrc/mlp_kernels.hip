@@ -605,48 +605,6 @@ mlp_reduce_kernel(const float* __restrict__ part, int nblocks, float* __restrict
 }
 
 // --------------------------------------------------- closure in the fluid --
-// Third moment of every cell for one RK stage: the network's heat flux
-// (scale * y) turned into Q-calligraphic = Q + sym(u P) - 2 m n uuu, written
-// at [c*20 + 10 + k] (the raw-moment layout the flux kernels read); or, when
-// *fallback is set, the kinetic wa*QA + wb*QB.
-// Species blockIdx.y of the set; scale, y and qc hold the set's species one
-// after the other.
-__global__ void mlp_qcal_kernel(MlpSet S, const double* __restrict__ scale, const float* __restrict__ y, double wa,
-                                double wb, long long cells, double* __restrict__ qc) {
-    const int sp = blockIdx.y;
-    const double* __restrict__ U = S.U[sp];
-    const int* __restrict__ fallback = S.fallback[sp];
-    const double* __restrict__ QA = S.QA[sp];
-    const double* __restrict__ QB = S.QB[sp];
-    const double m = S.m[sp];
-    scale += (size_t)sp * cells;
-    y += (size_t)sp * cells * kOutPad;
-    qc += (size_t)sp * cells * 20;
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells) return;
-    if (fallback && *fallback) {
-#pragma unroll
-        for (int k = 0; k < 10; ++k)
-            qc[c * 20 + 10 + k] = wa * QA[c * 20 + 10 + k] + (wb != 0.0 ? wb * QB[c * 20 + 10 + k] : 0.0);
-        return;
-    }
-    const double n = U[c * 10];
-    const double u[3] = {U[c * 10 + 1] / n, U[c * 10 + 2] / n, U[c * 10 + 3] / n};
-    double P[3][3];
-    const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 2};
-#pragma unroll
-    for (int k = 0; k < 6; ++k) P[pa[k]][pb[k]] = P[pb[k]][pa[k]] = U[c * 10 + 4 + k];
-    const int ta[10] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 2}, tb[10] = {0, 0, 0, 1, 1, 2, 1, 1, 2, 2},
-              tc[10] = {0, 1, 2, 1, 2, 2, 1, 2, 2, 2};
-    const double sc = scale[c];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) {
-        const int a = ta[k], b = tb[k], d = tc[k];
-        qc[c * 20 + 10 + k] = sc * (double)y[c * 16 + k] + (u[a] * P[b][d] + u[b] * P[a][d] + u[d] * P[a][b]) -
-                              2.0 * m * n * u[a] * u[b] * u[d];
-    }
-}
-
 // Judge: sums over cells of |q_net - q_kin|^2 and |q_kin|^2 (q_i = Q_ijj),
 // per block in a fixed order.
 __global__ void __launch_bounds__(256)
@@ -783,26 +741,6 @@ hipError_t launch_mlp_train_step(float* P, float* m1, float* m2, long long step,
                                  const unsigned short* x, const float* t, long long n, float* part, float* grad,
                                  hipStream_t st, const long long* idx, long long nrows) {
     return grad_and_sum(P, x, t, n, part, grad, st, idx, nrows, adam_args(P, m1, m2, step, lr));
-}
-
-hipError_t launch_mlp_qcal_set(const MlpSet& S, int ns, const double* scale, const float* y, double wa, double wb,
-                               long long cells, double* qc, hipStream_t st) {
-    if (ns < 1 || ns > 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(mlp_qcal_kernel, dim3((unsigned)((cells + 255) / 256), ns), dim3(256), 0, st, S, scale, y, wa,
-                       wb, cells, qc);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_qcal(const double* U, const double* scale, const float* y, const int* fallback,
-                           const double* QA, const double* QB, double wa, double wb, long long cells, double m,
-                           double* qc, hipStream_t st) {
-    MlpSet S{};
-    S.U[0] = U;
-    S.fallback[0] = const_cast<int*>(fallback);
-    S.QA[0] = QA;
-    S.QB[0] = QB;
-    S.m[0] = m;
-    return launch_mlp_qcal_set(S, 1, scale, y, wa, wb, cells, qc, st);
 }
 
 size_t mlp_judge_part_doubles() { return 2 * kJudgeBlocks; }

@@ -170,17 +170,17 @@ size_t fluid_doubles(const vl_config& c) {
 }
 
 // Learned-closure scratch of the step: features (BF16 [cells][64] = 16
-// doubles per cell), scale (1), network outputs (FP32 [cells][16] = 8), third
-// moment (20 per cell, raw-moment layout), judge partials.
+// doubles per cell), scale (1), network outputs (FP32 [cells][16] = 8), judge
+// partials behind 45 doubles per cell.
 size_t mlp_step_doubles(const vl_config& c) {
     if (c.closure != VL_CLOSURE_MLP) return 0;
     const size_t cells = (size_t)c.nx * c.ny;
     return (size_t)c.nspecies * (45 * cells + vl::mlp_judge_part_doubles()) + 2;   // every species at once
 }
 
-// Fluid-only closure step: the step's field arrays, the fluid scratch, the
-// third moment (20 per cell), the Eq. 5 source (6 per cell) and the
-// network's scratch (25 per cell + 2).
+// Fluid-only closure step: the step's field arrays (18 per cell), U1 and U2 of
+// two species (40) and the network's features, scales and outputs of two
+// species (50), with some to spare.
 size_t fluid_closure_doubles(const vl_config& c) {
     const size_t cells = (size_t)c.nx * c.ny;
     return 18 * cells + fluid_doubles(c) + 20 * cells + 6 * cells + 25 * cells + 2;
@@ -312,12 +312,35 @@ vl_status fluid_step_impl(vl_ctx* ctx, int s, double* U, const double* mom_t, co
     const vl_species& sp = c.sp[s];
     Timed tm(ctx, VL_T_FLUID, st);
     if (c.dim_v == 3)
-        VL_HIP(vl::launch_fluid_rk3_3v(U, mom_t, mom_t1, E_t, B_t, E_t1, B_t1, E_th, B_th, dt, c.nx, c.ny, sp.q, sp.m,
-                                       dx_of(c), dy_of(c), work, st, per_y(c)));
+        VL_HIP(vl::launch_fluid_rk3_3v_set(1, &U, &mom_t, &mom_t1, E_t, B_t, E_t1, B_t1, E_th, B_th, dt, c.nx, c.ny,
+                                           &sp.q, &sp.m, dx_of(c), dy_of(c), work, st, per_y(c)));
     else
         VL_HIP(vl::launch_fluid_rk3_1v(U, U, mom_t, mom_t1, E_t, E_t1, E_th, nullptr, dt, c.nx, sp.q, sp.m, dx_of(c),
                                        work, st));
     return VL_OK;
+}
+
+// One fluid RK stage of all species with the network's heat flux: features
+// and outputs of the stage state (one launch each), then the stage.  G: the
+// stage's state buffers (and the kinetic third moments for species whose
+// fallback flag is set).
+hipError_t network_stage(vl_ctx* ctx, int ns, int k, vl::FluidSet& G, const float* params, unsigned short* x,
+                         double* scale, float* y, double wa, double wb, const double* E, const double* B, double dt,
+                         hipStream_t st) {
+    const vl_config& c = ctx->cfg;
+    vl::MlpSet F{};
+    for (int s = 0; s < ns; ++s) {
+        F.M[s] = G.Us[s];
+        F.m[s] = G.m[s] = c.sp[s].m;
+        G.q[s] = c.sp[s].q;
+        G.y[s] = y + (size_t)s * ctx->cells * 16;
+        G.scale[s] = scale + (size_t)s * ctx->cells;
+    }
+    hipError_t e = vl::launch_mlp_features_set(F, ns, 0, 10, B, c.nx, c.ny, x, scale, st);
+    if (e == hipSuccess) e = vl::launch_mlp_forward(params, x, ns * ctx->cells, y, st);
+    if (e != hipSuccess) return e;
+    return vl::launch_fluid_stage_3v_set(G, ns, vl::kThirdNetwork, k, wa, wb, E, B, dt, c.nx, c.ny, dx_of(c),
+                                         dy_of(c), st, per_y(c));
 }
 
 // Fluid RK3 of all species with the learned third moment (2X3V): judge the
@@ -335,7 +358,6 @@ vl_status fluid_step_mlp_all(vl_ctx* ctx, const vl_state* S, const double* E_t, 
     float* y = (float*)mwork;                           // 16-byte aligned (the caller aligns mwork)
     unsigned short* x = (unsigned short*)(mwork + 8 * ns * cells);
     double* scale = mwork + 24 * ns * cells;
-    double* qc = mwork + 25 * ns * cells;
     double* part = mwork + 45 * ns * cells;
     Timed tm(ctx, VL_T_FLUID, st);
     vl::MlpSet J{};
@@ -349,43 +371,17 @@ vl_status fluid_step_mlp_all(vl_ctx* ctx, const vl_state* S, const double* E_t, 
     VL_HIP(vl::launch_mlp_forward(S->mlp_params, x, ns * cells, y, st));
     VL_HIP(vl::launch_mlp_judge_set(J, ns, scale, y, cells, c.closure_tol, part, st));
     const double wa[3] = {1.0, 1.0, 0.5}, wb[3] = {0.0, 0.0, 0.5};
-    const double a[3] = {0.0, 0.75, 1.0 / 3.0}, b[3] = {1.0, 0.25, 2.0 / 3.0};
     const double* E[3] = {E_t, E_t1, E_th};
     const double* B[3] = {B_t, B_t1, B_th};
     for (int k = 0; k < 3; ++k) {
-        vl::MlpSet F{};
         vl::FluidSet G{};
         for (int s = 0; s < ns; ++s) {
-            double* U = S->U[s];
-            double* U1 = fwork + (size_t)s * fluid_doubles(c);
-            double* U2 = U1 + cells * 10;
-            const double* Us[3] = {U, U1, U2};
-            double* Uo[3] = {U1, U2, U};
-            const double* QA[3] = {S->mom_post[s], S->mom_pre[s], S->mom_post[s]};
-            const double* QB[3] = {S->mom_post[s], S->mom_pre[s], S->mom_pre[s]};
-            F.M[s] = Us[k];
-            F.U[s] = Us[k];
-            F.QA[s] = QA[k];
-            F.QB[s] = QB[k];
-            F.fallback[s] = S->closure_fallback + s;
-            F.m[s] = c.sp[s].m;
-            G.Us[s] = Us[k];
-            G.Un[s] = U;
-            G.Uo[s] = Uo[k];
-            G.QA[s] = qc + (size_t)s * 20 * cells;
-            G.QB[s] = G.QA[s];
-            G.Hx[s] = U2 + cells * 10;
-            G.Hy[s] = G.Hx[s] + cells * 10;
-            G.Sg[s] = nullptr;
-            G.m[s] = c.sp[s].m;
-            G.q[s] = c.sp[s].q;
-            G.gchi[s] = 0.0;
+            vl::rk3_buffers(G, s, k, S->U[s], fwork + (size_t)s * fluid_doubles(c), cells);
+            G.QA[s] = k == 1 ? S->mom_pre[s] : S->mom_post[s];
+            G.QB[s] = S->mom_pre[s];
+            G.fallback[s] = S->closure_fallback + s;
         }
-        VL_HIP(vl::launch_mlp_features_set(F, ns, 0, 10, B[k], c.nx, c.ny, x, scale, st));
-        VL_HIP(vl::launch_mlp_forward(S->mlp_params, x, ns * cells, y, st));
-        VL_HIP(vl::launch_mlp_qcal_set(F, ns, scale, y, wa[k], wb[k], cells, qc, st));
-        VL_HIP(vl::launch_fluid_stage_3v_set(G, ns, 1.0, 0.0, E[k], B[k], a[k], b[k], dt, c.nx, c.ny, dx_of(c),
-                                             dy_of(c), st, per_y(c)));
+        VL_HIP(network_stage(ctx, ns, k, G, S->mlp_params, x, scale, y, wa[k], wb[k], E[k], B[k], dt, st));
     }
     return VL_OK;
 }
@@ -407,14 +403,13 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
     double* B_h = E_h + 3 * cells;
     double* E_1 = B_h + 3 * cells;
     double* B_1 = E_1 + 3 * cells;
+    // U1, U2 of both species, then the network's scratch of both
     double* fwork = B_1 + 3 * cells;
-    double* qc = fwork + fluid_doubles(c);
-    double* sg = qc + 20 * cells;                         // Eq. 5 source of P, [cells][6]
-    double* mw = sg + 6 * cells;
+    double* mw = fwork + 40 * cells;
     mw += ((uintptr_t)mw & 15u) ? 1 : 0;                 // network outputs are stored as 16-byte vectors
     float* y = (float*)mw;
-    unsigned short* x = (unsigned short*)(mw + 8 * cells);
-    double* scale = mw + 24 * cells;
+    unsigned short* x = (unsigned short*)(mw + 8 * ns * cells);
+    double* scale = mw + 24 * ns * cells;
     const double* Uc[2] = {S->U[0], ns > 1 ? S->U[1] : nullptr};
     {
         Timed tm(ctx, VL_T_FIELDS, st);
@@ -425,33 +420,25 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
         // E^1 = 2 E^{t+1/2} - E^t and the same for B (E and B arrays adjacent)
         VL_HIP(vl::launch_axpby(E_h, E_t, 2.0, -1.0, E_1, 6 * cells, st));
     }
-    for (int s = 0; s < ns; ++s) {
-        const vl_species& sp = c.sp[s];
+    {
         Timed tm(ctx, VL_T_FLUID, st);
-        double* U = S->U[s];
-        double* U1 = fwork;
-        double* U2 = U1 + cells * 10;
-        double* Hx = U2 + cells * 10;
-        double* Hy = Hx + cells * 10;
-        struct Stage { const double* Us; double* Uo; const double* E; const double* B; double a, b; };
-        const Stage G[3] = {
-            {U, U1, E_t, B_t, 0.0, 1.0},
-            {U1, U2, E_1, B_1, 0.75, 0.25},
-            {U2, U, E_h, B_h, 1.0 / 3.0, 2.0 / 3.0},
-        };
-        // chi / k0 with chi = 2 sqrt(2/pi), k0 = 1/d_s, d_s = sqrt(m / q^2)
-        const double gchi = 2.0 * sqrt(2.0 / 3.14159265358979323846) * sqrt(sp.m / (sp.q * sp.q));
+        const double* E[3] = {E_t, E_1, E_h};
+        const double* B[3] = {B_t, B_1, B_h};
         for (int k = 0; k < 3; ++k) {
-            if (closure == VL_FLUID_GRADIENT) {
-                VL_HIP(vl::launch_qcal_q0(G[k].Us, cells, sp.m, qc, st));
-            } else {
-                VL_HIP(vl::launch_mlp_features(G[k].Us, 10, G[k].B, c.nx, c.ny, sp.m, s, x, scale, st));
-                VL_HIP(vl::launch_mlp_forward(S->mlp_params, x, cells, y, st));
-                VL_HIP(vl::launch_mlp_qcal(G[k].Us, scale, y, nullptr, qc, qc, 1.0, 0.0, cells, sp.m, qc, st));
+            vl::FluidSet G{};
+            for (int s = 0; s < ns; ++s) {
+                const vl_species& sp = c.sp[s];
+                vl::rk3_buffers(G, s, k, S->U[s], fwork + (size_t)s * 20 * cells, cells);
+                G.m[s] = sp.m;
+                G.q[s] = sp.q;
+                // chi / k0 with chi = 2 sqrt(2/pi), k0 = 1/d_s, d_s = sqrt(m / q^2)
+                G.gchi[s] = 2.0 * sqrt(2.0 / 3.14159265358979323846) * sqrt(sp.m / (sp.q * sp.q));
             }
-            VL_HIP(vl::launch_fluid_stage_3v(G[k].Us, U, G[k].Uo, qc, qc, 1.0, 0.0, G[k].E, G[k].B, G[k].a, G[k].b,
-                                             dt, c.nx, c.ny, sp.q, sp.m, dx_of(c), dy_of(c), Hx, Hy, st,
-                                             closure == VL_FLUID_GRADIENT ? gchi : 0.0, sg, per_y(c)));
+            if (closure == VL_FLUID_GRADIENT)
+                VL_HIP(vl::launch_fluid_stage_3v_set(G, ns, vl::kThirdGradient, k, 0.0, 0.0, E[k], B[k], dt, c.nx,
+                                                     c.ny, dx_of(c), dy_of(c), st, per_y(c)));
+            else
+                VL_HIP(network_stage(ctx, ns, k, G, S->mlp_params, x, scale, y, 0.0, 0.0, E[k], B[k], dt, st));
         }
     }
     Timed tm(ctx, VL_T_FIELDS, st);

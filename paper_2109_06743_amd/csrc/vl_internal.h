@@ -149,69 +149,63 @@ hipError_t launch_axpby(const double* x, const double* y, double a, double b, do
 
 // Per-species operands of one fluid stage: up to two species per launch.
 struct FluidSet {
-    const double* Us[2];
-    const double* Un[2];
+    const double* Us[2];          // stage state; U_out must not be it
+    const double* Un[2];          // state of the step's start (U_out may be it)
     double* Uo[2];
-    const double* QA[2];
+    const double* QA[2];          // kinetic third moments (raw-moment layout)
     const double* QB[2];
-    double* Hx[2];
-    double* Hy[2];
-    double* Sg[2];        // Eq. 5 source scratch, [cells][6] (needed where gchi != 0)
+    const float* y[2];            // network outputs [cells][16] and scales [cells]
+    const double* scale[2];
+    const int* fallback[2];       // network: take the kinetic moment where set (may be null)
     double m[2], q[2], gchi[2];
 };
+// Third moment of a stage: wa QA + wb QB; that of zero heat flux plus the Eq. 5
+// source of P (gchi = chi / k0); that of the network's heat flux.
+enum { kThirdFromF = 0, kThirdGradient = 1, kThirdNetwork = 2 };
 
-// Scratch of one species' SSP-RK3 step of the 3V fluid (doubles).
+// Scratch of one species' SSP-RK3 step of the 3V fluid (doubles): U1, U2 (10
+// per cell each); the rest is the caller's to use meanwhile.
 inline size_t fluid_rk3_3v_doubles(int nx, int ny) { return 30 * (size_t)nx * ny + 10 * (size_t)nx * (ny + 1); }
+inline size_t fluid_rk3_3v_used(int nx, int ny) { return 20 * (size_t)nx * ny; }
 
-// One SSP-RK3 step of ns (1 or 2) species, each kernel launched once for all
+// State buffers of stage k (0..2) of species s: U -> U1 -> U2 -> U.
+inline void rk3_buffers(FluidSet& S, int s, int k, double* U, double* work, long long cells) {
+    double* U1 = work;
+    double* U2 = U1 + cells * 10;
+    S.Us[s] = k == 0 ? U : (k == 1 ? U1 : U2);
+    S.Un[s] = U;
+    S.Uo[s] = k == 0 ? U1 : (k == 1 ? U2 : U);
+}
+
+// One SSP-RK3 step of ns (1 or 2) species, each stage launched once for all
 // of them; work: ns * fluid_rk3_3v_doubles(nx, ny) doubles.
 hipError_t launch_fluid_rk3_3v_set(int ns, double* const* U, const double* const* mom_t, const double* const* mom_t1,
                                    const double* E_t, const double* B_t, const double* E_t1, const double* B_t1,
                                    const double* E_th, const double* B_th, double dt, int nx, int ny, const double* q,
                                    const double* m, double dx, double dy, double* work, hipStream_t st, int per);
-hipError_t launch_fluid_stage_3v_set(const FluidSet& S, int ns, double wa, double wb, const double* E,
-                                     const double* B, double a, double b, double dt, int nx, int ny, double dx,
+// One stage (0..2) of the step for ns species.
+hipError_t launch_fluid_stage_3v_set(const FluidSet& S, int ns, int third, int stage, double wa, double wb,
+                                     const double* E, const double* B, double dt, int nx, int ny, double dx,
                                      double dy, hipStream_t st, int per);
-hipError_t launch_fluid_rk3_3v(double* U, const double* mom_t, const double* mom_t1, const double* E_t,
-                               const double* B_t, const double* E_t1, const double* B_t1, const double* E_th,
-                               const double* B_th, double dt, int nx, int ny, double q, double m, double dx,
-                               double dy, double* work, hipStream_t st, int per = 0);
 // U -> Uout (which may be U; work: 3 nx doubles, used then).  g set: the stage
 // fields are the Poisson solves of mom_t, mom_t1 and their mean.
 hipError_t launch_fluid_rk3_1v(double* U, double* Uout, const double* mom_t, const double* mom_t1, const double* E_t,
                                const double* E_t1, const double* E_th, const double* g, double dt, int nx, double q,
                                double m, double dx, double* work, hipStream_t st);
 
-// One SSP-RK3 stage of the 3V fluid: Uo = a Un + b (Us + dt L(Us)), third
-// moment wa QA + wb QB (raw-moment layout, entries 10..19 of 20 per cell).
-// One RK stage of the ten-moment fluid.  gchi != 0 adds the Eq. 5
-// temperature-gradient closure gchi n v_t lap T as a source of P, computed
-// into Sg ([cells][6] scratch, required then).
-hipError_t launch_fluid_stage_3v(const double* Us, const double* Un, double* Uo, const double* QA, const double* QB,
-                                 double wa, double wb, const double* E, const double* B, double a, double b, double dt,
-                                 int nx, int ny, double q, double m, double dx, double dy, double* Hx, double* Hy,
-                                 hipStream_t st, double gchi = 0.0, double* Sg = nullptr, int per = 0);
-// Qcal of fluid records U[cells][10] with zero heat flux, into qc[cells][20] (offsets 10..19).
-hipError_t launch_qcal_q0(const double* U, long long cells, double m, double* qc, hipStream_t st);
-
 // learned heat-flux closure (mlp_kernels.hip)
 constexpr int kMlpParams = 13520;
 // Per-species operands of the network kernels for up to two species per
-// launch; the features, scales, outputs and third moments of the set's
-// species are stored one after the other (cells of species 0, then 1).
+// launch; the features, scales and outputs of the set's species are stored
+// one after the other (cells of species 0, then 1).
 struct MlpSet {
     const double* M[2];     // features and judge: moment (stride 20) or fluid (stride 10) records
-    const double* U[2];     // qcal: the stage's fluid state
-    const double* QA[2];    // qcal: kinetic third moments for the fallback
-    const double* QB[2];
-    int* fallback[2];       // judge output / qcal input (or null)
+    int* fallback[2];       // judge output
     double* err[2];         // judge output
     double m[2];
 };
 hipError_t launch_mlp_features_set(const MlpSet& S, int ns, int s0, int stride, const double* B, int nx, int ny,
                                    unsigned short* x, double* scale, hipStream_t st);
-hipError_t launch_mlp_qcal_set(const MlpSet& S, int ns, const double* scale, const float* y, double wa, double wb,
-                               long long cells, double* qc, hipStream_t st);
 hipError_t launch_mlp_judge_set(const MlpSet& S, int ns, const double* scale, const float* y, long long cells,
                                 double tol, double* part, hipStream_t st);
 hipError_t launch_mlp_features(const double* M, int stride, const double* B, int nx, int ny, double m, int species,
@@ -228,9 +222,6 @@ hipError_t launch_mlp_gradient(const float* P, const unsigned short* x, const fl
 hipError_t launch_mlp_train_step(float* P, float* m1, float* m2, long long step, double lr,
                                  const unsigned short* x, const float* t, long long n, float* part, float* grad,
                                  hipStream_t st, const long long* idx = nullptr, long long nrows = 0);
-hipError_t launch_mlp_qcal(const double* U, const double* scale, const float* y, const int* fallback,
-                           const double* QA, const double* QB, double wa, double wb, long long cells, double m,
-                           double* qc, hipStream_t st);
 size_t mlp_judge_part_doubles();
 hipError_t launch_mlp_judge(const double* M, const double* scale, const float* y, long long cells, double m,
                             double tol, double* part, int* fallback, double* err, hipStream_t st);
