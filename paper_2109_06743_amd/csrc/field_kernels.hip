@@ -166,10 +166,229 @@ __global__ void cell_fields_kernel(YeeView F, double* __restrict__ E, double* __
     B[c * 3 + 2] = 0.5 * (lo + hi);
 }
 
-__global__ void axpby_kernel(const double* __restrict__ x, const double* __restrict__ y, double a, double b,
-                             double* __restrict__ out, long long n) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = a * x[i] + b * y[i];
+// A whole half step from F to G (which must not overlap) in one launch, with
+// the cell-centred averages the step takes from it: a block produces kFRows
+// Yee rows x kFCols columns and holds what they depend on in shared memory (E
+// two rows and columns beyond, B and the current one or two), so that the three
+// updates run there.  As separate kernels a step's two half steps, averages and
+// extrapolation are nine launches, of about 3 us each on a small grid, and at
+// 1024 x 512 move every component four times (123 us; this 84).  Expressions
+// and roundings are those of the kernels above: the velocity sweeps round the
+// fields to FP32 coefficients, so a last-bit change here is not one there.
+// Rows q of the tile are virtual: periodic y wraps them; between walls the
+// integer-row components of E beyond a wall are minus their mirror image.
+// With periodic y rows 0 and ny of the [ny+1] arrays are the same points but
+// two copies, each advanced by itself: the integer rows beyond the seam take
+// the copy on their own side (row ny below row 0, row 0 above row ny - 1).
+constexpr int kFCols = 32, kFRows = 8;
+constexpr int kEC = kFCols + 4, kER = kFRows + 4;      // E: columns i0-2 .. i0+33, rows r0-2 .. r0+9
+constexpr int kBC = kFCols + 3, kBR = kFRows + 3;      // B: columns i0-2 .. i0+32, rows r0-1 .. r0+9
+constexpr int kJC = kFCols + 3, kJR = kFRows + 3;      // current: columns i0-1 .. i0+33, rows r0-2 .. r0+8
+
+struct HalfArgs {
+    YeeView F, G;
+    Currents J;
+    double hb, he, dx, dy;      // B -= hb curl E; E += he (curl B - j)
+    // averages to cell centres (null: not wanted): of F, of G, and 2 G - F
+    double *E0, *B0, *E1, *B1, *E2, *B2;
+};
+
+__global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
+    __shared__ double ex[kER][kEC], ey[kER][kEC], ez[kER][kEC];
+    __shared__ double bx[kBR][kBC], by[kBR][kBC], bz[kBR][kBC];
+    __shared__ double jx[kJR][kJC], jy[kJR][kJC], jz[kJR][kJC];
+    __shared__ double eys[2][kEC], bxs[2][kBC], bzs[2][kBC];         // the seam's other copies: rows ny, 0
+    const int nx = A.F.nx, ny = A.F.ny, per = A.F.per;
+    const int i0 = (int)blockIdx.x * kFCols, r0 = (int)blockIdx.y * kFRows;
+    const int tid = threadIdx.x;
+    auto col = [nx](int i) {
+        i %= nx;
+        return i < 0 ? i + nx : i;
+    };
+    auto wrap = [ny](int q, int n) {          // periodic rows: the points of row q mod ny, in [0, n]
+        while (q < 0) q += ny;
+        while (q > n) q -= ny;
+        return q;
+    };
+    // E: rows of Ex, Ez outside [0, ny) by the boundary; rows no valid point needs are 0
+    for (int e = tid; e < kER * kEC; e += 256) {
+        const int r = e / kEC, c = e % kEC;
+        const int i = col(i0 - 2 + c);
+        int q = r0 - 2 + r, h = q;
+        double sgn = 1.0;
+        bool ok = true, okh = q >= 0 && q <= ny;
+        if (per) {
+            q = wrap(q, ny - 1);
+            h = wrap(h, ny);
+            okh = true;
+        } else if (q < 0) {
+            ok = q == -1;
+            q = 0;
+            sgn = -1.0;
+        } else if (q >= ny) {
+            ok = q == ny;
+            q = ny - 1;
+            sgn = -1.0;
+        }
+        const size_t at = (size_t)q * nx + i;
+        ex[r][c] = ok ? sgn * A.F.Ex[at] : 0.0;
+        ez[r][c] = ok ? sgn * A.F.Ez[at] : 0.0;
+        ey[r][c] = okh ? A.F.Ey[(size_t)h * nx + i] : 0.0;
+    }
+    for (int e = tid; e < kBR * kBC; e += 256) {
+        const int r = e / kBC, c = e % kBC;
+        const int i = col(i0 - 2 + c);
+        int q = r0 - 1 + r, h = q;
+        bool ok = q >= 0 && q < ny, okh = q >= 0 && q <= ny;
+        if (per) {
+            q = wrap(q, ny - 1);
+            h = wrap(h, ny);
+            ok = okh = true;
+        }
+        bx[r][c] = okh ? A.F.Bx[(size_t)h * nx + i] : 0.0;
+        bz[r][c] = okh ? A.F.Bz[(size_t)h * nx + i] : 0.0;
+        by[r][c] = ok ? A.F.By[(size_t)q * nx + i] : 0.0;
+    }
+    for (int e = tid; e < kJR * kJC; e += 256) {
+        const int r = e / kJC, c = e % kJC;
+        int q = r0 - 2 + r;
+        bool ok = q >= 0 && q < ny;
+        if (per) {
+            q = wrap(q, ny - 1);
+            ok = true;
+        }
+        double v[3] = {0.0, 0.0, 0.0};
+        if (ok) {
+            const size_t cell = (size_t)q * nx + col(i0 - 1 + c);
+            for (int k = 0; k < A.J.ns; ++k) {
+                const double* m = A.J.mom[k] + cell * A.J.stride + 1;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) v[d] = fma(A.J.q[k], m[d], v[d]);
+            }
+        }
+        jx[r][c] = v[0];
+        jy[r][c] = v[1];
+        jz[r][c] = v[2];
+    }
+    // the seam in this tile: row 0 at virtual row 0, and row ny
+    const bool seam[2] = {per && r0 == 0, per && r0 + kFRows + 1 >= ny};
+    if (per) {
+        for (int e = tid; e < 2 * kEC; e += 256) {
+            const int s = e / kEC, c = e % kEC;
+            const size_t at = (s == 0 ? (size_t)ny * nx : 0) + col(i0 - 2 + c);
+            if (!seam[s]) continue;
+            eys[s][c] = A.F.Ey[at];
+            if (c < kBC) {
+                bxs[s][c] = A.F.Bx[at];
+                bzs[s][c] = A.F.Bz[at];
+            }
+        }
+    }
+    __syncthreads();
+    // this thread's point: column i0 + tc, row r0 + tr
+    const int tc = tid % kFCols, tr = tid / kFCols;
+    const int i = i0 + tc, q = r0 + tr;
+    const bool cell = i < nx && q < ny;
+    // averages at the cell (E arrays start two rows and columns before the tile, B arrays one row and two columns)
+    auto averages = [&](double (&e)[3], double (&b)[3]) {
+        const int re = tr + 2, rb = tr + 1, c = tc + 2;
+        e[0] = 0.5 * (ex[re][c - 1] + ex[re][c]);
+        e[1] = 0.5 * (ey[re][c] + ey[re + 1][c]);
+        e[2] = ez[re][c];
+        b[0] = 0.5 * (bx[rb][c] + bx[rb + 1][c]);
+        b[1] = 0.5 * (by[rb][c - 1] + by[rb][c]);
+        const double lo = 0.5 * (bz[rb][c - 1] + bz[rb][c]);
+        const double hi = 0.5 * (bz[rb + 1][c - 1] + bz[rb + 1][c]);
+        b[2] = 0.5 * (lo + hi);
+    };
+    double e0[3] = {0.0, 0.0, 0.0}, b0[3] = {0.0, 0.0, 0.0};
+    const size_t at3 = ((size_t)q * nx + i) * 3;
+    if (A.E0 && cell) {
+        averages(e0, b0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            A.E0[at3 + d] = e0[d];
+            A.B0[at3 + d] = b0[d];
+        }
+    }
+    __syncthreads();
+    // B -= hb curl E on the whole B region (B row r is E row r + 1)
+    auto curl_e = [&](int r, int c) {
+        const double dEz = (ez[r + 1][c] - ez[r][c]) / A.dy;
+        const double dEy = (ey[r + 1][c + 1] - ey[r + 1][c]) / A.dx, dEx = (ex[r + 1][c] - ex[r][c]) / A.dy;
+        bx[r][c] = fma(-A.hb, dEz, bx[r][c]);
+        bz[r][c] = fma(-A.hb, dEy - dEx, bz[r][c]);
+        by[r][c] = by[r][c] + A.hb * (ez[r + 1][c + 1] - ez[r + 1][c]) / A.dx;
+    };
+    for (int e = tid; e < kBR * kBC; e += 256) curl_e(e / kBC, e % kBC);
+    if (per) {
+        for (int e = tid; e < 2 * kBC; e += 256) {
+            const int s = e / kBC, c = e % kBC;
+            if (!seam[s]) continue;
+            const int re = (s == 0 ? 0 : ny) - (r0 - 2);
+            const double dEz = (ez[re][c] - ez[re - 1][c]) / A.dy;
+            const double dEy = (eys[s][c + 1] - eys[s][c]) / A.dx, dEx = (ex[re][c] - ex[re - 1][c]) / A.dy;
+            bxs[s][c] = fma(-A.hb, dEz, bxs[s][c]);
+            bzs[s][c] = fma(-A.hb, dEy - dEx, bzs[s][c]);
+        }
+    }
+    __syncthreads();
+    // E += he (curl B - j) on rows r0-1 .. r0+8, columns i0-1 .. i0+32
+    for (int e = tid; e < (kFRows + 2) * (kFCols + 2); e += 256) {
+        const int r = e / (kFCols + 2) + 1, c = e % (kFCols + 2) + 1;     // in the E arrays
+        const int rb = r - 1, rj = r, cj = c - 1;
+        const int row = r0 - 2 + r;
+        const bool below = per && row == -1, above = per && row == ny;
+        const double bzl = above ? bzs[1][c] : bz[rb][c], bzh = below ? bzs[0][c] : bz[rb + 1][c];
+        const double bxl = above ? bxs[1][c] : bx[rb][c], bxh = below ? bxs[0][c] : bx[rb + 1][c];
+        const double cx = (bzh - bzl) / A.dy - 0.5 * (jx[rj][cj] + jx[rj][cj + 1]);
+        const bool wall = !per && (row == 0 || row == ny);
+        const double cy = -(bz[rb][c] - bz[rb][c - 1]) / A.dx - (wall ? 0.0 : 0.5 * (jy[rj - 1][cj] + jy[rj][cj]));
+        const double cz = (by[rb][c] - by[rb][c - 1]) / A.dx - (bxh - bxl) / A.dy - jz[rj][cj];
+        ex[r][c] = fma(A.he, cx, ex[r][c]);
+        ey[r][c] = fma(A.he, cy, ey[r][c]);
+        ez[r][c] = fma(A.he, cz, ez[r][c]);
+    }
+    __syncthreads();
+    if (!per) {        // ghost rows -1 and ny mirror rows 0 and ny - 1
+        for (int e = tid; e < 2 * (kFCols + 2); e += 256) {
+            const int c = e % (kFCols + 2) + 1;
+            const int g = (e < kFCols + 2 ? -1 : ny) - (r0 - 2), m = (e < kFCols + 2 ? 0 : ny - 1) - (r0 - 2);
+            if (g >= 1 && g <= kFRows + 2 && m >= 1 && m <= kFRows + 2) {
+                ex[g][c] = -ex[m][c];
+                ez[g][c] = -ez[m][c];
+            }
+        }
+        __syncthreads();
+    }
+    // B -= hb curl E on rows r0 .. r0+8, columns i0-1 .. i0+31
+    for (int e = tid; e < (kFRows + 1) * (kFCols + 1); e += 256) curl_e(e / (kFCols + 1) + 1, e % (kFCols + 1) + 1);
+    __syncthreads();
+    if (i < nx && q <= ny) {
+        const size_t at = (size_t)q * nx + i;
+        const int re = tr + 2, rb = tr + 1, c = tc + 2;
+        A.G.Ey[at] = ey[re][c];
+        A.G.Bx[at] = bx[rb][c];
+        A.G.Bz[at] = bz[rb][c];
+        if (q < ny) {
+            A.G.Ex[at] = ex[re][c];
+            A.G.Ez[at] = ez[re][c];
+            A.G.By[at] = by[rb][c];
+        }
+    }
+    if (A.E1 && cell) {
+        double e1[3], b1[3];
+        averages(e1, b1);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            A.E1[at3 + d] = e1[d];
+            A.B1[at3 + d] = b1[d];
+            if (A.E2) {
+                A.E2[at3 + d] = 2.0 * e1[d] - e0[d];
+                A.B2[at3 + d] = 2.0 * b1[d] - b0[d];
+            }
+        }
+    }
 }
 
 // The B-curl kernel reads the current from the species' moment records (8-byte
@@ -205,9 +424,32 @@ hipError_t launch_cell_fields(const double* yee, int nx, int ny, double* E, doub
     return hipGetLastError();
 }
 
-hipError_t launch_axpby(const double* x, const double* y, double a, double b, double* out, long long n,
-                        hipStream_t st) {
-    hipLaunchKernelGGL(axpby_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, y, a, b, out, n);
+hipError_t launch_yee_half(const double* from, double* to, int nx, int ny, const double* const* mom, const double* q,
+                           int ns, double dt, double c, double dx, double dy, int mstride, int per,
+                           const CellFields& at_from, const CellFields& at_to, const CellFields& ahead,
+                           hipStream_t st) {
+    HalfArgs A;
+    A.F = yee_view(const_cast<double*>(from), nx, ny);
+    A.G = yee_view(to, nx, ny);
+    A.F.per = A.G.per = per;
+    A.J.ns = ns;
+    A.J.stride = mstride;
+    for (int k = 0; k < 2; ++k) {
+        A.J.mom[k] = k < ns ? mom[k] : nullptr;
+        A.J.q[k] = k < ns ? q[k] : 0.0;
+    }
+    const double h = 0.5 * dt;
+    A.hb = 0.5 * h;
+    A.he = h * (c * c);
+    A.dx = dx;
+    A.dy = dy;
+    A.E0 = at_from.E;
+    A.B0 = at_from.B;
+    A.E1 = at_to.E;
+    A.B1 = at_to.B;
+    A.E2 = ahead.E;
+    A.B2 = ahead.B;
+    hipLaunchKernelGGL(yee_half_kernel, dim3((nx + kFCols - 1) / kFCols, (ny + kFRows) / kFRows), dim3(256), 0, st, A);
     return hipGetLastError();
 }
 

@@ -411,14 +411,15 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
     unsigned short* x = (unsigned short*)(mw + 8 * ns * cells);
     double* scale = mw + 24 * ns * cells;
     const double* Uc[2] = {S->U[0], ns > 1 ? S->U[1] : nullptr};
+    // the fields after the first half step wait behind U1, U2 of both species;
+    // the network's scratch fills that space, so with it they go back at once
+    double* yee1 = mw;
     {
         Timed tm(ctx, VL_T_FIELDS, st);
-        VL_HIP(vl::launch_cell_fields(S->fields, c.nx, c.ny, E_t, B_t, st));   // the fields at t
-        VL_HIP(vl::launch_maxwell_half(S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), st, 10,
-                                       per_y(c)));
-        VL_HIP(vl::launch_cell_fields(S->fields, c.nx, c.ny, E_h, B_h, st));
-        // E^1 = 2 E^{t+1/2} - E^t and the same for B (E and B arrays adjacent)
-        VL_HIP(vl::launch_axpby(E_h, E_t, 2.0, -1.0, E_1, 6 * cells, st));
+        VL_HIP(vl::launch_yee_half(S->fields, yee1, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), 10, per_y(c),
+                                   {E_t, B_t}, {E_h, B_h}, {E_1, B_1}, st));
+        if (closure == VL_FLUID_MLP)
+            VL_HIP(hipMemcpyAsync(S->fields, yee1, yee_doubles(c) * sizeof(double), hipMemcpyDeviceToDevice, st));
     }
     {
         Timed tm(ctx, VL_T_FLUID, st);
@@ -442,8 +443,12 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
         }
     }
     Timed tm(ctx, VL_T_FIELDS, st);
-    VL_HIP(vl::launch_maxwell_half(S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), st, 10,
-                                   per_y(c)));
+    if (closure == VL_FLUID_MLP)
+        VL_HIP(vl::launch_maxwell_half(S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), st, 10,
+                                       per_y(c)));
+    else
+        VL_HIP(vl::launch_yee_half(yee1, S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), 10, per_y(c),
+                                   {}, {}, {}, st));
     return VL_OK;
 }
 
@@ -470,19 +475,15 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
         double* fwork = B_1 + 3 * cells;
         double* mwork = fwork + (size_t)ns * fluid_doubles(c);
         mwork += ((uintptr_t)mwork & 15u) ? 1 : 0;         // network outputs are stored as 16-byte vectors
+        // the fields after the first half step wait in the part of the fluid
+        // scratch that its stages leave free
+        double* yee1 = fwork + vl::fluid_rk3_3v_used(c.nx, c.ny);
         {
             Timed tm(ctx, VL_T_FIELDS, st);
-            if (c.fit) {
-                VL_HIP(vl::launch_cell_fields(S->fields, c.nx, c.ny, E_t, B_t, st));   // the fields at t
-            }
             const double* mom_t[2] = {S->mom_post[0], ns > 1 ? S->mom_post[1] : nullptr};
-            VL_HIP(vl::launch_maxwell_half(S->fields, c.nx, c.ny, mom_t, q, ns, dt, c.c, dx_of(c), dy_of(c), st, 20,
-                                            per_y(c)));
-            VL_HIP(vl::launch_cell_fields(S->fields, c.nx, c.ny, E_h, B_h, st));
-            if (c.fit) {
-                // E^1 = 2 E^{t+1/2} - E^t and the same for B (E and B arrays adjacent)
-                VL_HIP(vl::launch_axpby(E_h, E_t, 2.0, -1.0, E_1, 6 * cells, st));
-            }
+            const vl::CellFields none{}, at_t{E_t, B_t}, ahead{E_1, B_1};
+            VL_HIP(vl::launch_yee_half(S->fields, yee1, c.nx, c.ny, mom_t, q, ns, dt, c.c, dx_of(c), dy_of(c), 20,
+                                       per_y(c), c.fit ? at_t : none, {E_h, B_h}, c.fit ? ahead : none, st));
         }
         for (int s = 0; s < ns; ++s) {
             T* f = (T*)S->f[s];
@@ -526,8 +527,8 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
         }
         const double* mom_t1[2] = {S->mom_post[0], ns > 1 ? S->mom_post[1] : nullptr};
         Timed tm(ctx, VL_T_FIELDS, st);
-        VL_HIP(vl::launch_maxwell_half(S->fields, c.nx, c.ny, mom_t1, q, ns, dt, c.c, dx_of(c), dy_of(c), st, 20,
-                                        per_y(c)));
+        VL_HIP(vl::launch_yee_half(yee1, S->fields, c.nx, c.ny, mom_t1, q, ns, dt, c.c, dx_of(c), dy_of(c), 20,
+                                   per_y(c), {}, {}, {}, st));
     } else {
         const int nx = c.nx;
         double* mom_half = S->work;

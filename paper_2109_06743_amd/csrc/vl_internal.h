@@ -144,8 +144,18 @@ hipError_t launch_maxwell_half(double* yee, int nx, int ny, const double* const*
 hipError_t launch_cell_fields(const double* yee, int nx, int ny, double* E, double* B, hipStream_t st);
 hipError_t launch_field_energy(const double* fields, int dim_x, int nx, int ny, double c, double dX, double* part,
                                double* out, hipStream_t st);
-hipError_t launch_axpby(const double* x, const double* y, double a, double b, double* out, long long n,
-                        hipStream_t st);
+// The same half step out of place (from and to must not overlap), in one
+// launch, with the cell-centred averages of the fields before (at_from) and
+// after (at_to) and 2 after - before (ahead); null pointers: not wanted (ahead
+// needs the other two).
+struct CellFields {
+    double* E = nullptr;
+    double* B = nullptr;
+};
+hipError_t launch_yee_half(const double* from, double* to, int nx, int ny, const double* const* mom, const double* q,
+                           int ns, double dt, double c, double dx, double dy, int mstride, int per,
+                           const CellFields& at_from, const CellFields& at_to, const CellFields& ahead,
+                           hipStream_t st);
 
 // Per-species operands of one fluid stage: up to two species per launch.
 struct FluidSet {
