@@ -14,6 +14,8 @@
 // is already the B operand of the next layer (rows = the K index): samples
 // run along the 16 lanes of a row group, features along (l/16, j), and no
 // data moves between layers.
+#include <type_traits>
+
 #include "vl_internal.h"
 
 namespace vl {
@@ -65,6 +67,32 @@ struct NetLdsT {
 
 __device__ void load_net(const float* __restrict__ P, NetLds& N, NetLdsT* T) {
     const int tid = threadIdx.x, nthr = blockDim.x;
+    if (nthr == 512 && !T && !((uintptr_t)P & 15u)) {
+        // 512 threads, no transposes: seven float4 loads each in flight
+        float4 v[7];
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+            const int e = i * 512 + tid;                      // float4 index over W1, W2, W3, W4
+            const int off = e < 1024 ? kOffW1 : (e < 2048 ? kOffW2 : (e < 3072 ? kOffW3 : kOffW4));
+            v[i] = e < 3072 + 256 ? reinterpret_cast<const float4*>(P + off)[e & 1023] : float4{0.f, 0.f, 0.f, 0.f};
+        }
+        const float bv = tid < 3 * kWid + kOutPad
+                             ? P[tid < 64 ? kOffB1 + tid
+                                          : (tid < 128 ? kOffB2 + tid - 64
+                                                       : (tid < 192 ? kOffB3 + tid - 128 : kOffB4 + tid - 192))]
+                             : 0.f;
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+            const int e = i * 512 + tid;
+            if (e >= 3072 + 256) continue;
+            const int w = 4 * (e & 1023), r = w / kIn, c = w % kIn;
+            const uint2 pk = {(unsigned)bf16_of(v[i].x) | ((unsigned)bf16_of(v[i].y) << 16),
+                              (unsigned)bf16_of(v[i].z) | ((unsigned)bf16_of(v[i].w) << 16)};
+            *reinterpret_cast<uint2*>(e < 3072 ? &N.w[e >> 10][r * kLdw + c] : &N.w4[r * kLdw + c]) = pk;
+        }
+        if (tid < 3 * kWid + kOutPad) N.bias[tid] = bv;
+        return;
+    }
     if (nthr == 256 && !((uintptr_t)P & 15u)) {
         // 256 threads, 16-byte aligned parameters: all 13 float4 loads of a
         // thread are issued before the first conversion
@@ -248,31 +276,44 @@ __device__ __forceinline__ bool local_nuT(const double* __restrict__ M, int stri
 }
 
 // Species blockIdx.z of the set (species index s0 + blockIdx.z); its
-// features and scales are stored after those of the set's earlier species.
-// A 256-thread block covers 4 rows x 64 columns of cells: n, u, T of its
-// 6 x 66 stencil cells are formed once each into LDS (rather than nine times,
-// once per neighbour), each thread then forms its cell's features from
-// there, and the 256 feature rows (128 B each) leave through LDS, so that
-// every wave store writes 256 contiguous bytes.
-constexpr int kFeatCols = 64, kFeatRows = 4;
+// features, outputs and scales are stored after those of the set's earlier
+// species.  A 512-thread block covers 4 rows x 64 columns of cells: n, u, T of
+// its 6 x 66 stencil cells are formed once each into LDS (rather than nine
+// times, once per neighbour), two threads then form each cell's features (34
+// and 30 of them) from there as packed BF16 rows in LDS.  kNet = false: the
+// rows leave for x, every wave store writing 256 contiguous bytes.  kNet: the
+// block's waves run the network on them, two 16-cell tiles each, and only the
+// outputs leave: the rows need not go through memory (2 x 128 B a cell) and a
+// launch goes.  256 x 128 cells, two species: 15.7 us for the features by one
+// thread per cell and 12.0 for the network, 16.5 in one.
+constexpr int kFeatCols = 64, kFeatRows = 4, kFeatCells = kFeatCols * kFeatRows;
 union FeatLds {
     double nut[kFeatRows + 2][kFeatCols + 2][11];   // n, u, T (padded against bank conflicts)
-    unsigned out[kFeatRows * kFeatCols][33];         // packed BF16 feature rows (padded)
+    unsigned out[kFeatCells][34];                    // packed BF16 feature rows (padded, 8-byte aligned)
 };
+struct NoNet {};
 
-__global__ void __launch_bounds__(256)
+template <bool kNet>
+__global__ void __launch_bounds__(2 * kFeatCells)
 mlp_features_kernel(MlpSet S, int s0, int stride, const double* __restrict__ B, int nx, int ny,
-                    unsigned short* __restrict__ x, double* __restrict__ scale) {
+                    unsigned short* __restrict__ x, double* __restrict__ scale, const float* __restrict__ P,
+                    float* __restrict__ y) {
     __shared__ FeatLds L;
+    __shared__ typename std::conditional<kNet, NetLds, NoNet>::type N;
     const int sp = blockIdx.z;
     const double* __restrict__ M = S.M[sp];
     const double m = S.m[sp];
     const int species = s0 + sp;
-    x += (size_t)sp * nx * ny * kIn;
+    if constexpr (kNet) {
+        y += (size_t)sp * nx * ny * kOutPad;
+        load_net(P, N, nullptr);
+    } else {
+        x += (size_t)sp * nx * ny * kIn;
+    }
     scale += (size_t)sp * nx * ny;
     const int i0 = blockIdx.x * kFeatCols, j0 = blockIdx.y * kFeatRows;
     const int tid = threadIdx.x;
-    for (int q = tid; q < (kFeatRows + 2) * (kFeatCols + 2); q += blockDim.x) {
+    for (int q = tid; q < (kFeatRows + 2) * (kFeatCols + 2); q += 2 * kFeatCells) {
         const int rr = q / (kFeatCols + 2), cc = q % (kFeatCols + 2);
         double* d = L.nut[rr][cc];
         int jj = j0 - 1 + rr;
@@ -294,66 +335,94 @@ mlp_features_kernel(MlpSet S, int s0, int stride, const double* __restrict__ B, 
         for (int k = 0; k < 6; ++k) d[4 + k] = TT[k];
     }
     __syncthreads();
-    const int r = tid / kFeatCols, cl = tid % kFeatCols;
+    const bool second = tid >= kFeatCells;         // wave-uniform: which part of the features
+    const int ct = tid & (kFeatCells - 1);
+    const int r = ct / kFeatCols, cl = ct % kFeatCols;
     const int i = i0 + cl, j = j0 + r;
     const bool valid = i < nx && j < ny;
-    float f[64];    // features are rounded to FP32 (then BF16) anyway
+    float f[34];    // features are rounded to FP32 (then BF16) anyway
 #pragma unroll
-    for (int k = 0; k < 64; ++k) f[k] = 0.f;
+    for (int k = 0; k < 34; ++k) f[k] = 0.f;
     double sc = 0.0;
     if (valid) {
         const double* C = L.nut[r + 1][cl + 1];
         const double n0 = C[0];
-        const double u0[3] = {C[1], C[2], C[3]};
-        double T0[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) T0[k] = C[4 + k];
-        const double Tref = (T0[0] + T0[3] + T0[5]) / 3.0;
+        const double Tref = (C[4] + C[7] + C[9]) / 3.0;
         if (n0 > 1e-12 && Tref > 0.0) {
             const double vt = sqrt(Tref / m);
             const double ivt = 1.0 / vt, iT = 1.0 / Tref, in0 = 1.0 / n0;
             sc = n0 * m * vt * vt * vt;
-            f[0] = (float)(u0[0] * ivt);
-            f[1] = (float)(u0[1] * ivt);
-            f[2] = (float)(u0[2] * ivt);
+            // five stencil fields n/n_c, u/v_t, T/T_ref at offset (dj, di)
+            auto differences = [&](int k0, float* out) {
 #pragma unroll
-            for (int k = 0; k < 6; ++k) f[3 + k] = (float)(T0[k] * iT);
-            // stencil fields n/n_c, u/v_t, T/T_ref at offset (dj, di)
+                for (int q = 0; q < 5; ++q) {
+                    const int k = k0 + q;
+                    const double sk = k == 0 ? in0 : (k < 4 ? ivt : iT);
+                    auto P = [&](int dj, int di) { return L.nut[r + 1 + dj][cl + 1 + di][k] * sk; };
+                    const double c0 = P(0, 0);
+                    out[5 * q + 0] = (float)((P(0, 1) - P(0, -1)) / 2.0);
+                    out[5 * q + 1] = (float)((P(1, 0) - P(-1, 0)) / 2.0);
+                    out[5 * q + 2] = (float)(P(0, 1) - 2.0 * c0 + P(0, -1));
+                    out[5 * q + 3] = (float)(P(1, 0) - 2.0 * c0 + P(-1, 0));
+                    out[5 * q + 4] = (float)((P(1, 1) - P(-1, 1) - P(1, -1) + P(-1, -1)) / 4.0);
+                }
+            };
+            if (!second) {         // features 0 .. 33
+                f[0] = (float)(C[1] * ivt);
+                f[1] = (float)(C[2] * ivt);
+                f[2] = (float)(C[3] * ivt);
 #pragma unroll
-            for (int k = 0; k < 10; ++k) {
-                const double sk = k == 0 ? in0 : (k < 4 ? ivt : iT);
-                auto P = [&](int dj, int di) { return L.nut[r + 1 + dj][cl + 1 + di][k] * sk; };
-                const double c0 = P(0, 0);
-                f[9 + 5 * k + 0] = (float)((P(0, 1) - P(0, -1)) / 2.0);
-                f[9 + 5 * k + 1] = (float)((P(1, 0) - P(-1, 0)) / 2.0);
-                f[9 + 5 * k + 2] = (float)(P(0, 1) - 2.0 * c0 + P(0, -1));
-                f[9 + 5 * k + 3] = (float)(P(1, 0) - 2.0 * c0 + P(-1, 0));
-                f[9 + 5 * k + 4] = (float)((P(1, 1) - P(-1, 1) - P(1, -1) + P(-1, -1)) / 4.0);
-            }
-            f[59 + species] = 1.f;
-            if (B) {     // direction of the cell-centred magnetic field
-                const long long c = (long long)j * nx + i;
-                const double bx = B[c * 3], by = B[c * 3 + 1], bz = B[c * 3 + 2];
-                const double bn = sqrt(bx * bx + by * by + bz * bz);
-                if (bn > 1e-12) {
-                    f[61] = (float)(bx / bn);
-                    f[62] = (float)(by / bn);
-                    f[63] = (float)(bz / bn);
+                for (int k = 0; k < 6; ++k) f[3 + k] = (float)(C[4 + k] * iT);
+                differences(0, f + 9);
+            } else {               // features 34 .. 63
+                differences(5, f);
+                if (species == 0) f[25] = 1.f;
+                else f[26] = 1.f;
+                if (B) {     // direction of the cell-centred magnetic field
+                    const long long c = (long long)j * nx + i;
+                    const double bx = B[c * 3], by = B[c * 3 + 1], bz = B[c * 3 + 2];
+                    const double bn = sqrt(bx * bx + by * by + bz * bz);
+                    if (bn > 1e-12) {
+                        f[27] = (float)(bx / bn);
+                        f[28] = (float)(by / bn);
+                        f[29] = (float)(bz / bn);
+                    }
                 }
             }
         }
     }
     __syncthreads();     // every read of the stencil values is done: the union now holds the output
+    auto pack = [&](int k) { return bf16_of(f[2 * k]) | ((unsigned)bf16_of(f[2 * k + 1]) << 16); };
+    if (!second) {
 #pragma unroll
-    for (int k = 0; k < 32; ++k) L.out[tid][k] = bf16_of(f[2 * k]) | ((unsigned)bf16_of(f[2 * k + 1]) << 16);
-    __syncthreads();
-    for (int q = tid; q < kFeatRows * kFeatCols * 32; q += blockDim.x) {
-        const int rr = q >> 5, part = q & 31;
-        const int ii = i0 + rr % kFeatCols, jj = j0 + rr / kFeatCols;
-        if (ii < nx && jj < ny)
-            reinterpret_cast<unsigned*>(x + ((long long)jj * nx + ii) * kIn)[part] = L.out[rr][part];
+        for (int k = 0; k < 17; ++k) L.out[ct][k] = pack(k);
+        if (valid) scale[(long long)j * nx + i] = sc;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 15; ++k) L.out[ct][17 + k] = pack(k);
     }
-    if (valid) scale[(long long)j * nx + i] = sc;
+    __syncthreads();
+    if constexpr (kNet) {
+        const int lane = tid & 63, s = lane & 15, g = lane >> 4;
+#pragma unroll 1
+        for (int t = tid / 64; t < kFeatCells / 16; t += 2 * kFeatCells / 64) {
+            const int cell = t * 16 + s;
+            uint2 v[4];
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) v[kb] = *reinterpret_cast<const uint2*>(&L.out[cell][8 * kb + 2 * g]);
+            Tile T;
+            forward_from(v, N, false, T);
+            const int ii = i0 + cell % kFeatCols, jj = j0 + cell / kFeatCols;
+            if (ii < nx && jj < ny) *reinterpret_cast<f32x4*>(y + ((long long)jj * nx + ii) * kOutPad + 4 * g) = T.y;
+        }
+    } else {
+        for (int q = tid; q < kFeatCells * 32; q += 2 * kFeatCells) {
+            const int rr = q >> 5, part = q & 31;
+            const int ii = i0 + rr % kFeatCols, jj = j0 + rr / kFeatCols;
+            if (ii < nx && jj < ny)
+                reinterpret_cast<unsigned*>(x + ((long long)jj * nx + ii) * kIn)[part] = L.out[rr][part];
+        }
+    }
 }
 
 // Heat-flux tensor of one cell from its raw moments (TRIPLES order).
@@ -673,8 +742,16 @@ constexpr int kJudgeBlocks = 256;
 hipError_t launch_mlp_features_set(const MlpSet& S, int ns, int s0, int stride, const double* B, int nx, int ny,
                                    unsigned short* x, double* scale, hipStream_t st) {
     if (ns < 1 || ns > 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(mlp_features_kernel, dim3((nx + kFeatCols - 1) / kFeatCols, (ny + kFeatRows - 1) / kFeatRows, ns),
-                       dim3(kFeatRows * kFeatCols), 0, st, S, s0, stride, B, nx, ny, x, scale);
+    hipLaunchKernelGGL(mlp_features_kernel<false>, dim3((nx + kFeatCols - 1) / kFeatCols, (ny + kFeatRows - 1) / kFeatRows, ns),
+                       dim3(2 * kFeatCells), 0, st, S, s0, stride, B, nx, ny, x, scale, nullptr, nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_network_set(const MlpSet& S, int ns, int s0, int stride, const double* B, int nx, int ny,
+                                  const float* params, double* scale, float* y, hipStream_t st) {
+    if (ns < 1 || ns > 2) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(mlp_features_kernel<true>, dim3((nx + kFeatCols - 1) / kFeatCols, (ny + kFeatRows - 1) / kFeatRows, ns),
+                       dim3(2 * kFeatCells), 0, st, S, s0, stride, B, nx, ny, nullptr, scale, params, y);
     return hipGetLastError();
 }
 

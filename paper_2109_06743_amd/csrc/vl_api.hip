@@ -169,9 +169,8 @@ size_t fluid_doubles(const vl_config& c) {
     return 9 * (size_t)c.nx;
 }
 
-// Learned-closure scratch of the step: features (BF16 [cells][64] = 16
-// doubles per cell), scale (1), network outputs (FP32 [cells][16] = 8), judge
-// partials behind 45 doubles per cell.
+// Learned-closure scratch of the step: network outputs (FP32 [cells][16] = 8
+// doubles per cell), scale (1), judge partials behind 45 doubles per cell.
 size_t mlp_step_doubles(const vl_config& c) {
     if (c.closure != VL_CLOSURE_MLP) return 0;
     const size_t cells = (size_t)c.nx * c.ny;
@@ -179,8 +178,9 @@ size_t mlp_step_doubles(const vl_config& c) {
 }
 
 // Fluid-only closure step: the step's field arrays (18 per cell), U1 and U2 of
-// two species (40) and the network's features, scales and outputs of two
-// species (50), with some to spare.
+// two species (40), the network's outputs and scales of two species (18) and
+// the Yee fields between the half steps (6 and 3 per column), with some to
+// spare.
 size_t fluid_closure_doubles(const vl_config& c) {
     const size_t cells = (size_t)c.nx * c.ny;
     return 18 * cells + fluid_doubles(c) + 20 * cells + 6 * cells + 25 * cells + 2;
@@ -320,12 +320,12 @@ vl_status fluid_step_impl(vl_ctx* ctx, int s, double* U, const double* mom_t, co
     return VL_OK;
 }
 
-// One fluid RK stage of all species with the network's heat flux: features
-// and outputs of the stage state (one launch each), then the stage.  G: the
+// One fluid RK stage of all species with the network's heat flux: its outputs
+// for the stage state, then the stage.  G: the
 // stage's state buffers (and the kinetic third moments for species whose
 // fallback flag is set).
-hipError_t network_stage(vl_ctx* ctx, int ns, int k, vl::FluidSet& G, const float* params, unsigned short* x,
-                         double* scale, float* y, double wa, double wb, const double* E, const double* B, double dt,
+hipError_t network_stage(vl_ctx* ctx, int ns, int k, vl::FluidSet& G, const float* params, double* scale, float* y,
+                         double wa, double wb, const double* E, const double* B, double dt,
                          hipStream_t st) {
     const vl_config& c = ctx->cfg;
     vl::MlpSet F{};
@@ -336,8 +336,7 @@ hipError_t network_stage(vl_ctx* ctx, int ns, int k, vl::FluidSet& G, const floa
         G.y[s] = y + (size_t)s * ctx->cells * 16;
         G.scale[s] = scale + (size_t)s * ctx->cells;
     }
-    hipError_t e = vl::launch_mlp_features_set(F, ns, 0, 10, B, c.nx, c.ny, x, scale, st);
-    if (e == hipSuccess) e = vl::launch_mlp_forward(params, x, ns * ctx->cells, y, st);
+    const hipError_t e = vl::launch_mlp_network_set(F, ns, 0, 10, B, c.nx, c.ny, params, scale, y, st);
     if (e != hipSuccess) return e;
     return vl::launch_fluid_stage_3v_set(G, ns, vl::kThirdNetwork, k, wa, wb, E, B, dt, c.nx, c.ny, dx_of(c),
                                          dy_of(c), st, per_y(c));
@@ -356,7 +355,6 @@ vl_status fluid_step_mlp_all(vl_ctx* ctx, const vl_state* S, const double* E_t, 
     const int ns = c.nspecies;
     const long long cells = ctx->cells;
     float* y = (float*)mwork;                           // 16-byte aligned (the caller aligns mwork)
-    unsigned short* x = (unsigned short*)(mwork + 8 * ns * cells);
     double* scale = mwork + 24 * ns * cells;
     double* part = mwork + 45 * ns * cells;
     Timed tm(ctx, VL_T_FLUID, st);
@@ -367,8 +365,7 @@ vl_status fluid_step_mlp_all(vl_ctx* ctx, const vl_state* S, const double* E_t, 
         J.fallback[s] = S->closure_fallback + s;
         J.err[s] = S->closure_err + s;
     }
-    VL_HIP(vl::launch_mlp_features_set(J, ns, 0, 20, B_t1, c.nx, c.ny, x, scale, st));
-    VL_HIP(vl::launch_mlp_forward(S->mlp_params, x, ns * cells, y, st));
+    VL_HIP(vl::launch_mlp_network_set(J, ns, 0, 20, B_t1, c.nx, c.ny, S->mlp_params, scale, y, st));
     VL_HIP(vl::launch_mlp_judge_set(J, ns, scale, y, cells, c.closure_tol, part, st));
     const double wa[3] = {1.0, 1.0, 0.5}, wb[3] = {0.0, 0.0, 0.5};
     const double* E[3] = {E_t, E_t1, E_th};
@@ -381,7 +378,7 @@ vl_status fluid_step_mlp_all(vl_ctx* ctx, const vl_state* S, const double* E_t, 
             G.QB[s] = S->mom_pre[s];
             G.fallback[s] = S->closure_fallback + s;
         }
-        VL_HIP(network_stage(ctx, ns, k, G, S->mlp_params, x, scale, y, wa[k], wb[k], E[k], B[k], dt, st));
+        VL_HIP(network_stage(ctx, ns, k, G, S->mlp_params, scale, y, wa[k], wb[k], E[k], B[k], dt, st));
     }
     return VL_OK;
 }
@@ -408,18 +405,14 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
     double* mw = fwork + 40 * cells;
     mw += ((uintptr_t)mw & 15u) ? 1 : 0;                 // network outputs are stored as 16-byte vectors
     float* y = (float*)mw;
-    unsigned short* x = (unsigned short*)(mw + 8 * ns * cells);
-    double* scale = mw + 24 * ns * cells;
+    double* scale = mw + 8 * ns * cells;
     const double* Uc[2] = {S->U[0], ns > 1 ? S->U[1] : nullptr};
-    // the fields after the first half step wait behind U1, U2 of both species;
-    // the network's scratch fills that space, so with it they go back at once
-    double* yee1 = mw;
+    // the fields after the first half step wait behind the network's outputs
+    double* yee1 = mw + 9 * ns * cells;
     {
         Timed tm(ctx, VL_T_FIELDS, st);
         VL_HIP(vl::launch_yee_half(S->fields, yee1, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), 10, per_y(c),
                                    {E_t, B_t}, {E_h, B_h}, {E_1, B_1}, st));
-        if (closure == VL_FLUID_MLP)
-            VL_HIP(hipMemcpyAsync(S->fields, yee1, yee_doubles(c) * sizeof(double), hipMemcpyDeviceToDevice, st));
     }
     {
         Timed tm(ctx, VL_T_FLUID, st);
@@ -439,16 +432,12 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
                 VL_HIP(vl::launch_fluid_stage_3v_set(G, ns, vl::kThirdGradient, k, 0.0, 0.0, E[k], B[k], dt, c.nx,
                                                      c.ny, dx_of(c), dy_of(c), st, per_y(c)));
             else
-                VL_HIP(network_stage(ctx, ns, k, G, S->mlp_params, x, scale, y, 0.0, 0.0, E[k], B[k], dt, st));
+                VL_HIP(network_stage(ctx, ns, k, G, S->mlp_params, scale, y, 0.0, 0.0, E[k], B[k], dt, st));
         }
     }
     Timed tm(ctx, VL_T_FIELDS, st);
-    if (closure == VL_FLUID_MLP)
-        VL_HIP(vl::launch_maxwell_half(S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), st, 10,
-                                       per_y(c)));
-    else
-        VL_HIP(vl::launch_yee_half(yee1, S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), 10, per_y(c),
-                                   {}, {}, {}, st));
+    VL_HIP(vl::launch_yee_half(yee1, S->fields, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), 10, per_y(c), {},
+                               {}, {}, st));
     return VL_OK;
 }
 

@@ -216,6 +216,9 @@ struct MlpSet {
 };
 hipError_t launch_mlp_features_set(const MlpSet& S, int ns, int s0, int stride, const double* B, int nx, int ny,
                                    unsigned short* x, double* scale, hipStream_t st);
+// Features and network in one launch: outputs y [cells][16] and scales.
+hipError_t launch_mlp_network_set(const MlpSet& S, int ns, int s0, int stride, const double* B, int nx, int ny,
+                                  const float* params, double* scale, float* y, hipStream_t st);
 hipError_t launch_mlp_judge_set(const MlpSet& S, int ns, const double* scale, const float* y, long long cells,
                                 double tol, double* part, hipStream_t st);
 hipError_t launch_mlp_features(const double* M, int stride, const double* B, int nx, int ny, double m, int species,

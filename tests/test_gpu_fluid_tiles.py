@@ -66,3 +66,25 @@ def test_gradient_stage_tiles(nx, ny, bc):
     ctx.sync()
     for s in range(2):
         assert rel_l2(host(fs.U[s], U[s].shape), ref["U"][s]) < 1e-12, s
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 2), (63, 3), (64, 4), (65, 5), (129, 9)])
+def test_network_tiles(nx, ny):
+    """Features and network in one kernel at the edges of its 64 x 4 tiles: a
+    step of the fluid model with the network closure, U to 2e-5 (the network
+    rounds activations to BF16, the oracle's does not)."""
+    from paper_2109_06743_amd import vl
+    cfg, U, F0 = W.gem_fluid(nx=nx, ny=ny, dt=1e-4)
+    rng = np.random.default_rng(nx * 100 + ny)
+    U = [u * (1 + 0.05 * rng.uniform(-1, 1, size=u.shape[:2] + (1,))) for u in U]
+    F = OF.Yee(nx, ny)
+    for k in ("Ex", "Ey", "Ez", "Bx", "By", "Bz"):
+        setattr(F, k, getattr(F0, k).copy())
+    net = W.mlp_init(3)
+    ctx = vl.Context(cfg, "f64")
+    fs = vl.FluidState(ctx, U, vl.yee_pack(F), mlp_params=net)
+    ctx.fluid_closure_step(fs, cfg["dt"], "mlp")
+    ref = OS.fluid_step_2x3v({"U": [u.copy() for u in U], "F": F}, cfg, cfg["dt"], "mlp", net)
+    ctx.sync()
+    for s in range(2):
+        assert rel_l2(host(fs.U[s], U[s].shape), ref["U"][s]) < 2e-5, s
