@@ -285,7 +285,7 @@ __device__ __forceinline__ bool local_nuT(const double* __restrict__ M, int stri
 // block's waves run the network on them, two 16-cell tiles each, and only the
 // outputs leave: the rows need not go through memory (2 x 128 B a cell) and a
 // launch goes.  256 x 128 cells, two species: 15.7 us for the features by one
-// thread per cell and 12.0 for the network, 16.5 in one.
+// thread per cell and 12.0 for the network, 15.2 in one.
 constexpr int kFeatCols = 64, kFeatRows = 4, kFeatCells = kFeatCols * kFeatRows;
 union FeatLds {
     double nut[kFeatRows + 2][kFeatCols + 2][11];   // n, u, T (padded against bank conflicts)

@@ -25,78 +25,6 @@ struct VGrid {
 
 __device__ __forceinline__ double vc(const VGrid& G, int d, int i) { return G.lo[d] + (i + 0.5) * G.dv[d]; }
 
-// 20 raw moments (already multiplied by dV, and by m for P and Q) of a block
-// held in shared memory with rows of length nvz at stride pz.  Result in
-// mom[] of every thread.  red: shared scratch of 20 * (blockDim/64) doubles.
-template <class T>
-__device__ void block_moments3(const T* blk, int pz, const VGrid& G, double (&mom)[20], double* red) {
-    double acc[20];
-#pragma unroll
-    for (int k = 0; k < 20; ++k) acc[k] = 0.0;
-    const int rows = G.nvx * G.nvy;
-    for (int r = threadIdx.x; r < rows; r += blockDim.x) {
-        const int ix = r / G.nvy, iy = r % G.nvy;
-        const T* row = blk + r * pz;
-        double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-        for (int iz = 0; iz < G.nvz; ++iz) {
-            const double f = (double)row[iz];
-            const double z = vc(G, 2, iz);
-            const double fz = f * z;
-            s0 += f;
-            s1 += fz;
-            s2 += fz * z;
-            s3 += fz * z * z;
-        }
-        const double X = vc(G, 0, ix), Y = vc(G, 1, iy);
-        const double X2 = X * X, Y2 = Y * Y, XY = X * Y;
-        acc[0] += s0;
-        acc[1] += X * s0;
-        acc[2] += Y * s0;
-        acc[3] += s1;
-        acc[4] += X2 * s0;      // xx
-        acc[5] += XY * s0;      // xy
-        acc[6] += X * s1;       // xz
-        acc[7] += Y2 * s0;      // yy
-        acc[8] += Y * s1;       // yz
-        acc[9] += s2;           // zz
-        acc[10] += X2 * X * s0; // xxx
-        acc[11] += X2 * Y * s0; // xxy
-        acc[12] += X2 * s1;     // xxz
-        acc[13] += X * Y2 * s0; // xyy
-        acc[14] += XY * s1;     // xyz
-        acc[15] += X * s2;      // xzz
-        acc[16] += Y2 * Y * s0; // yyy
-        acc[17] += Y2 * s1;     // yyz
-        acc[18] += Y * s2;      // yzz
-        acc[19] += s3;          // zzz
-    }
-    block_sum<20>(acc, red);
-    const double dV = G.dv[0] * G.dv[1] * G.dv[2];
-#pragma unroll
-    for (int k = 0; k < 20; ++k) mom[k] = acc[k] * (k < 4 ? dV : G.m * dV);
-}
-
-template <class T>
-__global__ void __launch_bounds__(256) moments3_kernel(const T* __restrict__ f, double* __restrict__ mom, VGrid G) {
-    extern __shared__ unsigned char smem_raw[];
-    T* blk = reinterpret_cast<T*>(smem_raw);
-    __shared__ double red[20 * 4];
-    const long long cell = blockIdx.x;
-    const int nv = G.nvx * G.nvy * G.nvz;
-    const int pz = G.nvz | 1;
-    const T* src = f + cell * nv;
-    for (int e = threadIdx.x; e < nv; e += blockDim.x) blk[e + row_of(e, G.inv_nvz) * (pz - G.nvz)] = src[e];
-    __syncthreads();
-    double m[20];
-    block_moments3(blk, pz, G, m, red);
-    if (threadIdx.x < 20) {
-        double v = 0;
-#pragma unroll
-        for (int k = 0; k < 20; ++k) v = (threadIdx.x == k) ? m[k] : v;
-        mom[cell * 20 + threadIdx.x] = v;
-    }
-}
-
 template <class T>
 __global__ void __launch_bounds__(256) moments1_kernel(const T* __restrict__ f, double* __restrict__ mom, int nv,
                                                        double vlo, double dv, double mass) {
@@ -163,142 +91,6 @@ __device__ __forceinline__ T expo(T x);
 template <> __device__ __forceinline__ float expo<float>(float x) { return __expf(x); }
 template <> __device__ __forceinline__ double expo<double>(double x) { return exp(x); }
 
-// Exponent -(m/2) w^T Tinv w with coefficients A = (m/2) Tinv (off-diagonals doubled).
-template <class T>
-struct Quad {
-    T axx, axy, axz, ayy, ayz, azz;
-    T ux, uy, uz;
-    __device__ __forceinline__ void set(const double (&inv)[6], const double (&u)[3], double m) {
-        const double h = 0.5 * m;
-        axx = (T)(h * inv[0]); axy = (T)(2.0 * h * inv[1]); axz = (T)(2.0 * h * inv[2]);
-        ayy = (T)(h * inv[3]); ayz = (T)(2.0 * h * inv[4]); azz = (T)(h * inv[5]);
-        ux = (T)u[0]; uy = (T)u[1]; uz = (T)u[2];
-    }
-    __device__ __forceinline__ T g(T vx, T vy, T vz) const {
-        const T wx = vx - ux, wy = vy - uy, wz = vz - uz;
-        const T q = wx * (axx * wx + axy * wy + axz * wz) + wy * (ayy * wy + ayz * wz) + azz * wz * wz;
-        return expo<T>(-q);
-    }
-};
-
-// Per-cell fit.  One block per spatial cell; the block's f values sit in
-// registers (EPT per thread, element e = tid + k * blockDim), the clipped f''
-// is staged in shared memory for the separable moment sums.
-template <class T, int EPT>
-__global__ void __launch_bounds__(256)
-fit3_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, double* __restrict__ U,
-            double* __restrict__ mom_post, unsigned long long* __restrict__ counters,
-            unsigned* __restrict__ clip_part, VGrid G, typename Bits<T>::U* __restrict__ max_out) {
-    extern __shared__ unsigned char smem_raw[];
-    T* blk = reinterpret_cast<T*>(smem_raw);
-    __shared__ double red[21 * 4];
-    const long long cell = blockIdx.x;
-    const int nv = G.nvx * G.nvy * G.nvz;
-    const int pz = G.nvz | 1;
-    const double dV = G.dv[0] * G.dv[1] * G.dv[2];
-    const T* src = fin + cell * nv;
-    T* dst = fout + cell * nv;
-
-    T fv[EPT];
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-        const int e = threadIdx.x + k * blockDim.x;
-        fv[k] = (e < nv) ? src[e] : T(0);
-    }
-
-    // cell parameters (every thread computes the same values)
-    double mp[10], Uc[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) { mp[k] = mom_pre[cell * 20 + k]; Uc[k] = U[cell * 10 + k]; }
-    const double nV = mp[0], nF = Uc[0];
-    double uV[3], TV[6], uF[3], TF[6], iV[6], iF[6];
-    bool ok = nV > 1e-12 && nF > 1e-12;
-    if (ok) {
-        u_and_T(mp + 1, nV, G.m, uV, TV);
-        u_and_T(Uc + 1, nF, G.m, uF, TF);
-        ok = spd_inverse(TV, iV) && spd_inverse(TF, iF);
-    }
-
-    T outv[EPT];
-    unsigned long long nclip = 0;
-    if (ok) {
-        Quad<T> qv, qf;
-        qv.set(iV, uV, G.m);
-        qf.set(iF, uF, G.m);
-        T gv[EPT], gf[EPT];
-        double sums[2] = {0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < EPT; ++k) {
-            const int e = threadIdx.x + k * blockDim.x;
-            gv[k] = T(0);
-            gf[k] = T(0);
-            if (e < nv) {
-                const int iz = e % G.nvz, r = e / G.nvz;
-                const T vx = (T)vc(G, 0, r / G.nvy), vy = (T)vc(G, 1, r % G.nvy), vz = (T)vc(G, 2, iz);
-                gv[k] = qv.g(vx, vy, vz);
-                gf[k] = qf.g(vx, vy, vz);
-                sums[0] += (double)gv[k];
-                sums[1] += (double)gf[k];
-            }
-        }
-        block_sum<2>(sums, red);
-        const T A = (T)(nV / (sums[0] * dV));
-        const T Bc = (T)(nV / (sums[1] * dV));
-#pragma unroll
-        for (int k = 0; k < EPT; ++k) {
-            const int e = threadIdx.x + k * blockDim.x;
-            const T x = fv[k] - A * gv[k] + Bc * gf[k];
-            if (e < nv && x < T(0)) ++nclip;
-            outv[k] = fmax(x, T(0));
-            if (e < nv) blk[(e / G.nvz) * pz + e % G.nvz] = outv[k];
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < EPT; ++k) {
-            const int e = threadIdx.x + k * blockDim.x;
-            outv[k] = fv[k];
-            if (e < nv) blk[(e / G.nvz) * pz + e % G.nvz] = fv[k];
-        }
-    }
-    __syncthreads();
-    double mm[20];
-    block_moments3(blk, pz, G, mm, red);
-    const double scale = ok ? nV / mm[0] : 1.0;
-    const T sc = (T)scale;
-    T mx = T(0);
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-        const int e = threadIdx.x + k * blockDim.x;
-        if (e < nv) {
-            const T o = ok ? outv[k] * sc : outv[k];
-            dst[e] = o;
-            mx = fmax(mx, o);
-        }
-    }
-    if (threadIdx.x < 20 && mom_post) {
-        double v = 0;
-#pragma unroll
-        for (int k = 0; k < 20; ++k) v = (threadIdx.x == k) ? mm[k] : v;
-        mom_post[cell * 20 + threadIdx.x] = v * scale;
-    }
-    if (ok && threadIdx.x < 10) {
-        const double r = nV / nF;
-        double v = 0;
-#pragma unroll
-        for (int k = 0; k < 10; ++k) v = (threadIdx.x == k) ? Uc[k] : v;
-        U[cell * 10 + threadIdx.x] = v * r;
-    }
-    if (counters) {
-        double c[1] = {(double)nclip};
-        block_sum<1>(c, red);
-        if (threadIdx.x == 0) {
-            clip_part[cell] = (unsigned)c[0];
-            if (!ok) atomicAdd(&counters[1], 1ull);
-        }
-    }
-    if (max_out) block_max_part(mx, max_out);
-}
-
 // ------------------------------------------------------- cubic blocks -------
 // Velocity blocks with N cells per axis: thread t < N*N owns the v_x pencil at
 // (v_y, v_z) = (t / N, t % N); element (ix, t) sits at t + N*N*ix, so the loads
@@ -318,6 +110,77 @@ __device__ __forceinline__ void pencil_moments(const double (&S)[4], double vy, 
     a[10] = S[3];       a[11] = vy * S[2];  a[12] = vz * S[2];  a[13] = vy2 * S[1];
     a[14] = vyz * S[1]; a[15] = vz2 * S[1]; a[16] = vy2 * vy * S[0];
     a[17] = vy2 * vz * S[0]; a[18] = vy * vz2 * S[0]; a[19] = vz2 * vz * S[0];
+}
+
+// Any velocity grid with axes up to 32: NW waves per cell (four cells per
+// 256-thread block with NW = 1, for the small blocks), thread t owns the v_x
+// pencils t, t + 64 NW, ... and reads them as they lie (unit stride over the
+// lanes), in code for exactly their length, so that a pencil's loads are in
+// flight together.  The kernel before took each cell through shared memory,
+// one v_z row per thread: 100 x 50 cells of 20x16x24 FP32 124 us in a step;
+// with eight loads in flight 69, this way 33 (4.6 TB/s).
+template <class T, int N>
+__device__ __forceinline__ void pencil_sums(const T* __restrict__ src, unsigned off, unsigned plane, const XTable& X,
+                                            double (&S)[4]) {
+    T v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = src[off + (unsigned)k * plane];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double g = (double)v[k];
+        S[0] += g;
+        S[1] = fma(g, X.v[k], S[1]);
+        S[2] = fma(g, X.v2[k], S[2]);
+        S[3] = fma(g, X.v3[k], S[3]);
+    }
+}
+
+// Runs VL_LEN(N) for the run-time length n in 2..32.
+#define VL_LENGTHS(n)                                                                                        \
+    switch (n) {                                                                                             \
+        VL_LEN(2) VL_LEN(3) VL_LEN(4) VL_LEN(5) VL_LEN(6) VL_LEN(7) VL_LEN(8) VL_LEN(9) VL_LEN(10)           \
+        VL_LEN(11) VL_LEN(12) VL_LEN(13) VL_LEN(14) VL_LEN(15) VL_LEN(16) VL_LEN(17) VL_LEN(18) VL_LEN(19)   \
+        VL_LEN(20) VL_LEN(21) VL_LEN(22) VL_LEN(23) VL_LEN(24) VL_LEN(25) VL_LEN(26) VL_LEN(27) VL_LEN(28)   \
+        VL_LEN(29) VL_LEN(30) VL_LEN(31) VL_LEN(32)                                                          \
+    }
+
+template <class T, int NW>
+__global__ void __launch_bounds__(256)
+moments3_kernel(const T* __restrict__ f, double* __restrict__ mom, long long cells, VGrid G, XTable X) {
+    __shared__ double red[NW == 1 ? 1 : 4 * 20];
+    __shared__ double fin_s[20];
+    const int tid = threadIdx.x & (64 * NW - 1), lane = threadIdx.x & 63;
+    const long long cell = NW == 1 ? (long long)xcd_work_index(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)
+                                   : (long long)xcd_work_index(blockIdx.x, gridDim.x);
+    if (NW == 1 && cell >= cells) return;
+    const int npen = G.nvy * G.nvz;
+    const T* src = f + cell * npen * G.nvx;
+    double acc[20];
+#pragma unroll
+    for (int q = 0; q < 20; ++q) acc[q] = 0.0;
+    for (int t = tid; t < npen; t += 64 * NW) {
+        double S[4] = {0.0, 0.0, 0.0, 0.0};
+#define VL_LEN(N)                                                          \
+    case N:                                                                \
+        pencil_sums<T, N>(src, (unsigned)t, (unsigned)npen, X, S);         \
+        break;
+        VL_LENGTHS(G.nvx)
+#undef VL_LEN
+        const int iy = row_of(t, G.inv_nvz);
+        double a[20];
+        pencil_moments(S, vc(G, 1, iy), vc(G, 2, t - iy * G.nvz), a);
+#pragma unroll
+        for (int q = 0; q < 20; ++q) acc[q] += a[q];
+    }
+    const double dV = G.dv[0] * G.dv[1] * G.dv[2];
+    if constexpr (NW == 1) {
+        int idx = 0, cnt = 20;
+        const double v = ReduceScatter<20, 32>::run(acc, lane, idx, cnt);
+        if ((lane & 1) == 0 && cnt > 0) mom[cell * 20 + idx] = v * (idx < 4 ? dV : G.m * dV);
+    } else {
+        block_sum_rs<20>(acc, red, fin_s);
+        if (threadIdx.x < 20) mom[cell * 20 + threadIdx.x] = fin_s[threadIdx.x] * (threadIdx.x < 4 ? dV : G.m * dV);
+    }
 }
 
 // One wave per cell (four cells per 256-thread block): lane l owns the v_x
@@ -828,6 +691,139 @@ fit3_stream_kernel(const T* fin, T* fout, const FitCell* __restrict__ P, double*
     if (max_out) block_max_part(mx, max_out);
 }
 
+// Moment fitting on any velocity grid with axes up to 32 (the general form of
+// fit3_cube_kernel): one block per cell, thread t owns the v_x pencils t,
+// t + blockDim, ...  A first pass over the grid sums the two Maxwellians (no
+// memory traffic), a second reads f, exchanges, clips, sums the moments and
+// leaves the result in shared memory, from where the same thread rescales and
+// stores it.  Between the passes the kinetic samples wait in that memory, the
+// fluid's are formed again.  exp(-q) with q summed in the order of Quad::g,
+// added in FP64.
+// 100 x 50 cells of 20x16x24 FP32: 283 us by the kernel that held 32 strided
+// elements per thread with their indices formed by division and row sums
+// through shared memory, now 99 (code for the exact pencil length, as in the
+// moments: 119, too many registers).
+template <class T>
+struct Quad {       // (m/2) w^T T^-1 w for fixed (v_y, v_z)
+    T axx, axz, azz, ux;
+    T wz, xy, yy, wy;      // w_z, a_xy w_y, a_yy w_y + a_yz w_z, w_y
+    __device__ __forceinline__ void set(const double* a, const double* u, T vy, T vz) {
+#pragma clang fp contract(off)
+        axx = (T)a[0];
+        axz = (T)(2.0 * a[2]);
+        ux = (T)u[0];
+        wy = vy - (T)u[1];
+        wz = vz - (T)u[2];
+        xy = wy * (T)(2.0 * a[1]);
+        yy = fma(wz, (T)(2.0 * a[4]), wy * (T)a[3]);
+        azz = wz * (T)a[5];
+    }
+    __device__ __forceinline__ T g(T vx) const {
+#pragma clang fp contract(off)
+        const T wx = vx - ux;
+        const T q = fma(wz, azz, fma(wy, yy, wx * fma(wz, axz, fma(wx, axx, xy))));
+        return expo<T>(-q);
+    }
+};
+
+template <class T>
+__global__ void __launch_bounds__(256)
+fit3_kernel(const T* fin, T* fout, const FitCell* __restrict__ P, double* __restrict__ mom_post,
+            unsigned* __restrict__ clip_part, VGrid G, XTable X, typename Bits<T>::U* __restrict__ max_out) {
+    extern __shared__ unsigned char smem_raw[];
+    T* blk = reinterpret_cast<T*>(smem_raw);
+    __shared__ double red[4 * 21];
+    __shared__ double fin_s[21];
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const long long cell = xcd_work_index(blockIdx.x, gridDim.x);
+    const int npen = G.nvy * G.nvz, nvx = G.nvx;
+    const double dV = G.dv[0] * G.dv[1] * G.dv[2];
+    const T* src = fin + cell * npen * nvx;
+    T* dst = fout + cell * npen * nvx;
+    const FitCell& C = P[cell];
+    const bool ok = C.ok != 0.0;
+    const double nV = C.nV;
+    T A = T(0), Bc = T(0);
+    auto at = [&](int t, Quad<T>& qv, Quad<T>& qf) {
+        const int iy = row_of(t, G.inv_nvz);
+        const T vy = (T)vc(G, 1, iy), vz = (T)vc(G, 2, t - iy * G.nvz);
+        qv.set(C.aV, C.uV, vy, vz);
+        qf.set(C.aF, C.uF, vy, vz);
+    };
+    if (ok) {
+        double s[2] = {0.0, 0.0};
+        for (int t = tid; t < npen; t += nthr) {
+            Quad<T> qv, qf;
+            at(t, qv, qf);
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll 4
+            for (int k = 0; k < nvx; ++k) {
+                const T gv = qv.g((T)X.v[k]);
+                blk[k * npen + t] = gv;
+                s0 += (double)gv;
+                s1 += (double)qf.g((T)X.v[k]);
+            }
+            s[0] += s0;
+            s[1] += s1;
+        }
+        block_sum_rs<2>(s, red, fin_s);
+        A = (T)(nV / (fin_s[0] * dV));
+        Bc = (T)(nV / (fin_s[1] * dV));
+    }
+    double acc[21];
+#pragma unroll
+    for (int q = 0; q < 21; ++q) acc[q] = 0.0;
+    unsigned nclip = 0;
+    for (int t = tid; t < npen; t += nthr) {
+        Quad<T> qv, qf;
+        if (ok) at(t, qv, qf);
+        double S[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int k0 = 0; k0 < nvx; k0 += 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = k0 + u < nvx ? src[(unsigned)((k0 + u) * npen + t)] : T(0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (k0 + u >= nvx) break;
+                const int k = k0 + u;
+                T x = v[u];
+                if (ok) {
+                    x = fma(Bc, qf.g((T)X.v[k]), fma(-A, blk[k * npen + t], x));
+                    nclip += x < T(0) ? 1u : 0u;
+                    x = fmax(x, T(0));
+                }
+                blk[k * npen + t] = x;
+                const double g = (double)x;
+                S[0] += g;
+                S[1] = fma(g, X.v[k], S[1]);
+                S[2] = fma(g, X.v2[k], S[2]);
+                S[3] = fma(g, X.v3[k], S[3]);
+            }
+        }
+        const int iy = row_of(t, G.inv_nvz);
+        double a[20];
+        pencil_moments(S, vc(G, 1, iy), vc(G, 2, t - iy * G.nvz), a);
+#pragma unroll
+        for (int q = 0; q < 20; ++q) acc[q] += a[q];
+    }
+    acc[20] = (double)nclip;
+    block_sum_rs<21>(acc, red, fin_s);
+    const double scale = ok ? nV / (fin_s[0] * dV) : 1.0;
+    const T sc = (T)scale;     // 1 exactly when the cell is skipped
+    T mx = T(0);
+    for (int t = tid; t < npen; t += nthr) {
+#pragma unroll 8
+        for (int k = 0; k < nvx; ++k) {
+            const T o = ok ? blk[k * npen + t] * sc : blk[k * npen + t];
+            dst[(unsigned)(k * npen + t)] = o;
+            mx = fmax(mx, o);
+        }
+    }
+    if (mom_post && tid < 20) mom_post[cell * 20 + tid] = fin_s[tid] * (tid < 4 ? dV : G.m * dV) * scale;
+    if (clip_part && tid == 0) clip_part[cell] = (unsigned)fin_s[20];
+    if (max_out) block_max_part(mx, max_out);
+}
+
 template <class T>
 __global__ void __launch_bounds__(256)
 fit1_kernel(const T* fin, T* fout, const double* __restrict__ mom_pre, const double* Uin, double* U,
@@ -958,9 +954,16 @@ hipError_t launch_moments3(const T* f, double* mom, long long cells, const VGrid
                                G, X);
         return hipGetLastError();
     }
-    const size_t shm = sizeof(T) * (size_t)a.nv[0] * a.nv[1] * (a.nv[2] | 1);
-    hipLaunchKernelGGL((moments3_kernel<T>), dim3((unsigned)cells), dim3(threads_for(a.nv[0] * a.nv[1])), shm, st, f,
-                       mom, G);
+    const XTable X = xtable(a);
+    // One wave per cell where that fills the chip (its reduction is a quarter of
+    // the work of four waves' and needs no barrier: 20000 cells of 10^3 34 us
+    // per call against 57) or where a wave has at most two pencils per lane; four waves
+    // for few large cells (1000 of 20x16x24: 9.8 us against 18.1).
+    if (a.nv[1] * a.nv[2] <= 128 || cells >= 4096)
+        hipLaunchKernelGGL((moments3_kernel<T, 1>), dim3((unsigned)((cells + 3) / 4)), dim3(256), 0, st, f, mom, cells,
+                           G, X);
+    else
+        hipLaunchKernelGGL((moments3_kernel<T, 4>), dim3((unsigned)cells), dim3(256), 0, st, f, mom, cells, G, X);
     return hipGetLastError();
 }
 
@@ -1110,20 +1113,16 @@ hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, 
                        long long cells, const VGridArgs& a, const MaxSink& sink, unsigned* clip_part,
                        double* scratch, hipStream_t st) {
     VGrid G{a.nv[0], a.nv[1], a.nv[2], {a.lo[0], a.lo[1], a.lo[2]}, {a.dv[0], a.dv[1], a.dv[2]}, a.m, 1.0f / (float)a.nv[2]};
-    const int nv = a.nv[0] * a.nv[1] * a.nv[2];
-    const size_t shm = sizeof(T) * (size_t)a.nv[0] * a.nv[1] * (a.nv[2] | 1);
-    const int threads = 256;
-    const int ept = (nv + threads - 1) / threads;
     auto* cnt = (unsigned long long*)counters;
     auto* mo = sink.target<T>(cells);
     unsigned* cp = cnt ? clip_part : nullptr;
     const int N = cube_edge(a);
+    const XTable X = xtable(a);
+    const dim3 grid((unsigned)cells);
+    FitCell* P = reinterpret_cast<FitCell*>(scratch);
+    hipLaunchKernelGGL(fit3_params_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, mom_pre, U, cells,
+                       a.m, N ? ExpK<T>::scale : 1.0, P, cnt);
     if (N) {
-        const XTable X = xtable(a);
-        const dim3 grid((unsigned)cells);
-        FitCell* P = reinterpret_cast<FitCell*>(scratch);
-        hipLaunchKernelGGL(fit3_params_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, mom_pre, U,
-                           cells, a.m, ExpK<T>::scale, P, cnt);
         // waves per cell and pencils per thread: every lane busy for 16^3, 3/4 for 12^3
         if constexpr (sizeof(T) == 4) {
             if (N == 16) hipLaunchKernelGGL((fit3_cube_kernel<T, 16, kFit16Waves, kFit16Pencils>), grid, dim3(64 * kFit16Waves), 0, st, fin, fout, P, mom_post, cp, G, X, mo);
@@ -1142,20 +1141,11 @@ hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, 
         }
         return hipGetLastError();
     }
-    if (ept <= 4)
-        hipLaunchKernelGGL((fit3_kernel<T, 4>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, cp, G, mo);
-    else if (ept <= 8)
-        hipLaunchKernelGGL((fit3_kernel<T, 8>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, cp, G, mo);
-    else if (ept <= 16)
-        hipLaunchKernelGGL((fit3_kernel<T, 16>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, cp, G, mo);
-    else if (ept <= 32)
-        hipLaunchKernelGGL((fit3_kernel<T, 32>), dim3((unsigned)cells), dim3(threads), shm, st, fin, fout, mom_pre, U,
-                           mom_post, cnt, cp, G, mo);
-    else
-        return hipErrorInvalidValue;
+    const int npen = a.nv[1] * a.nv[2];
+    const size_t shm = sizeof(T) * (size_t)a.nv[0] * npen;
+    int threads = pencil_threads(&npen, 1, shm, sizeof(T) == 4 ? 20 : 16, cells, false);
+    if (threads > 256) threads = 256;
+    hipLaunchKernelGGL((fit3_kernel<T>), grid, dim3(threads), shm, st, fin, fout, P, mom_post, cp, G, X, mo);
     return hipGetLastError();
 }
 

@@ -572,119 +572,201 @@ pfc_v1_kernel(const T* fin, T* fout, int nx, int nv, LineField S, double qm_tau_
 }
 
 // ---------------------------------------------------------------------------
-// 3V velocity operator V(tau): one block per spatial cell; the velocity block
-// lives in shared memory with rows along v_z padded to an odd length, so a
-// wave reading pencils along any of the three axes hits distinct banks.  Each
-// thread owns whole pencils of the current sweep (at most NMAX long) in
-// registers; the displaced results are written back in place.  The five
-// sweeps are vx(tau/2) vy(tau/2) vz(tau) vy(tau/2) vx(tau/2), each a uniform
-// shift by (q/m)(E_d + (v x B)_d) at the pencil's transverse velocities.
-template <class T, int NMAX>
-__device__ __forceinline__ void sweep3(T* blk, int d, double sigma, const V3Params& P, const double* EB,
-                                       T finf) {
-    const int nv[3] = {P.nvx, P.nvy, P.nvz};
+// 3V velocity operator V(tau) on any velocity grid (axes of 2 to 32 cells):
+// one block per spatial cell, the velocity block in shared memory with rows
+// along v_z padded to an odd length, so a wave reading pencils along any of the
+// three axes hits distinct banks.  The five sweeps are vx(tau/2) vy(tau/2)
+// vz(tau) vy(tau/2) vx(tau/2), each a uniform shift by
+// (q/m)(E_d + (v x B)_d) at the pencil's transverse velocities; a thread sweeps
+// whole pencils in registers.
+//
+// The pencil length is a run-time number, but each sweep runs code for exactly
+// that length (a switch, uniform over the launch): a pencil of 20 cells in code
+// for 32 with a window shifted by K, guards on every cell and unmerged
+// differences took 3.5 times the instructions.  The first v_x sweep reads its
+// pencils from global memory and the last writes them there (unit stride over
+// the lanes), which saves two passes through shared memory and a barrier.
+// 100 x 50 cells of 20x16x24 FP32: 578 us with one kernel for all lengths up
+// to 32, 131 this way (2.3 TB/s).  Bound by its vector instructions (13 per cell and sweep
+// besides the address of each access).
+
+// Partial flux factor of a cell with value w between neighbours at distance dm
+// below and dp above: phi = a X (the limited parabola of pfc_phi, the same
+// operations: results as if it were called).
+template <class T>
+__device__ __forceinline__ T flux_factor(T w, T dm, T dp, T c1, T c2, T finf) {
+    const T room = fmax(finf, w) - w;
+    const T w2 = w + w, r2 = room + room;
+    const T lp = med3(dp, -r2, w2), lm = med3(dm, -w2, r2);
+    return fma(lm, c2, fma(lp, c1, w));
+}
+
+// Sub-cell sweep of a pencil in registers, in its direction of motion.
+template <class T, int N>
+__device__ __forceinline__ void sweep_exact(T (&g)[N], T a, T c1, T c2, T finf) {
+#pragma clang fp contract(off)
+    T dm = g[0];                 // g_m - g_{m-1}, zero ghost below
+    T X = T(0), phi_prev = T(0);
+#pragma unroll
+    for (int m = 0; m < N - 1; ++m) {
+        const T dp = g[m + 1] - g[m];
+        X = flux_factor(g[m], dm, dp, c1, c2, finf);
+        const T phi = X * a;
+        g[m] = fmax((g[m] + phi_prev) - phi, T(0));
+        phi_prev = phi;
+        dm = dp;
+    }
+    g[N - 1] = fmax(fma(X, a, g[N - 1]), T(0));      // the wall face carries no flux
+}
+
+// A pencil in shared memory that moves by K >= 1 cells (element k at
+// first + k step, downwind order), in place from its far end: output p reads
+// cells up to p - K + 1, which outputs below p have not overwritten; the wall
+// cell keeps all that reaches it.
+template <class T>
+__device__ __attribute__((noinline)) void pencil_far(T* blk, int first, int step, int n, int K, T a, T c1, T c2,
+                                                      T finf) {
+#pragma clang fp contract(off)
+    auto val = [&](int k) -> T { return k >= 0 ? blk[first + k * step] : T(0); };
+    auto factor = [&](int k) {
+        const T w = val(k);
+        return flux_factor(w, w - val(k - 1), val(k + 1) - w, c1, c2, finf);
+    };
+    T top = T(0);
+    for (int m = n - 1 - K > 0 ? n - 1 - K : 0; m < n; ++m) top += val(m);
+    T X = factor(n - 2 - K);
+    const T wall = fmax(fma(X, a, top), T(0));
+    T phi = X * a;                                    // leaving window position p = n - 2
+    for (int p = n - 2; p >= 0; --p) {
+        const T w = val(p - K);
+        X = factor(p - 1 - K);
+        const T below = X * a;
+        // the cells at and above p are read by no later output
+        const T o = fmax((w + below) - phi, T(0));
+        blk[first + p * step] = o;
+        phi = below;
+    }
+    blk[first + (n - 1) * step] = wall;
+}
+
+// One pencil of N cells: kIn from global memory (else from shared), kOut to
+// global memory (else back to shared).  Element m lives at first + m step in
+// shared and goff + m gstep in global memory, in the direction of motion.
+template <class T, int N, bool kIn, bool kOut>
+__device__ __forceinline__ void pencil_exact(const T* __restrict__ src, T* __restrict__ dst, T* blk, unsigned goff,
+                                             unsigned gstep, int first, int step, const Shift<T>& sh, T finf, T& mx) {
+    T g[N];
+    if constexpr (kIn) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) g[m] = src[goff + (unsigned)m * gstep];
+    } else {
+#pragma unroll
+        for (int m = 0; m < N; ++m) g[m] = blk[first + m * step];
+    }
+    if (sh.K == 0) {
+        sweep_exact<T, N>(g, sh.a, sh.c1, sh.c2, finf);
+    } else {
+        // beyond n + 2 cells every output but the wall cell is 0 either way
+        const int K = sh.K > (long long)(N + 2) ? N + 2 : (int)sh.K;
+        if constexpr (kIn) {
+#pragma unroll
+            for (int m = 0; m < N; ++m) blk[first + m * step] = g[m];
+        }
+        pencil_far<T>(blk, first, step, N, K, sh.a, sh.c1, sh.c2, finf);
+#pragma unroll
+        for (int m = 0; m < N; ++m) g[m] = blk[first + m * step];
+    }
+    if constexpr (kOut) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            dst[goff + (unsigned)m * gstep] = g[m];
+            mx = fmax(mx, g[m]);
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < N; ++m) blk[first + m * step] = g[m];
+    }
+}
+
+template <class T, bool kIn, bool kOut>
+__device__ __forceinline__ void sweep_any(const T* __restrict__ src, T* __restrict__ dst, T* blk, int d, double sigma,
+                                          const V3Params& P, const double (&EB)[6], T finf, T& mx) {
     const int pz = P.nvz | 1;
-    const int n = nv[d];
-    const int npen = (P.nvx * P.nvy * P.nvz) / n;
+    const int n = d == 0 ? P.nvx : (d == 1 ? P.nvy : P.nvz);
+    const int npen = d == 0 ? P.nvy * P.nvz : (d == 1 ? P.nvx * P.nvz : P.nvx * P.nvy);
+    const int n2 = d == 2 ? P.nvy : P.nvz;            // second transverse axis
+    const float inv_n2 = d == 2 ? P.inv_nvy : P.inv_nvz;
     for (int pen = threadIdx.x; pen < npen; pen += blockDim.x) {
+        const int i1 = row_of(pen, inv_n2), i2 = pen - i1 * n2;
         int base, stride;
         double acc;
         if (d == 0) {           // pencil (iy, iz)
-            const int iy = pen / P.nvz, iz = pen % P.nvz;
-            base = iy * pz + iz;
+            base = i1 * pz + i2;
             stride = P.nvy * pz;
-            const double vy = P.lo[1] + (iy + 0.5) * P.dv[1], vz = P.lo[2] + (iz + 0.5) * P.dv[2];
+            const double vy = P.lo[1] + (i1 + 0.5) * P.dv[1], vz = P.lo[2] + (i2 + 0.5) * P.dv[2];
             acc = EB[0] + vy * EB[5] - vz * EB[4];
         } else if (d == 1) {    // pencil (ix, iz)
-            const int ix = pen / P.nvz, iz = pen % P.nvz;
-            base = ix * P.nvy * pz + iz;
+            base = i1 * P.nvy * pz + i2;
             stride = pz;
-            const double vx = P.lo[0] + (ix + 0.5) * P.dv[0], vz = P.lo[2] + (iz + 0.5) * P.dv[2];
+            const double vx = P.lo[0] + (i1 + 0.5) * P.dv[0], vz = P.lo[2] + (i2 + 0.5) * P.dv[2];
             acc = EB[1] + vz * EB[3] - vx * EB[5];
         } else {                // pencil (ix, iy)
-            const int ix = pen / P.nvy, iy = pen % P.nvy;
-            base = (ix * P.nvy + iy) * pz;
+            base = (i1 * P.nvy + i2) * pz;
             stride = 1;
-            const double vx = P.lo[0] + (ix + 0.5) * P.dv[0], vy = P.lo[1] + (iy + 0.5) * P.dv[1];
+            const double vx = P.lo[0] + (i1 + 0.5) * P.dv[0], vy = P.lo[1] + (i2 + 0.5) * P.dv[1];
             acc = EB[2] + vx * EB[4] - vy * EB[3];
         }
         const double s = P.qm * acc * sigma * P.inv_dv[d];
         const bool pos = s >= 0.0;
         const Shift<T> sh(fabs(s));
-        // beyond n + 2 cells every output but the wall cell is 0 either way
-        const int K = sh.K > (long long)(n + 2) ? n + 2 : (int)sh.K;
-        // pencil in upwind-to-downwind order: element k lives at first + k * step
         const int first = pos ? base : base + (n - 1) * stride;
         const int step = pos ? stride : -stride;
-        // shifted window W[j + 2] = g_{j - K} for j = -2 .. n-1 (zero outside the box),
-        // so output p reads W at static positions p-2 .. p+1
-        T W[NMAX + 2];
-#pragma unroll
-        for (int j = -2; j < NMAX; ++j) {
-            const int src = j - K;
-            const bool in = j < n && src >= 0;
-            const T v = blk[first + (in ? src : 0) * step];
-            W[j + 2] = in ? v : T(0);
-        }
-        // wall cell: every cell that reaches it stays, plus the partial flux of
-        // the cell K below: sum_{m >= n-1-K} g_m + phi(g_{n-3-K}, g_{n-2-K}, g_{n-1-K})
-        T top = T(0);
-        for (int m = (n - 1 - K > 0 ? n - 1 - K : 0); m < n; ++m) top += blk[first + m * step];
-#pragma unroll
-        for (int p = 0; p < NMAX; ++p)
-            if (p == n - 1) top += pfc_phi(W[p], W[p + 1], W[p + 2], sh.a, sh.c1, sh.c2, finf);
-        T phi_prev = pfc_phi(W[0], W[1], W[2], sh.a, sh.c1, sh.c2, finf);   // phi at window position -1
-#pragma unroll
-        for (int p = 0; p < NMAX; ++p) {
-            // W[p + 3] exists for p < NMAX - 1; the last position is the wall cell or unused
-            const T wn = (p + 3 < NMAX + 2) ? W[(p + 3 < NMAX + 2) ? p + 3 : NMAX + 1] : T(0);
-            const T phi_next = pfc_phi(W[p + 1], W[p + 2], wn, sh.a, sh.c1, sh.c2, finf);
-            const T o = (p == n - 1) ? top : W[p + 2] + phi_prev - phi_next;
-            phi_prev = phi_next;
-            if (p < n) blk[first + p * step] = fmax(o, T(0));
+        const unsigned plane = (unsigned)(P.nvy * P.nvz);
+        const unsigned goff = pos ? (unsigned)pen : (unsigned)pen + (unsigned)(n - 1) * plane;
+        const unsigned gstep = pos ? plane : 0u - plane;
+        switch (n) {
+#define VL_LEN(N)                                                                                     \
+    case N:                                                                                           \
+        pencil_exact<T, N, kIn, kOut>(src, dst, blk, goff, gstep, first, step, sh, finf, mx);         \
+        break;
+            VL_LEN(2) VL_LEN(3) VL_LEN(4) VL_LEN(5) VL_LEN(6) VL_LEN(7) VL_LEN(8) VL_LEN(9) VL_LEN(10) VL_LEN(11)
+            VL_LEN(12) VL_LEN(13) VL_LEN(14) VL_LEN(15) VL_LEN(16) VL_LEN(17) VL_LEN(18) VL_LEN(19) VL_LEN(20)
+            VL_LEN(21) VL_LEN(22) VL_LEN(23) VL_LEN(24) VL_LEN(25) VL_LEN(26) VL_LEN(27) VL_LEN(28) VL_LEN(29)
+            VL_LEN(30) VL_LEN(31) VL_LEN(32)
+#undef VL_LEN
         }
     }
 }
 
-template <class T, int NMAX, bool kFold>
-__global__ void __launch_bounds__(256)
+template <class T>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 pfc_v3_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B,
               V3Params P, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
     T* blk = reinterpret_cast<T*>(smem_raw);
-    __shared__ double EB[6];
-    const long long cell = blockIdx.x;
+    const long long cell = xcd_work_index(blockIdx.x, gridDim.x);
     const int nv = P.nvx * P.nvy * P.nvz;
-    const int pz = P.nvz | 1;
-    const T finf = max_of<T, kFold>(finf_r);
-    if (threadIdx.x < 3) {
-        EB[threadIdx.x] = E[cell * 3 + threadIdx.x];
-        EB[3 + threadIdx.x] = B ? B[cell * 3 + threadIdx.x] : 0.0;
+    const T finf = max_of<T, true>(finf_r);
+    double eb[6];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        eb[k] = E[cell * 3 + k];
+        eb[3 + k] = B ? B[cell * 3 + k] : 0.0;
     }
     const T* src = fin + cell * nv;
-    for (int e = threadIdx.x; e < nv; e += blockDim.x) blk[e + row_of(e, P.inv_nvz) * (pz - P.nvz)] = src[e];
-    __syncthreads();
-    double ebl[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) ebl[k] = EB[k];
-    const double half = 0.5 * P.tau;
-    sweep3<T, NMAX>(blk, 0, half, P, ebl, finf);
-    __syncthreads();
-    sweep3<T, NMAX>(blk, 1, half, P, ebl, finf);
-    __syncthreads();
-    sweep3<T, NMAX>(blk, 2, P.tau, P, ebl, finf);
-    __syncthreads();
-    sweep3<T, NMAX>(blk, 1, half, P, ebl, finf);
-    __syncthreads();
-    sweep3<T, NMAX>(blk, 0, half, P, ebl, finf);
-    __syncthreads();
     T* dst = fout + cell * nv;
+    const double half = 0.5 * P.tau;
     T mx = T(0);
-    for (int e = threadIdx.x; e < nv; e += blockDim.x) {
-        const T o = blk[e + row_of(e, P.inv_nvz) * (pz - P.nvz)];
-        dst[e] = o;
-        mx = fmax(mx, o);
+    sweep_any<T, true, false>(src, dst, blk, 0, half, P, eb, finf, mx);
+    __syncthreads();
+    // one copy of the in-block code: vy, vz, vy
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        const int d = k == 1 ? 2 : 1;
+        sweep_any<T, false, false>(src, dst, blk, d, d == 2 ? P.tau : half, P, eb, finf, mx);
+        __syncthreads();
     }
+    sweep_any<T, false, true>(src, dst, blk, 0, half, P, eb, finf, mx);
     if (max_out) block_max_part(mx, max_out);
 }
 
@@ -1485,17 +1567,41 @@ size_t v3_shared_bytes(int nvx, int nvy, int nvz, size_t elem) {
     return elem * (size_t)nvx * nvy * (nvz | 1);
 }
 
+// Threads per block for a kernel whose blocks (one per cell) run n rounds over
+// pens[0..n) pencils, one pencil per thread: the count that takes the least
+// time if lane slots go through at a rate set by the waves resident on a CU
+// (as many blocks as its LDS, its registers -- `cap` waves -- and the number of
+// cells allow).  V, FP32, per call: 5000 cells of 20x16x24 373 us with 64
+// threads, 244 with 128, 191 with 256 (the LDS holds five blocks); 200 such
+// cells 117, 75, 58, and 36 with 512; 20000 cells of 10^3 101 with 64, 144 with
+// 256 (100 pencils).  Ties go to more threads if `wide`, else to fewer.
+int pencil_threads(const int* pens, int n, size_t lds, int cap, long long cells, bool wide) {
+    const long long cus = xy_cus();
+    long long held = 163840 / (lds + 256);
+    const long long per_cu = (cells + cus - 1) / cus;
+    if (per_cu < held) held = per_cu;
+    int best = 64;
+    double best_cost = 0.0;
+    for (int t = 64; t <= 512; t *= 2) {
+        const int w = t / 64;
+        long long blocks = cap / w < held ? cap / w : held;
+        if (blocks < 1) blocks = 1;
+        long long slots = 0;
+        for (int k = 0; k < n; ++k) slots += (long long)((pens[k] + t - 1) / t) * t;
+        const double cost = (double)slots / (double)(blocks * w);
+        if (t == 64 || cost < best_cost || (wide && cost == best_cost)) {
+            best = t;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 template <class T>
 hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E, const double* B,
                          const V3Params& P, MaxRef finf, const MaxSink& sink, hipStream_t st) {
     const int nmax = P.nvx > P.nvy ? (P.nvx > P.nvz ? P.nvx : P.nvz) : (P.nvy > P.nvz ? P.nvy : P.nvz);
     const size_t shm = v3_shared_bytes(P.nvx, P.nvy, P.nvz, sizeof(T));
-    int maxpen = P.nvx * P.nvy;
-    if (P.nvx * P.nvz > maxpen) maxpen = P.nvx * P.nvz;
-    if (P.nvy * P.nvz > maxpen) maxpen = P.nvy * P.nvz;
-    int threads = ((maxpen + 63) / 64) * 64;
-    if (threads > 256) threads = 256;
-    if (threads < 64) threads = 64;
     const bool cube = P.nvx == P.nvy && P.nvy == P.nvz;
     auto* mo = sink.target<T>(cells);
     const dim3 grid((unsigned)cells);
@@ -1515,12 +1621,10 @@ hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E
         hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, 12, 192, true> : pfc_v3_cube_kernel<T, 12, 192, false>), grid, dim3(192), 0, st, fin, fout, E, B, P, finf, mo);
     } else if (cube && P.nvx == 8) {
         hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, 8, 64, true> : pfc_v3_cube_kernel<T, 8, 64, false>), grid, dim3(64), 0, st, fin, fout, E, B, P, finf, mo);
-    } else if (nmax <= 8) {
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_kernel<T, 8, true> : pfc_v3_kernel<T, 8, false>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
-    } else if (nmax <= 16) {
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_kernel<T, 16, true> : pfc_v3_kernel<T, 16, false>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
     } else if (nmax <= 32) {
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_kernel<T, 32, true> : pfc_v3_kernel<T, 32, false>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
+        const int pens[5] = {P.nvy * P.nvz, P.nvx * P.nvz, P.nvx * P.nvy, P.nvx * P.nvz, P.nvy * P.nvz};
+        const int threads = pencil_threads(pens, 5, shm, sizeof(T) == 4 ? 16 : 8, cells, true);
+        hipLaunchKernelGGL((pfc_v3_kernel<T>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
     } else {
         return hipErrorInvalidValue;
     }

@@ -236,6 +236,7 @@ vl_status advect_v_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double
     P.qm = sp.q / sp.m;
     P.tau = tau;
     P.inv_nvz = 1.0f / (float)sp.nv[2];
+    P.inv_nvy = 1.0f / (float)sp.nv[1];
     if (c.vsplit == VL_VSPLIT_BACKSUB)
         VL_HIP((vl::launch_pfc_v3b<T>(fin, fout, ctx->cells, E, B, P, finf, sink, st)));
     else

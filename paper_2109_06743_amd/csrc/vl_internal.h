@@ -53,7 +53,7 @@ struct V3Params {
     int nvx, nvy, nvz;
     double lo[3], dv[3], inv_dv[3];
     double qm, tau;
-    float inv_nvz;   // 1/nvz, for the exact row index (e + 0.5) / nvz of small e
+    float inv_nvz, inv_nvy;   // 1/nvz, 1/nvy, for the exact row index (e + 0.5) / nvz of small e
 };
 
 // Row index e / n for 0 <= e < 2^16 without integer division: (e + 0.5)/n is
@@ -63,6 +63,8 @@ __device__ __forceinline__ int row_of(int e, float inv_n) { return (int)(((float
 template <class T>
 hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E, const double* B, const V3Params& P,
                          MaxRef finf, const MaxSink& sink, hipStream_t st);
+// Threads per block of the general kernels whose threads own pencils.
+int pencil_threads(const int* pens, int n, size_t lds, int cap, long long cells, bool wide);
 size_t v3_shared_bytes(int nvx, int nvy, int nvz, size_t elem);
 // V(tau) by the backsubstitution split: three affine sweeps with per-face
 // feet (every velocity axis <= 32).
