@@ -135,15 +135,6 @@ __device__ __forceinline__ void pencil_sums(const T* __restrict__ src, unsigned 
     }
 }
 
-// Runs VL_LEN(N) for the run-time length n in 2..32.
-#define VL_LENGTHS(n)                                                                                        \
-    switch (n) {                                                                                             \
-        VL_LEN(2) VL_LEN(3) VL_LEN(4) VL_LEN(5) VL_LEN(6) VL_LEN(7) VL_LEN(8) VL_LEN(9) VL_LEN(10)           \
-        VL_LEN(11) VL_LEN(12) VL_LEN(13) VL_LEN(14) VL_LEN(15) VL_LEN(16) VL_LEN(17) VL_LEN(18) VL_LEN(19)   \
-        VL_LEN(20) VL_LEN(21) VL_LEN(22) VL_LEN(23) VL_LEN(24) VL_LEN(25) VL_LEN(26) VL_LEN(27) VL_LEN(28)   \
-        VL_LEN(29) VL_LEN(30) VL_LEN(31) VL_LEN(32)                                                          \
-    }
-
 template <class T, int NW>
 __global__ void __launch_bounds__(256)
 moments3_kernel(const T* __restrict__ f, double* __restrict__ mom, long long cells, VGrid G, XTable X) {

@@ -111,6 +111,15 @@ __device__ __forceinline__ void block_sum_rs(const double (&a)[K], double* red, 
     __syncthreads();
 }
 
+// Runs VL_LEN(N) for the run-time length n in 2..32.
+#define VL_LENGTHS(n)                                                                                        \
+    switch (n) {                                                                                             \
+        VL_LEN(2) VL_LEN(3) VL_LEN(4) VL_LEN(5) VL_LEN(6) VL_LEN(7) VL_LEN(8) VL_LEN(9) VL_LEN(10)           \
+        VL_LEN(11) VL_LEN(12) VL_LEN(13) VL_LEN(14) VL_LEN(15) VL_LEN(16) VL_LEN(17) VL_LEN(18) VL_LEN(19)   \
+        VL_LEN(20) VL_LEN(21) VL_LEN(22) VL_LEN(23) VL_LEN(24) VL_LEN(25) VL_LEN(26) VL_LEN(27) VL_LEN(28)   \
+        VL_LEN(29) VL_LEN(30) VL_LEN(31) VL_LEN(32)                                                          \
+    }
+
 // Streaming access to f: non-temporal (the lines are not kept in the caches)
 // when NT, else an ordinary access.  Velocity blocks whose rows are not whole
 // 128-byte lines (12^3 FP32: 576 B) have lines shared by two wave accesses;

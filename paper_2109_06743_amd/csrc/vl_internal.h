@@ -84,7 +84,7 @@ template <class T>
 hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy, int nvz, double vx_lo, double dvx,
                          double tau_dx, double vy_lo, double dvy, double tau_dy, int per, MaxRef finf,
                          const MaxSink& sink, hipStream_t st);
-constexpr long long kMaxArrayBlocks = 4096;
+constexpr long long kMaxArrayBlocks = 2048;
 // Reductions of up to kFoldOne per-block partials (maxima, clip counts) run in
 // one launch of one block, longer ones in two:
 // fin_split(n).blocks <= kFinStage blocks fold ranges of fin_split(n).chunk

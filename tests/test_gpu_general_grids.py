@@ -57,6 +57,34 @@ def test_v_operator(nv, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("nv", GRIDS + [(8, 8, 8), (12, 12, 12), (16, 16, 16)])
+def test_v_backsub(nv, dtype):
+    """The backsubstitution split with feet within a cell of their faces, on
+    either side, in the first cell and several cells away in the others (both
+    forms in one wave).  FP32: three sweeps, each foot (up to 32 cells) to one
+    rounding, slopes of f up to its size per cell."""
+    from paper_2109_06743_amd import vl
+    cfg, f, rng = _problem(nv, dtype)
+    cfg = dict(cfg, vsplit="backsub")
+    s, sp = 0, cfg["species"][0]
+    v, dv = OS._grids(cfg, sp)
+    tau = 0.01
+    unit = abs(sp["m"] / sp["q"]) * max(dv) / tau
+    E = rng.uniform(-1, 1, size=(2, 3, 3)) * unit * np.linspace(0.3, 4.0, 6).reshape(2, 3, 1)
+    B = rng.uniform(-1, 1, size=(2, 3, 3)) * np.linspace(0.2, 4.0, 6).reshape(2, 3, 1)
+    ctx = vl.Context(cfg, dtype)
+    fd = dev(f, dtype)
+    out = fd.clone()
+    ctx.pfc_advect_v(s, fd, out, dev(E, "f64"), dev(B, "f64"), tau)
+    ctx.sync()
+    ref = OV.v_advect_3v_backsub(f, E, B, sp["q"], sp["m"], v, dv, tau)
+    got = host(out, f.shape)
+    assert rel_l2(got, ref) < (3 * 32 * 2.0 ** -24 if dtype == "f32" else 1e-13)
+    assert (got >= 0).all()
+    np.testing.assert_allclose(got.sum((2, 3, 4)), f.sum((2, 3, 4)), rtol=1e-6 if dtype == "f32" else 1e-13)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("nx,ny,nv", [(3, 2, nv) for nv in GRIDS] + [(64, 64, (4, 5, 27)), (63, 65, (3, 12, 11))])
 def test_moments_and_fit(nx, ny, nv, dtype):
     """Moments per group and the fit against the oracle on a sample of cells."""
