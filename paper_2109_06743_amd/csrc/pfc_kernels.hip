@@ -1540,7 +1540,8 @@ template <class T> constexpr int xy_cols_big() { return sizeof(T) == 4 ? 16 : 8;
 // S + 2 Kmax + 4 rows for S outputs.  Beyond the one-round case in
 // xy_segment, the model cost rounds(S) * (S + 4 + 2 Kmax), with rounds the
 // number of times the waves of the launch refill the GPU, picks the segment
-// count (at most 64, segments of at least 8 rows).
+// count (at most 64, segments of at least 8 rows; of at least 4 where the waves
+// then still have a SIMD each).
 static int xy_cus() {
     static int cus = 0;
     if (cus <= 0) {
@@ -1564,9 +1565,9 @@ static int xy_segment(int ny, long long waves_per_seg, int kb, int waves_per_cu)
     double best = 0.0;
     for (int n = 1; n <= kXyMaxSeg && n <= ny; ++n) {
         const int S = (ny + n - 1) / n;
-        if (n > 1 && S < 8) break;
         if ((ny + S - 1) / S != n) continue;      // the same split as a smaller n
         const long long w = waves_per_seg * n;
+        if (n > 1 && S < (w <= 4 * xy_cus() ? 4 : 8)) break;
         const double cost = (double)((w + resident - 1) / resident) * (double)(S + 4 + 2 * kb);
         if (n == 1 || cost < best * 0.999) {
             best = cost;
@@ -1616,7 +1617,7 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     const double kd = floor(vymax * tau_dy) + 1.0;
     const int L = per ? ny : 2 * ny;
     const int kb = kd >= (double)L ? L - 1 : (int)kd;
-    A.S = xy_segment(ny, xy_waves_per_seg(nx, A.Nv, C), kb, sizeof(T) == 4 ? 12 : 8);
+    A.S = xy_segment(ny, xy_waves_per_seg(nx, A.Nv, C), kb, sizeof(T) == 4 ? (C <= 4 ? 16 : 12) : 8);
     A.nseg = (ny + A.S - 1) / A.S;
     const long long waves = xy_waves_per_seg(nx, A.Nv, C) * A.nseg;
     const long long blocks = (waves + 3) / 4;
@@ -1629,10 +1630,12 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     // velocity blocks thrash the caches and the address translation less.
     // Measured per launch (FP32): 34^3 blocks (157 KB per cell) one workgroup
     // per CU, 12.9 -> 11.0 ms on 512x256; blocks of at most 8 KB (12^3) two,
-    // 1.70 -> 1.57 ms on 1024x512; 16^3 unchanged with the register limit's
-    // three (two: +1 %, one: +33 %).
+    // 1.70 -> 1.57 ms on 1024x512 and 0.42 -> 0.41 on 512x256 (906 MB), but only
+    // where f is far beyond the caches: 8^3 on 512x256 (268 MB) 112 us without,
+    // 124 with, and 256x128 (67 MB) 35 and 41; 16^3 unchanged with the register
+    // limit's three (two: +1 %, one: +33 %).
     const size_t cellb = (size_t)A.Nv * sizeof(T);
-    const size_t shm = cellb >= 65536 ? 102400 : (cellb <= 8192 ? 61440 : 0);
+    const size_t shm = cellb >= 65536 ? 102400 : (cellb <= 8192 && rowbytes * ny >= ((size_t)512 << 20) ? 61440 : 0);
     if (wide)
         hipLaunchKernelGGL((finf.n > 1 ? pfc_xy_kernel<T, C, true, true> : pfc_xy_kernel<T, C, true, false>), dim3((unsigned)blocks), dim3(256), shm, st, fin, fout, A,
                            finf, mo);
@@ -1648,12 +1651,25 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
 // workgroup per CU there anyway): 11.0 -> 10.2 ms per 512x256x34^3 FP32
 // launch (FP64 34^3: 8 against 4 columns, 5.28 -> 4.68 ms per 256x128x34^3
 // launch).  At 12^3 and 16^3 the wider FP32 strip is 3-18 % slower, and 4,
-// 6, 10 or 12 columns are slower than 8 at 12^3.
+// 6, 10 or 12 columns are slower than 8 at 12^3 on large grids.  Small grids
+// take 4: a wave's walk is a chain of rows whose length in time grows with the
+// strip, and 8 columns leave SIMDs without a wave.  The line is a launch of
+// kXyNarrow waves per CU at 4 columns and 8 rows.  Below it, per launch in a
+// step: FP32 32x16x8^3 14.4 -> 8.5 us (with the shorter segments); per step: FP32
+// 20x11x16^3 168 -> 139 us, 80x50x8^3 178 -> 168, FP64 32x16x12^3 192 -> 164; per
+// call with the maximum of f: FP64 45x22x16^3 40 -> 31, 64x32x16^3 53 -> 47.
+// Beyond it 8 columns win at 16^3 (FP64 128x64 154 against 162, FP32 256x128 315
+// against 330).
+constexpr int kXyNarrow = 16;
 template <class T>
 hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy, int nvz, double vx_lo, double dvx,
                          double tau_dx, double vy_lo, double dvy, double tau_dy, int per, MaxRef finf,
                          const MaxSink& sink, hipStream_t st) {
-    const size_t cellb = (size_t)nvx * nvy * nvz * sizeof(T);
+    const long long Nv = (long long)nvx * nvy * nvz;
+    const size_t cellb = (size_t)Nv * sizeof(T);
+    if (cellb < 65536 && xy_waves_per_seg(nx, Nv, 4) * ((ny + 7) / 8) <= (long long)kXyNarrow * xy_cus())
+        return launch_pfc_xy_cols<T, 4>(fin, fout, nx, ny, nvx, nvy, nvz, vx_lo, dvx, tau_dx, vy_lo, dvy, tau_dy, per,
+                                        finf, sink, st);
     if (cellb >= 65536)
         return launch_pfc_xy_cols<T, xy_cols_big<T>()>(fin, fout, nx, ny, nvx, nvy, nvz, vx_lo, dvx, tau_dx, vy_lo, dvy, tau_dy,
                                              per, finf, sink, st);
