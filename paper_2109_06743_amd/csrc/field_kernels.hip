@@ -172,7 +172,10 @@ __global__ void cell_fields_kernel(YeeView F, double* __restrict__ E, double* __
 // two rows and columns beyond, B and the current one or two), so that the three
 // updates run there.  As separate kernels a step's two half steps, averages and
 // extrapolation are nine launches, of about 3 us each on a small grid, and at
-// 1024 x 512 move every component four times (123 us; this 84).  Expressions
+// 1024 x 512 move every component four times (123 us; this 72).  Latency of the
+// loads bounds it: 512 threads hold one point of each region, so all twelve loads
+// of a thread are in flight at once (256 threads looping over the regions: 42 us
+// at 1024 x 512, 11.4 at 256 x 128, 10 at 32 x 16; now 36, 6.7, 5.4).  Expressions
 // and roundings are those of the kernels above: the velocity sweeps round the
 // fields to FP32 coefficients, so a last-bit change here is not one there.
 // Rows q of the tile are virtual: periodic y wraps them; between walls the
@@ -180,7 +183,7 @@ __global__ void cell_fields_kernel(YeeView F, double* __restrict__ E, double* __
 // With periodic y rows 0 and ny of the [ny+1] arrays are the same points but
 // two copies, each advanced by itself: the integer rows beyond the seam take
 // the copy on their own side (row ny below row 0, row 0 above row ny - 1).
-constexpr int kFCols = 32, kFRows = 8;
+constexpr int kFCols = 32, kFRows = 8, kHalfThreads = 512;
 constexpr int kEC = kFCols + 4, kER = kFRows + 4;      // E: columns i0-2 .. i0+33, rows r0-2 .. r0+9
 constexpr int kBC = kFCols + 3, kBR = kFRows + 3;      // B: columns i0-2 .. i0+32, rows r0-1 .. r0+9
 constexpr int kJC = kFCols + 3, kJR = kFRows + 3;      // current: columns i0-1 .. i0+33, rows r0-2 .. r0+8
@@ -193,7 +196,7 @@ struct HalfArgs {
     double *E0, *B0, *E1, *B1, *E2, *B2;
 };
 
-__global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
+__global__ void __launch_bounds__(kHalfThreads) yee_half_kernel(HalfArgs A) {
     __shared__ double ex[kER][kEC], ey[kER][kEC], ez[kER][kEC];
     __shared__ double bx[kBR][kBC], by[kBR][kBC], bz[kBR][kBC];
     __shared__ double jx[kJR][kJC], jy[kJR][kJC], jz[kJR][kJC];
@@ -210,85 +213,118 @@ __global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
         while (q > n) q -= ny;
         return q;
     };
-    // E: rows of Ex, Ez outside [0, ny) by the boundary; rows no valid point needs are 0
-    for (int e = tid; e < kER * kEC; e += 256) {
-        const int r = e / kEC, c = e % kEC;
-        const int i = col(i0 - 2 + c);
-        int q = r0 - 2 + r, h = q;
-        double sgn = 1.0;
-        bool ok = true, okh = q >= 0 && q <= ny;
+    // every load of a thread (one point of each region) in flight together: E's
+    // rows of Ex, Ez outside [0, ny) by the boundary; rows no valid point needs are 0
+    static_assert(kER * kEC <= kHalfThreads && kBR * kBC <= kHalfThreads && kJR * kJC <= kHalfThreads &&
+                  2 * kEC <= kHalfThreads, "one point of each region per thread");
+    const int re_ = min(tid / kEC, kER - 1), ce_ = tid % kEC;
+    double sgn = 1.0;
+    bool ok = true, okh = true;
+    size_t at, ath;
+    {
+        const int i = col(i0 - 2 + ce_);
+        int q = r0 - 2 + re_, h = q;
         if (per) {
             q = wrap(q, ny - 1);
             h = wrap(h, ny);
-            okh = true;
-        } else if (q < 0) {
-            ok = q == -1;
-            q = 0;
-            sgn = -1.0;
-        } else if (q >= ny) {
-            ok = q == ny;
-            q = ny - 1;
-            sgn = -1.0;
-        }
-        const size_t at = (size_t)q * nx + i;
-        ex[r][c] = ok ? sgn * A.F.Ex[at] : 0.0;
-        ez[r][c] = ok ? sgn * A.F.Ez[at] : 0.0;
-        ey[r][c] = okh ? A.F.Ey[(size_t)h * nx + i] : 0.0;
-    }
-    for (int e = tid; e < kBR * kBC; e += 256) {
-        const int r = e / kBC, c = e % kBC;
-        const int i = col(i0 - 2 + c);
-        int q = r0 - 1 + r, h = q;
-        bool ok = q >= 0 && q < ny, okh = q >= 0 && q <= ny;
-        if (per) {
-            q = wrap(q, ny - 1);
-            h = wrap(h, ny);
-            ok = okh = true;
-        }
-        bx[r][c] = okh ? A.F.Bx[(size_t)h * nx + i] : 0.0;
-        bz[r][c] = okh ? A.F.Bz[(size_t)h * nx + i] : 0.0;
-        by[r][c] = ok ? A.F.By[(size_t)q * nx + i] : 0.0;
-    }
-    for (int e = tid; e < kJR * kJC; e += 256) {
-        const int r = e / kJC, c = e % kJC;
-        int q = r0 - 2 + r;
-        bool ok = q >= 0 && q < ny;
-        if (per) {
-            q = wrap(q, ny - 1);
-            ok = true;
-        }
-        double v[3] = {0.0, 0.0, 0.0};
-        if (ok) {
-            const size_t cell = (size_t)q * nx + col(i0 - 1 + c);
-            for (int k = 0; k < A.J.ns; ++k) {
-                const double* m = A.J.mom[k] + cell * A.J.stride + 1;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) v[d] = fma(A.J.q[k], m[d], v[d]);
+        } else {
+            okh = q >= 0 && q <= ny;
+            h = min(max(h, 0), ny);
+            if (q < 0) {
+                ok = q == -1;
+                q = 0;
+                sgn = -1.0;
+            } else if (q >= ny) {
+                ok = q == ny;
+                q = ny - 1;
+                sgn = -1.0;
             }
         }
-        jx[r][c] = v[0];
-        jy[r][c] = v[1];
-        jz[r][c] = v[2];
+        at = (size_t)q * nx + i;
+        ath = (size_t)h * nx + i;
+    }
+    const double vex = A.F.Ex[at], vez = A.F.Ez[at], vey = A.F.Ey[ath];
+    const int rb_ = min(tid / kBC, kBR - 1), cb_ = tid % kBC;
+    bool bok = true, bokh = true;
+    {
+        const int i = col(i0 - 2 + cb_);
+        int q = r0 - 1 + rb_, h = q;
+        if (per) {
+            q = wrap(q, ny - 1);
+            h = wrap(h, ny);
+        } else {
+            bok = q >= 0 && q < ny;
+            bokh = q >= 0 && q <= ny;
+            h = min(max(h, 0), ny);
+            q = min(max(q, 0), ny - 1);
+        }
+        at = (size_t)q * nx + i;
+        ath = (size_t)h * nx + i;
+    }
+    const double vbx = A.F.Bx[ath], vbz = A.F.Bz[ath], vby = A.F.By[at];
+    const int rj_ = min(tid / kJC, kJR - 1), cj_ = tid % kJC;
+    bool jok = true;
+    double m0[3] = {0.0, 0.0, 0.0}, m1[3] = {0.0, 0.0, 0.0};
+    {
+        int q = r0 - 2 + rj_;
+        if (per) {
+            q = wrap(q, ny - 1);
+        } else {
+            jok = q >= 0 && q < ny;
+            q = min(max(q, 0), ny - 1);
+        }
+        const size_t cell = (size_t)q * nx + col(i0 - 1 + cj_);
+        if (A.J.ns > 0) {
+            const double* m = A.J.mom[0] + cell * A.J.stride + 1;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) m0[d] = m[d];
+        }
+        if (A.J.ns > 1) {
+            const double* m = A.J.mom[1] + cell * A.J.stride + 1;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) m1[d] = m[d];
+        }
     }
     // the seam in this tile: row 0 at virtual row 0, and row ny
     const bool seam[2] = {per && r0 == 0, per && r0 + kFRows + 1 >= ny};
-    if (per) {
-        for (int e = tid; e < 2 * kEC; e += 256) {
-            const int s = e / kEC, c = e % kEC;
-            const size_t at = (s == 0 ? (size_t)ny * nx : 0) + col(i0 - 2 + c);
-            if (!seam[s]) continue;
-            eys[s][c] = A.F.Ey[at];
+    if (per && tid < 2 * kEC) {
+        const int s = tid / kEC, c = tid % kEC;
+        const size_t as = (s == 0 ? (size_t)ny * nx : 0) + col(i0 - 2 + c);
+        if (seam[s]) {
+            eys[s][c] = A.F.Ey[as];
             if (c < kBC) {
-                bxs[s][c] = A.F.Bx[at];
-                bzs[s][c] = A.F.Bz[at];
+                bxs[s][c] = A.F.Bx[as];
+                bzs[s][c] = A.F.Bz[as];
             }
         }
+    }
+    if (tid < kER * kEC) {
+        ex[re_][ce_] = ok ? sgn * vex : 0.0;
+        ez[re_][ce_] = ok ? sgn * vez : 0.0;
+        ey[re_][ce_] = okh ? vey : 0.0;
+    }
+    if (tid < kBR * kBC) {
+        bx[rb_][cb_] = bokh ? vbx : 0.0;
+        bz[rb_][cb_] = bokh ? vbz : 0.0;
+        by[rb_][cb_] = bok ? vby : 0.0;
+    }
+    if (tid < kJR * kJC) {
+        double v[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            v[d] = A.J.ns > 0 ? fma(A.J.q[0], m0[d], 0.0) : 0.0;
+            if (A.J.ns > 1) v[d] = fma(A.J.q[1], m1[d], v[d]);
+            if (!jok) v[d] = 0.0;
+        }
+        jx[rj_][cj_] = v[0];
+        jy[rj_][cj_] = v[1];
+        jz[rj_][cj_] = v[2];
     }
     __syncthreads();
     // this thread's point: column i0 + tc, row r0 + tr
     const int tc = tid % kFCols, tr = tid / kFCols;
     const int i = i0 + tc, q = r0 + tr;
-    const bool cell = i < nx && q < ny;
+    const bool point = tid < kFRows * kFCols && i < nx, cell = point && q < ny;
     // averages at the cell (E arrays start two rows and columns before the tile, B arrays one row and two columns)
     auto averages = [&](double (&e)[3], double (&b)[3]) {
         const int re = tr + 2, rb = tr + 1, c = tc + 2;
@@ -320,11 +356,10 @@ __global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
         bz[r][c] = fma(-A.hb, dEy - dEx, bz[r][c]);
         by[r][c] = by[r][c] + A.hb * (ez[r + 1][c + 1] - ez[r + 1][c]) / A.dx;
     };
-    for (int e = tid; e < kBR * kBC; e += 256) curl_e(e / kBC, e % kBC);
+    if (tid < kBR * kBC) curl_e(tid / kBC, tid % kBC);
     if (per) {
-        for (int e = tid; e < 2 * kBC; e += 256) {
-            const int s = e / kBC, c = e % kBC;
-            if (!seam[s]) continue;
+        const int s = tid / kBC, c = tid % kBC;
+        if (s < 2 && seam[s]) {
             const int re = (s == 0 ? 0 : ny) - (r0 - 2);
             const double dEz = (ez[re][c] - ez[re - 1][c]) / A.dy;
             const double dEy = (eys[s][c + 1] - eys[s][c]) / A.dx, dEx = (ex[re][c] - ex[re - 1][c]) / A.dy;
@@ -334,8 +369,8 @@ __global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
     }
     __syncthreads();
     // E += he (curl B - j) on rows r0-1 .. r0+8, columns i0-1 .. i0+32
-    for (int e = tid; e < (kFRows + 2) * (kFCols + 2); e += 256) {
-        const int r = e / (kFCols + 2) + 1, c = e % (kFCols + 2) + 1;     // in the E arrays
+    if (tid < (kFRows + 2) * (kFCols + 2)) {
+        const int r = tid / (kFCols + 2) + 1, c = tid % (kFCols + 2) + 1;     // in the E arrays
         const int rb = r - 1, rj = r, cj = c - 1;
         const int row = r0 - 2 + r;
         const bool below = per && row == -1, above = per && row == ny;
@@ -351,9 +386,9 @@ __global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
     }
     __syncthreads();
     if (!per) {        // ghost rows -1 and ny mirror rows 0 and ny - 1
-        for (int e = tid; e < 2 * (kFCols + 2); e += 256) {
-            const int c = e % (kFCols + 2) + 1;
-            const int g = (e < kFCols + 2 ? -1 : ny) - (r0 - 2), m = (e < kFCols + 2 ? 0 : ny - 1) - (r0 - 2);
+        if (tid < 2 * (kFCols + 2)) {
+            const int c = tid % (kFCols + 2) + 1;
+            const int g = (tid < kFCols + 2 ? -1 : ny) - (r0 - 2), m = (tid < kFCols + 2 ? 0 : ny - 1) - (r0 - 2);
             if (g >= 1 && g <= kFRows + 2 && m >= 1 && m <= kFRows + 2) {
                 ex[g][c] = -ex[m][c];
                 ez[g][c] = -ez[m][c];
@@ -362,9 +397,9 @@ __global__ void __launch_bounds__(256) yee_half_kernel(HalfArgs A) {
         __syncthreads();
     }
     // B -= hb curl E on rows r0 .. r0+8, columns i0-1 .. i0+31
-    for (int e = tid; e < (kFRows + 1) * (kFCols + 1); e += 256) curl_e(e / (kFCols + 1) + 1, e % (kFCols + 1) + 1);
+    if (tid < (kFRows + 1) * (kFCols + 1)) curl_e(tid / (kFCols + 1) + 1, tid % (kFCols + 1) + 1);
     __syncthreads();
-    if (i < nx && q <= ny) {
+    if (point && q <= ny) {
         const size_t at = (size_t)q * nx + i;
         const int re = tr + 2, rb = tr + 1, c = tc + 2;
         A.G.Ey[at] = ey[re][c];
@@ -449,7 +484,7 @@ hipError_t launch_yee_half(const double* from, double* to, int nx, int ny, const
     A.B1 = at_to.B;
     A.E2 = ahead.E;
     A.B2 = ahead.B;
-    hipLaunchKernelGGL(yee_half_kernel, dim3((nx + kFCols - 1) / kFCols, (ny + kFRows) / kFRows), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(yee_half_kernel, dim3((nx + kFCols - 1) / kFCols, (ny + kFRows) / kFRows), dim3(kHalfThreads), 0, st, A);
     return hipGetLastError();
 }
 
