@@ -358,10 +358,23 @@ struct FitCell {
 };
 static_assert(sizeof(FitCell) == kFitCellDoubles * sizeof(double), "FitCell layout");
 
+// blockIdx.y: species of the set (their outputs one after the other); a launch
+// of its own is 5 us on a grid of any size up to 32768 cells, bound by its chain
+// of divisions and square roots.
+struct FitSet {
+    const double* mom_pre[2];
+    double* U[2];
+    double m[2], kscale[2];
+};
+
 __global__ void __launch_bounds__(256)
-fit3_params_kernel(const double* __restrict__ mom_pre, double* __restrict__ U, long long cells, double m,
-                   double kscale, FitCell* __restrict__ out, unsigned long long* __restrict__ counters) {
+fit3_params_kernel(FitSet S, long long cells, FitCell* __restrict__ out, unsigned long long* __restrict__ counters) {
     __shared__ int nskip;
+    const int sp = blockIdx.y;
+    const double* __restrict__ mom_pre = S.mom_pre[sp];
+    double* __restrict__ U = S.U[sp];
+    const double m = S.m[sp], kscale = S.kscale[sp];
+    out += sp * cells;
     if (threadIdx.x == 0) nskip = 0;
     __syncthreads();
     const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1100,19 +1113,31 @@ hipError_t launch_fit_fold(int ns, const MaxSink* sinks, unsigned* const* clips,
 }
 
 template <class T>
-hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
-                       long long cells, const VGridArgs& a, const MaxSink& sink, unsigned* clip_part,
-                       double* scratch, hipStream_t st) {
+hipError_t launch_fit3_params(int ns, const double* const* mom_pre, double* const* U, const VGridArgs* a,
+                              long long cells, double* params, void* counters, hipStream_t st) {
+    if (ns < 1 || ns > 2) return hipErrorInvalidValue;
+    FitSet S{};
+    for (int k = 0; k < ns; ++k) {
+        S.mom_pre[k] = mom_pre[k];
+        S.U[k] = U[k];
+        S.m[k] = a[k].m;
+        S.kscale[k] = cube_edge(a[k]) ? ExpK<T>::scale : 1.0;
+    }
+    hipLaunchKernelGGL(fit3_params_kernel, dim3((unsigned)((cells + 255) / 256), ns), dim3(256), 0, st, S, cells,
+                       reinterpret_cast<FitCell*>(params), (unsigned long long*)counters);
+    return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_fit3(const T* fin, T* fout, double* mom_post, void* counters, long long cells, const VGridArgs& a,
+                       const MaxSink& sink, unsigned* clip_part, const double* params, hipStream_t st) {
     VGrid G{a.nv[0], a.nv[1], a.nv[2], {a.lo[0], a.lo[1], a.lo[2]}, {a.dv[0], a.dv[1], a.dv[2]}, a.m, 1.0f / (float)a.nv[2]};
-    auto* cnt = (unsigned long long*)counters;
     auto* mo = sink.target<T>(cells);
-    unsigned* cp = cnt ? clip_part : nullptr;
+    unsigned* cp = counters ? clip_part : nullptr;
     const int N = cube_edge(a);
     const XTable X = xtable(a);
     const dim3 grid((unsigned)cells);
-    FitCell* P = reinterpret_cast<FitCell*>(scratch);
-    hipLaunchKernelGGL(fit3_params_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, mom_pre, U, cells,
-                       a.m, N ? ExpK<T>::scale : 1.0, P, cnt);
+    const FitCell* P = reinterpret_cast<const FitCell*>(params);
     if (N) {
         // waves per cell and pencils per thread: every lane busy for 16^3, 3/4 for 12^3
         if constexpr (sizeof(T) == 4) {
@@ -1156,8 +1181,10 @@ hipError_t launch_fit1(const T* fin, T* fout, const double* mom_pre, const doubl
     template hipError_t launch_moments3<T>(const T*, double*, long long, const VGridArgs&, hipStream_t);         \
     template hipError_t launch_moments1<T>(const T*, double*, long long, int, double, double, double,            \
                                            hipStream_t);                                                        \
-    template hipError_t launch_fit3<T>(const T*, T*, const double*, double*, double*, void*, long long,         \
-                                       const VGridArgs&, const MaxSink&, unsigned*, double*, hipStream_t);      \
+    template hipError_t launch_fit3_params<T>(int, const double* const*, double* const*, const VGridArgs*,    \
+                                              long long, double*, void*, hipStream_t);                         \
+    template hipError_t launch_fit3<T>(const T*, T*, double*, void*, long long, const VGridArgs&, const MaxSink&, \
+                                       unsigned*, const double*, hipStream_t);      \
     template hipError_t launch_fit_fold<T>(int, const MaxSink*, unsigned* const*, void*, long long,             \
                                            hipStream_t);                                                       \
     template hipError_t launch_fit1<T>(const T*, T*, const double*, const double*, double*, double*, void*,     \

@@ -267,6 +267,26 @@ vl_status moments_typed(vl_ctx* ctx, int s, const T* f, double* mom, hipStream_t
     return VL_OK;
 }
 
+double* fit_scratch_of(const vl_ctx* c, int s) { return c->fit_scratch + (size_t)s * c->cells * vl::kFitCellDoubles; }
+
+// Per-cell parameters of the 3V fits of species [s0, s0 + ns), ahead of them.
+template <class T>
+vl_status fit_params(vl_ctx* ctx, int s0, int ns, const double* const* mom_pre, double* const* U, int64_t* counters,
+                     hipStream_t st) {
+    const vl_config& c = ctx->cfg;
+    if (c.dim_v == 1) return VL_OK;
+    Timed tm(ctx, VL_T_FIT, st);
+    if (!ctx->fit_scratch) {
+        void* p = nullptr;
+        VL_HIP(hipMalloc(&p, sizeof(double) * vl::kFitCellDoubles * (size_t)ctx->cells * c.nspecies));
+        ctx->fit_scratch = (double*)p;
+    }
+    const vl::VGridArgs a[2] = {grid_args(c.sp[s0]), grid_args(c.sp[s0 + ns - 1])};
+    VL_HIP((vl::launch_fit3_params<T>(ns, mom_pre, U, a, ctx->cells, fit_scratch_of(ctx, s0), counters, st)));
+    return VL_OK;
+}
+
+// 3V: after fit_params; the caller folds the partials (fit_fold) after its last fit.
 template <class T>
 vl_status fit_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post,
                     int64_t* counters, const vl::MaxSink& sink, hipStream_t st) {
@@ -276,16 +296,9 @@ vl_status fit_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* mom
     if (c.dim_v == 1)
         VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, U, mom_post, counters, ctx->cells, sp.nv[0], sp.v_lo[0],
                                    dv_of(sp, 0), sp.m, sink, st)));
-    else {
-        if (!ctx->fit_scratch) {
-            void* p = nullptr;
-            VL_HIP(hipMalloc(&p, sizeof(double) * vl::kFitCellDoubles * (size_t)ctx->cells));
-            ctx->fit_scratch = (double*)p;
-        }
-        // the caller folds the partials (fit_fold) after its last fit
-        VL_HIP((vl::launch_fit3<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, grid_args(sp), sink,
-                                   ctx->bclip[s], ctx->fit_scratch, st)));
-    }
+    else
+        VL_HIP((vl::launch_fit3<T>(fin, fout, mom_post, counters, ctx->cells, grid_args(sp), sink, ctx->bclip[s],
+                                   fit_scratch_of(ctx, s), st)));
     return VL_OK;
 }
 
@@ -508,6 +521,7 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
                 VL_HIP(vl::launch_fluid_rk3_3v_set(ns, S->U, mt, mt1, E_t, B_t, E_1, B_1, E_h, B_h, dt, c.nx, c.ny, q,
                                                    ms, dx_of(c), dy_of(c), fwork, st, per_y(c)));
             }
+            if ((r = fit_params<T>(ctx, 0, ns, S->mom_pre, S->U, S->counters, st)) != VL_OK) return r;
             for (int s = 0; s < ns; ++s)
                 if ((r = fit_typed<T>(ctx, s, (T*)S->f[s], (T*)S->f[s], S->mom_pre[s], S->U[s], S->mom_post[s],
                                       S->counters, max_to(ctx, 0, s), st)) != VL_OK)
@@ -611,8 +625,9 @@ vl_status fit_noalloc_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const dou
     }
     double* params = (double*)sp;
     unsigned* clip = (unsigned*)((char*)sp + kNoAllocParamBytes);
-    VL_HIP((vl::launch_fit3<T>(fin, fout, mom_pre, U, mom_post, counters, ctx->cells, grid_args(sc), kNoMax, clip,
-                               params, st)));
+    const vl::VGridArgs a = grid_args(sc);
+    VL_HIP((vl::launch_fit3_params<T>(1, &mom_pre, &U, &a, ctx->cells, params, counters, st)));
+    VL_HIP((vl::launch_fit3<T>(fin, fout, mom_post, counters, ctx->cells, a, kNoMax, clip, params, st)));
     VL_HIP((vl::launch_fit_fold<T>(1, &kNoMax, &clip, counters, ctx->cells, st)));
     return VL_OK;
 }
@@ -784,6 +799,9 @@ vl_status vl_moment_fit(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out, c
     if (!f_in || !f_out || !mom_pre || !U) return fail(ctx, VL_EINVAL, "null argument");
     if ((r = ensure_device(ctx)) != VL_OK) return r;
     hipStream_t st = (hipStream_t)stream;
+    r = DISPATCH(ctx, fit_params<float>(ctx, s, 1, &mom_pre, &U, counters, st),
+                 fit_params<double>(ctx, s, 1, &mom_pre, &U, counters, st));
+    if (r != VL_OK) return r;
     r = DISPATCH(ctx,
                  fit_typed<float>(ctx, s, (const float*)f_in, (float*)f_out, mom_pre, U, mom_post, counters, kNoMax,
                                   st),

@@ -114,16 +114,19 @@ hipError_t launch_moments3(const T* f, double* mom, long long cells, const VGrid
 template <class T>
 hipError_t launch_moments1(const T* f, double* mom, long long cells, int nv, double vlo, double dv, double m,
                            hipStream_t st);
-// Per-cell fitting parameters (cubic velocity blocks): kFitCellDoubles doubles
-// per spatial cell of device scratch.
 // Edge of the large cubic velocity grid with fixed-size kernels (FP32 only:
 // 34 x 34 x 35 floats = 161840 bytes of LDS per cell in the V operator).
 constexpr int kBigCube = 34;
+// Per-cell parameters of the fits, kFitCellDoubles doubles per spatial cell of
+// device scratch: launch_fit3_params fills those of ns species (one after the
+// other) and rescales U in place, then launch_fit3 runs per species.
 constexpr int kFitCellDoubles = 20;
 template <class T>
-hipError_t launch_fit3(const T* fin, T* fout, const double* mom_pre, double* U, double* mom_post, void* counters,
-                       long long cells, const VGridArgs& a, const MaxSink& sink, unsigned* clip_part,
-                       double* scratch, hipStream_t st);
+hipError_t launch_fit3_params(int ns, const double* const* mom_pre, double* const* U, const VGridArgs* a,
+                              long long cells, double* params, void* counters, hipStream_t st);
+template <class T>
+hipError_t launch_fit3(const T* fin, T* fout, double* mom_post, void* counters, long long cells, const VGridArgs& a,
+                       const MaxSink& sink, unsigned* clip_part, const double* params, hipStream_t st);
 // launch_fit3 leaves per-block maxima in the sink and per-cell clip counts in
 // clip_part; launch_fit_fold, after the fits of all ns species, folds them
 // into the sinks' slots and the counters.
