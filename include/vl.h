@@ -104,8 +104,9 @@ typedef struct {
 typedef struct vl_ctx vl_ctx;
 
 /* Create a context for one problem geometry.  Host-only: validates and copies
- * *cfg; device scratch (a few kilobytes, plus 160 bytes per spatial cell for
- * the 3V moment fitting on its first call) is allocated on first use on the
+ * *cfg; device scratch (64 KB, 12 bytes per species and block of the largest
+ * launch, 8 nx, plus 160 bytes per spatial cell and species for the 3V moment
+ * fitting on its first call) is allocated on first use on the
  * device current at that time and freed by vl_destroy.  Errors: VL_EINVAL (bad geometry, velocity
  * grid not symmetric in v_y for 2X3V), VL_ENOTSUP (unsupported combination, or a row of f --
  * nx velocity blocks -- of 4 GiB or more). */
