@@ -1553,6 +1553,7 @@ static int xy_cus() {
     return cus;
 }
 constexpr int kXyMaxSeg = 64;
+constexpr size_t kXyCached = (size_t)512 << 20;      // bytes of f
 static int xy_segment(int ny, long long waves_per_seg, int kb, int waves_per_cu) {
     const long long resident = (long long)waves_per_cu * xy_cus();
     // segments of 128 rows that fill at least half the GPU in one round: one
@@ -1579,6 +1580,30 @@ static int xy_segment(int ny, long long waves_per_seg, int kb, int waves_per_cu)
 
 static long long xy_waves_per_seg(int nx, long long Nv, int cols) {
     return ((Nv + kWave - 1) / kWave) * ((nx + cols - 1) / cols);
+}
+
+// Bound of the whole-cell y shift (one more than the FP64 estimate: the
+// kernel splits the shift in the storage type).
+static int xy_ky_bound(int ny, int nvy, double vy_lo, double dvy, double tau_dy, int per) {
+    const double vymax = fmax(fabs(vy_lo), fabs(vy_lo + nvy * dvy));
+    const double kd = floor(vymax * tau_dy) + 1.0;
+    const int L = per ? ny : 2 * ny;
+    return kd >= (double)L ? L - 1 : (int)kd;
+}
+
+template <class T>
+static int xy_waves_per_cu(int cols) {
+    return sizeof(T) == 4 ? (cols <= 4 ? 16 : 12) : 8;
+}
+
+// Mean over largest number of waves a SIMD gets from the launch with `cols`
+// columns.
+template <class T>
+static double xy_even(int nx, int ny, long long Nv, int kb, int cols) {
+    const long long w1 = xy_waves_per_seg(nx, Nv, cols), simds = 4LL * xy_cus();
+    const int S = xy_segment(ny, w1, kb, xy_waves_per_cu<T>(cols));
+    const long long w = w1 * ((ny + S - 1) / S);
+    return (double)w / (double)((w + simds - 1) / simds * simds);
 }
 
 // Upper bound of the launch's blocks over every segment length it can pick
@@ -1611,13 +1636,8 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     A.tau_dy = tau_dy;
     A.nchunks = (A.Nv + kWave - 1) / kWave;
     A.nst = (nx + C - 1) / C;
-    // bound of the whole-cell y shift (one more than the FP64 estimate: the
-    // kernel splits the shift in the storage type)
-    const double vymax = fmax(fabs(vy_lo), fabs(vy_lo + nvy * dvy));
-    const double kd = floor(vymax * tau_dy) + 1.0;
-    const int L = per ? ny : 2 * ny;
-    const int kb = kd >= (double)L ? L - 1 : (int)kd;
-    A.S = xy_segment(ny, xy_waves_per_seg(nx, A.Nv, C), kb, sizeof(T) == 4 ? (C <= 4 ? 16 : 12) : 8);
+    const int kb = xy_ky_bound(ny, nvy, vy_lo, dvy, tau_dy, per);
+    A.S = xy_segment(ny, xy_waves_per_seg(nx, A.Nv, C), kb, xy_waves_per_cu<T>(C));
     A.nseg = (ny + A.S - 1) / A.S;
     const long long waves = xy_waves_per_seg(nx, A.Nv, C) * A.nseg;
     const long long blocks = (waves + 3) / 4;
@@ -1635,7 +1655,7 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     // 124 with, and 256x128 (67 MB) 35 and 41; 16^3 unchanged with the register
     // limit's three (two: +1 %, one: +33 %).
     const size_t cellb = (size_t)A.Nv * sizeof(T);
-    const size_t shm = cellb >= 65536 ? 102400 : (cellb <= 8192 && rowbytes * ny >= ((size_t)512 << 20) ? 61440 : 0);
+    const size_t shm = cellb >= 65536 ? 102400 : (cellb <= 8192 && rowbytes * ny >= kXyCached ? 61440 : 0);
     if (wide)
         hipLaunchKernelGGL((finf.n > 1 ? pfc_xy_kernel<T, C, true, true> : pfc_xy_kernel<T, C, true, false>), dim3((unsigned)blocks), dim3(256), shm, st, fin, fout, A,
                            finf, mo);
@@ -1659,7 +1679,14 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
 // 20x11x16^3 168 -> 139 us, 80x50x8^3 178 -> 168, FP64 32x16x12^3 192 -> 164; per
 // call with the maximum of f: FP64 45x22x16^3 40 -> 31, 64x32x16^3 53 -> 47.
 // Beyond it 8 columns win at 16^3 (FP64 128x64 154 against 162, FP32 256x128 315
-// against 330).
+// against 330), except where they deal the SIMDs uneven numbers of waves, which
+// all walk a segment of the same length: 4 columns then if they are more even by
+// a fifth.  Calls as above: FP32 100x50x20x16x24 (1560 waves of 8 columns on 1024
+// SIMDs, 3000 of 4) 95 -> 89, FP64 100x50x20x16x18 187 -> 154; per step: FP64
+// 100x50x20x16x18 1640 -> 1521, 180x90x16^3 2165 -> 2040, FP32 150x80x20x16x24
+// 1925 -> 1871, 100x50x20x16x24 844 -> 842.  More even by less than a tenth: FP32
+// 180x90x16^3 163 -> 167, FP64 150x80x20x16x18 354 -> 373 (calls).  Only below
+// kXyCached bytes of f: beyond, what the caches hold decides.
 constexpr int kXyNarrow = 16;
 template <class T>
 hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy, int nvz, double vx_lo, double dvx,
@@ -1667,7 +1694,11 @@ hipError_t launch_pfc_xy(const T* fin, T* fout, int nx, int ny, int nvx, int nvy
                          const MaxSink& sink, hipStream_t st) {
     const long long Nv = (long long)nvx * nvy * nvz;
     const size_t cellb = (size_t)Nv * sizeof(T);
-    if (cellb < 65536 && xy_waves_per_seg(nx, Nv, 4) * ((ny + 7) / 8) <= (long long)kXyNarrow * xy_cus())
+    const int kb = xy_ky_bound(ny, nvy, vy_lo, dvy, tau_dy, per);
+    if (cellb < 65536 &&
+        (xy_waves_per_seg(nx, Nv, 4) * ((ny + 7) / 8) <= (long long)kXyNarrow * xy_cus() ||
+         ((size_t)nx * ny * cellb < kXyCached &&
+          xy_even<T>(nx, ny, Nv, kb, 4) > 1.2 * xy_even<T>(nx, ny, Nv, kb, xy_cols<T>()))))
         return launch_pfc_xy_cols<T, 4>(fin, fout, nx, ny, nvx, nvy, nvz, vx_lo, dvx, tau_dx, vy_lo, dvy, tau_dy, per,
                                         finf, sink, st);
     if (cellb >= 65536)

@@ -20,7 +20,7 @@ def lib():
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("bc", ["reflect", "periodic"])
 @pytest.mark.parametrize("nx,ny,nv,cells", [(128, 128, 8, 0.7), (129, 128, 8, 0.7), (129, 121, 8, 2.6), (5, 3, 8, 0.9),
-                                            (9, 23, 8, 0.4), (33, 22, 6, 3.3), (4, 13, 12, 1.2)])
+                                            (9, 23, 8, 0.4), (33, 22, 6, 3.3), (4, 13, 12, 1.2), (310, 16, 12, 0.8)])
 def test_x_operator(nx, ny, nv, cells, bc, dtype):
     import torch
     from paper_2109_06743_amd import vl
