@@ -14,43 +14,60 @@
 // xzz, yyy, yyz, yzz, zzz).  1V: U = (n, nu, P), Qcal = raw moment 3.
 #include "vl_internal.h"
 
-// Fuse multiply-adds as the expressions are written, not as each instantiation
-// happens to be optimised: a network closure that falls back gives the kinetic
-// step bit for bit.
-#pragma clang fp contract(on)
+// Every rounding here is written out: multiply-adds are fused where fma() says
+// so and nowhere else, quotients are correctly rounded.  The fit rounds
+// functions of U to the type of f, where a last bit of U can become one of f's,
+// so U must not depend on how a kernel is split or optimised: a network closure
+// that falls back gives the kinetic step bit for bit, and the tests form the
+// same roundings on the host.
+#pragma clang fp contract(off)
 
 namespace vl {
 
 constexpr double kCwenoEps = 1e-6;
+
+// Quotients by one divisor, bit for bit those of `/` while no step leaves the
+// normal numbers (divisors up to 2^1021, numerators from 2^-968; zeros,
+// infinities and NaN as `/`): the hardware's estimate of 1/x, two Newton steps
+// and a correction of each quotient by its remainder.  What `/` does besides is
+// to scale its operands, and to form 1/x again for every numerator.
+struct Divisor {
+    double x, r;
+    __device__ __forceinline__ explicit Divisor(double v) : x(v) {
+        r = __builtin_amdgcn_rcp(x);
+        r = fma(fma(-x, r, 1.0), r, r);
+        r = fma(fma(-x, r, 1.0), r, r);
+    }
+    __device__ __forceinline__ double under(double a) const {
+        const double q = a * r;
+        return __builtin_amdgcn_div_fixup(fma(fma(-x, q, a), r, q), x, a);
+    }
+};
 
 // CWENO-3 point values of cell j at its left (x_j - h/2) and right (x_j + h/2)
 // faces from the averages a = u_{j-1}, b = u_j, c = u_{j+1}.  The left, right
 // and centred polynomials evaluated at +-h/2 are
 //   P_L = b -+ (b - a)/2,  P_R = b -+ (c - b)/2,  P_C = b + d2/6 -+ (c - a)/4,
 // d2 = c - 2b + a, weighted with (1/4, 1/2, 1/4) / (eps + IS)^2, normalised.
-// With e = eps + IS the weights are, times a common factor, tl = (ec er)^2,
-// 2 tc = 2 (el er)^2 and tr = (el ec)^2, their sum S = tl + 2 tc + tr (one
-// reciprocal); since they sum to one the point values are b plus the weighted
-// corrections (a constant state reconstructs to itself exactly):
-//   b + h (2/3 tc d2 +- (tl dl + tc dc + tr dr)),  h = 1 / (2 S).
-// 31 operations and the hardware's estimate of 1/S, refined once to third
-// order; the reconstructions are two thirds of the stage kernel's arithmetic.
+// With D = (eps + IS)^2 the normalised weights are
+//   w_L = Dc Dr / S, w_C = 2 Dl Dr / S, w_R = Dl Dc / S,
+//   S = Dc Dr + 2 Dl Dr + Dl Dc
+// (one division), and since they sum to one the point values are b plus the
+// weighted corrections (a constant state reconstructs to itself exactly), here
+// b + 1/2 (w_C d2/3 +- (w_L (b-a) + w_R (c-b) + w_C (c-a)/2)).  39 operations;
+// the reconstructions are two thirds of the stage kernel's arithmetic.
 __device__ __forceinline__ void cweno(double a, double b, double c, double& left, double& right) {
-    const double dl = b - a, dr = c - b, d2 = dr - dl, dc = dr + dl;
+    const double dl = b - a, dr = c - b, d2 = fma(-2.0, b, c) + a, hc = 0.5 * (c - a);
     const double el = fma(dl, dl, kCwenoEps), er = fma(dr, dr, kCwenoEps);
-    const double ec = fma(13.0 / 3.0, d2 * d2, fma(0.25, dc * dc, kCwenoEps));
-    double tl = ec * er, tc = el * er, tr = el * ec;
-    tl *= tl;
-    tc *= tc;
-    tr *= tr;
-    const double sum = fma(2.0, tc, tl + tr);
-    const double r = __builtin_amdgcn_rcp(sum);
-    const double e = fma(-sum, r, 1.0);
-    const double h = 0.5 * fma(r, fma(e, e, e), r);
-    const double side = h * fma(tl, dl, fma(tc, dc, tr * dr));       // odd part
-    const double even = fma(h, ((2.0 / 3.0) * tc) * d2, b);          // even part
-    right = even + side;
-    left = even - side;
+    const double ec = fma(hc, hc, fma(d2, d2 * (13.0 / 3.0), kCwenoEps));
+    const double Dl = el * el, Dc = ec * ec, Dr = er * er, Dl2 = Dl + Dl;
+    const double tl = Dc * Dr, tc = Dl2 * Dr, tr = Dl * Dc;
+    const double inv = Divisor(fma(Dl, Dc, fma(Dl2, Dr, tl))).under(1.0);
+    const double wl = tl * inv, wc = tc * inv, wr = tr * inv;
+    const double side = fma(hc, wc, fma(dl, wl, dr * wr));           // twice the odd part
+    const double even = d2 * (1.0 / 3.0);                            // twice the even part: even wc
+    right = fma(0.5, fma(even, wc, side), b);
+    left = fma(0.5, fma(even, wc, -side), b);
 }
 
 // y-parity (+1/-1) of U and Qcal components under y -> -y
@@ -85,15 +102,17 @@ __device__ __forceinline__ double row_next(double v) {
 //    the previous lane's.
 // 3. y: the same for kRows + 2 rows, through shared memory (which no longer
 //    holds the cells).
-// 4. The second half adds both and the block writes rows of 140 doubles.
+// 4. The first half adds both and the second writes rows of 140 doubles.
 // The kernel is bound by its FP64 instructions (two thirds of them in cweno).
 // Two kernels per stage used to store the fluxes (160 B a cell) and read them
 // back from 80-byte records, reconstruct all 20 components per direction and,
 // with a closure, read and write a third moment (2 x 160 B) and an Eq. 5
 // source first: 125 + 63 + 25 + 22 us a stage at 1024 x 512, one species; this
-// takes 65 (Eq. 5), and 10.9 us instead of 6.6 + 4.1 on 32 x 16 cells (both
-// species).  One thread per cell of a 16 x 16 square for both directions took
-// 71 us there and 15.5 us on 32 x 16 cells (the length of its chain).
+// takes 71 (Eq. 5), and 11.4 us instead of 6.6 + 4.1 on 32 x 16 cells (both
+// species), with the same bits.  Estimated reciprocals in place of the quotients
+// and the two differences added to U one after the other took 65 and 10.9: the
+// bits of U changed, and with them, in one cell of a 1024 x 512 magnetotail step
+// in a few million, the FP32 distribution by 6e-8.
 enum { kThirdKinetic = 0, kThirdZero = 1, kThirdNet = 2 };
 constexpr int kRows = 16, kCols = 14;
 constexpr int kHaloR = kRows + 4, kHaloC = kCols + 4;
@@ -106,7 +125,7 @@ constexpr int kXStride = kXLanes + 1, kYStride = kYLanes + 1;    // of the excha
 static_assert(kXLanes <= kHalf && kYLanes <= kHalf && kHaloC * 10 <= kHalf, "one pass each");
 static_assert(17 * kYStride <= kStageComps * kHaloCells, "the y exchange fits the cells' memory");
 static_assert(kRows * kCols * 10 <= 10 * kYStride, "the results fit the y fluxes' memory");
-static_assert(10 * (kXStride + kYStride) <= kStageComps * kHaloCells, "fluxes and sums fit the cells' memory");
+static_assert(10 * (kXStride + kYStride) <= kStageComps * kHaloCells, "fluxes and differences fit the cells' memory");
 
 struct FluidArgs {
     int nx, ny;
@@ -119,28 +138,34 @@ struct FluidArgs {
     int tx, ty;           // tiles along x, y
 };
 
-// Third moment with heat flux q (Qcal of the zero-heat-flux state plus q):
-// u_a P_bc + u_b P_ac + u_c P_ab - 2 m n u_a u_b u_c, component k of nine.
-__device__ __forceinline__ void third_moment(const double (&U)[10], double m, double (&Q)[9]) {
-    const double in = 1.0 / U[0];
-    const double u[3] = {U[1] * in, U[2] * in, U[3] * in};
+// Third moment u_a P_bc + u_b P_ac + u_c P_ab - 2 m n u_a u_b u_c + heat[k], for
+// component k of nine (heat: the closure's heat flux, sc y in kNet's terms).
+template <class Heat>
+__device__ __forceinline__ void third_moment(const double (&U)[10], const double (&u)[3], double m, double (&Q)[9],
+                                             const Heat& heat) {
     const double mn2 = 2.0 * m * U[0];
     const double P[3][3] = {{U[4], U[5], U[6]}, {U[5], U[7], U[8]}, {U[6], U[8], U[9]}};
     const int ta[9] = {0, 0, 0, 0, 0, 0, 1, 1, 1}, tb[9] = {0, 0, 0, 1, 1, 2, 1, 1, 2}, tc[9] = {0, 1, 2, 1, 2, 2, 1, 2, 2};
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
         const int x = ta[k], y = tb[k], z = tc[k];
-        Q[k] = (u[x] * P[y][z] + u[y] * P[x][z] + u[z] * P[x][y]) - mn2 * u[x] * u[y] * u[z];
+        const double first = u[y] * P[x][z];
+        const double two = x == y ? first + first : fma(u[x], P[y][z], first);
+        const double three = heat(k, fma(u[z], P[x][y], two));
+        Q[k] = fma(-(mn2 * u[x] * u[y]), u[z], three);
     }
 }
 
 // Temperature tensor T = (P - m n u u) / n of a fluid record (PAIRS order).
-__device__ __forceinline__ void temperature6(const double (&V)[10], double m, double (&T)[6]) {
-    const double in = 1.0 / V[0];
-    const double u[3] = {V[1] * in, V[2] * in, V[3] * in};
+__device__ __forceinline__ void temperature6(const double (&V)[10], const double (&u)[3], const Divisor& n, double m,
+                                             double (&T)[6]) {
     const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 2};
+    const double mn = m * V[0];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) T[k] = V[4 + k] * in - m * u[pa[k]] * u[pb[k]];
+    for (int k = 0; k < 6; ++k) {
+        const double mnu = mn * u[pa[k]], ub = u[pb[k]];
+        T[k] = n.under(k == 1 || k == 4 ? V[4 + k] - mnu * ub : fma(-mnu, ub, V[4 + k]));
+    }
 }
 
 // Face fluxes of one direction: W components 0..9 are U, 10..15 the third
@@ -163,17 +188,18 @@ struct FluxMap {
 
 template <int D>
 __device__ __forceinline__ double wave_speed(const double (&W)[16], double m) {
-    const double in = 1.0 / W[0];
-    const double u = W[FluxMap<D>::nu] * in;
-    const double p = W[FluxMap<D>::pdd] - m * W[FluxMap<D>::nu] * u;
-    return fabs(u) + sqrt(fmax(3.0 * p * in / m, 0.0));
+    const double u = W[FluxMap<D>::nu] / W[0], mn = m * W[0];
+    const double p = fma(-u, mn * u, W[FluxMap<D>::pdd]);
+    return fabs(u) + sqrt(fmax(3.0 * p / mn, 0.0));
 }
 
-// Local Lax-Friedrichs flux k between the point values Wm (below) and Wp.
+// Local Lax-Friedrichs flux k between the point values Wm (below) and Wp; ha:
+// half the wave speed.
 template <int D>
-__device__ __forceinline__ double face_flux(const double (&Wm)[16], const double (&Wp)[16], int k, double a, double im) {
-    const double sum = Wp[FluxMap<D>::src(k)] + Wm[FluxMap<D>::src(k)];
-    return (k >= 1 && k < 4 ? 0.5 * im : 0.5) * sum - 0.5 * a * (Wp[k] - Wm[k]);
+__device__ __forceinline__ double face_flux(const double (&Wm)[16], const double (&Wp)[16], int k, double ha, double im) {
+    const double fm = Wm[FluxMap<D>::src(k)], fp = Wp[FluxMap<D>::src(k)];
+    const double sum = k >= 1 && k < 4 ? fma(im, fm, im * fp) : fp + fm;
+    return fma(0.5, sum, -(ha * (Wp[k] - Wm[k])));
 }
 
 template <int THIRD>
@@ -181,7 +207,7 @@ __global__ void __launch_bounds__(2 * kHalf) __attribute__((amdgpu_waves_per_eu(
 fluid3_stage_kernel(FluidSet S, FluidArgs A) {
     __shared__ double raw[kStageComps][kHaloCells];
     double* const pool = &raw[0][0];
-    double* const part = pool + 10 * kYStride;   // x half's sums, next to the y fluxes
+    double* const part = pool + 10 * kYStride;   // y differences, next to the y fluxes
     __shared__ double temp[THIRD == kThirdZero ? 6 * kTempCells : 1];
     const unsigned per_sp = (unsigned)(A.tx * A.ty);
     const unsigned w = xcd_work_index(blockIdx.x, gridDim.x);
@@ -269,20 +295,24 @@ fluid3_stage_kernel(FluidSet S, FluidArgs A) {
             double V[10], Q[9];
 #pragma unroll
             for (int k = 0; k < 10; ++k) V[k] = raw[k][c];
-            third_moment(V, m, Q);
+            const Divisor n(V[0]);
+            const double u[3] = {n.under(V[1]), n.under(V[2]), n.under(V[3])};
             if (THIRD == kThirdNet) {
                 const int row = map_row(j0 - 2 + jj);
                 const long long g = (long long)source_of(row) * nx + col_of_i(i0 - 2 + l);
                 const double sc = S.scale[sp][g];
                 const float* __restrict__ y = S.y[sp] + g * 16;
-#pragma unroll
-                for (int k = 0; k < 9; ++k) Q[k] += (row < 0 ? sc * par_q(k) : sc) * (double)y[k];
+                third_moment(V, u, m, Q, [&](int k, double v) {
+                    return fma(row < 0 ? sc * par_q(k) : sc, (double)y[k], v);
+                });
+            } else {
+                third_moment(V, u, m, Q, [](int, double v) { return v; });
             }
 #pragma unroll
             for (int k = 0; k < 9; ++k) raw[10 + k][c] = Q[k];
             if (THIRD == kThirdZero && l >= 1 && l <= kCols + 2 && jj >= 1 && jj <= kRows + 2) {
                 double T[6];
-                temperature6(V, m, T);
+                temperature6(V, u, n, m, T);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) temp[k * kTempCells + (jj - 1) * (kCols + 2) + l - 1] = T[k];
             }
@@ -298,7 +328,7 @@ fluid3_stage_kernel(FluidSet S, FluidArgs A) {
         const int r = (ty + 2) * kHaloC + tx + 1;
         const int i = i0 - 1 + tx, j = j0 + ty;
         const bool own = tx > 0 && tx <= kCols && i < nx && j < ny;
-        double u[10], L[10];
+        double u[10], D[10], L[10];           // L: sources, D: x differences of the fluxes
         {
             double lo[16], hi[16];
 #pragma unroll
@@ -308,13 +338,13 @@ fluid3_stage_kernel(FluidSet S, FluidArgs A) {
                 if (k % kBatch == kBatch - 1) __builtin_amdgcn_sched_barrier(0);
             }
             const double slo = wave_speed<0>(lo, m), shi = wave_speed<0>(hi, m);
-            const double a = fmax(shi, row_next<true>(slo));
+            const double ha = 0.5 * fmax(shi, row_next<true>(slo));
 #pragma unroll
             for (int k = 0; k < 16; ++k) lo[k] = row_next<true>(lo[k]);
 #pragma unroll
             for (int k = 0; k < 10; ++k) {
-                const double H = face_flux<0>(hi, lo, k, a, im);
-                L[k] = (row_next<false>(H) - H) * A.idx;
+                const double H = face_flux<0>(hi, lo, k, ha, im);
+                D[k] = H - row_next<false>(H);
             }
         }
         double Ev[3] = {0.0, 0.0, 0.0}, Bv[3] = {0.0, 0.0, 0.0};
@@ -329,27 +359,29 @@ fluid3_stage_kernel(FluidSet S, FluidArgs A) {
 #pragma unroll
         for (int k = 0; k < 10; ++k) u[k] = raw[k][r];
         __syncthreads();                      // every read of the cells is done
-        // sources: momentum (q/m)(n E + nu x B)
+        // sources: momentum (q/m)(n E + nu x B), the factor q/m below
         const double qm = q / m;
-        L[1] += qm * (u[0] * Ev[0] + u[2] * Bv[2] - u[3] * Bv[1]);
-        L[2] += qm * (u[0] * Ev[1] + u[3] * Bv[0] - u[1] * Bv[2]);
-        L[3] += qm * (u[0] * Ev[2] + u[1] * Bv[1] - u[2] * Bv[0]);
+        L[1] = fma(-u[3], Bv[1], fma(Ev[0], u[0], Bv[2] * u[2]));
+        L[2] = fma(-u[1], Bv[2], fma(Ev[1], u[0], Bv[0] * u[3]));
+        L[3] = fma(-u[2], Bv[0], fma(Ev[2], u[0], Bv[1] * u[1]));
         // second moment: q (nu_i E_j + nu_j E_i) + (q/m)(eps_jkl P_ik B_l + eps_ikl P_jk B_l)
         const double P[3][3] = {{u[4], u[5], u[6]}, {u[5], u[7], u[8]}, {u[6], u[8], u[9]}};
         double PxB[3][3];                     // row i of P crossed with B
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            PxB[d][0] = P[d][1] * Bv[2] - P[d][2] * Bv[1];
-            PxB[d][1] = P[d][2] * Bv[0] - P[d][0] * Bv[2];
-            PxB[d][2] = P[d][0] * Bv[1] - P[d][1] * Bv[0];
+            PxB[d][0] = d == 0 ? fma(-Bv[1], P[d][2], Bv[2] * P[d][1]) : fma(P[d][1], Bv[2], -(P[d][2] * Bv[1]));
+            PxB[d][1] = fma(P[d][2], Bv[0], -(P[d][0] * Bv[2]));
+            PxB[d][2] = fma(P[d][0], Bv[1], -(P[d][1] * Bv[0]));
         }
         const int ia[6] = {0, 0, 0, 1, 1, 2}, ib[6] = {0, 1, 2, 1, 2, 2};
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const int x = ia[k], y = ib[k];
-            L[4 + k] += q * (u[1 + x] * Ev[y] + u[1 + y] * Ev[x]) + qm * (PxB[x][y] + PxB[y][x]);
+            const double nE = u[1 + y] * Ev[x];
+            L[4 + k] = fma(q, x == y ? nE + nE : fma(u[1 + x], Ev[y], nE), qm * (PxB[x][y] + PxB[y][x]));
         }
         __syncthreads();                      // the y exchange is stored
+        double G[6];
         if constexpr (THIRD == kThirdZero) {
             // Eq. 5 as a source of P: -div Q = gchi n v_t lap T (gchi = chi / k0)
             if (own) {
@@ -360,39 +392,35 @@ fluid3_stage_kernel(FluidSet S, FluidArgs A) {
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
                     const double* tk = t + k * kTempCells;
-                    const double lx = (tk[1] - 2.0 * tk[0]) + tk[-1];
-                    const double ly = (tk[kCols + 2] - 2.0 * tk[0]) + tk[-(kCols + 2)];
-                    L[4 + k] += g * (lx * ix2 + ly * iy2);
+                    const double lx = fma(-2.0, tk[0], tk[1]) + tk[-1];
+                    const double ly = fma(-2.0, tk[0], tk[kCols + 2]) + tk[-(kCols + 2)];
+                    G[k] = g * fma(lx, ix2, ly * iy2);
                 }
             }
         }
         __syncthreads();                      // the y exchange has been read
-        // the half writes the block's results and loads U_n meanwhile
-        const int cols = nx - i0 < kCols ? nx - i0 : kCols, rows = ny - j0 < kRows ? ny - j0 : kRows;
-        const size_t g0 = ((size_t)j0 * nx + i0) * 10, stride = (size_t)nx * 10;
-        const double* Un = (A.a != 0.0 ? S.Un[sp] : Us) + g0;    // first stage: weight 0
-        const unsigned o = tid < cols * 10 ? (unsigned)tid : 0u;
-        double un[kRows];
-#pragma unroll
-        for (int jj = 0; jj < kRows; ++jj) un[jj] = (Un + (jj < rows ? jj : 0) * stride)[o];
         __syncthreads();                      // the y fluxes are stored
+        __syncthreads();                      // the y differences are stored
+        // 4. both directions
+        if (own) {
+            double* out = pool + (ty * kCols + tx - 1) * 10;
 #pragma unroll
-        for (int k = 0; k < 10; ++k) part[k * kXStride + tid] = fma(A.dt, L[k], u[k]);
-        __syncthreads();                      // the sums are stored
-        __syncthreads();                      // the results are stored
-        if (tid < cols * 10) {
-            double* Uo = S.Uo[sp] + g0;
-            const bool first = A.a == 0.0;
-#pragma unroll
-            for (int jj = 0; jj < kRows; ++jj) {
-                const double v = A.b * pool[jj * kCols * 10 + tid];
-                if (jj < rows) (Uo + jj * stride)[(unsigned)tid] = first ? v : fma(A.a, un[jj], v);
+            for (int k = 0; k < 10; ++k) {
+                const double d = fma(A.idx, D[k], part[k * kXStride + tid]);
+                double l = k == 0 ? -d : (k < 4 ? fma(qm, L[k], -d) : L[k] - d);
+                if constexpr (THIRD == kThirdZero)
+                    if (k >= 4) l += G[k - 4];
+                out[k] = fma(A.dt, l, u[k]);
             }
         }
+        __syncthreads();                      // the results are stored
     } else {
         // 3. y
         const bool lane = tid < kYLanes;
         const int t = lane ? tid : 0;
+        // lanes without a cell store into the padding entry: behind a branch the
+        // compiler would move part of every reconstruction, and its inputs spill
+        const int ts = lane ? tid : kYLanes;
         const int tx = t % kCols, ty = t / kCols;
         const int r = (ty + 1) * kHaloC + tx + 2;
         double lo[16], hi[16];
@@ -404,36 +432,49 @@ fluid3_stage_kernel(FluidSet S, FluidArgs A) {
         }
         const double slo = wave_speed<1>(lo, m), shi = wave_speed<1>(hi, m);
         __syncthreads();                      // every read of the cells is done
-        if (lane) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) pool[k * kYStride + t] = lo[k];
-            pool[16 * kYStride + t] = slo;
-        }
+        for (int k = 0; k < 16; ++k) pool[k * kYStride + ts] = lo[k];
+        pool[16 * kYStride + ts] = slo;
         __syncthreads();                      // the y exchange is stored
         const int up = ty <= kRows ? t + kCols : t;
 #pragma unroll
         for (int k = 0; k < 16; ++k) lo[k] = pool[k * kYStride + up];
-        const double a = fmax(shi, pool[16 * kYStride + up]);
+        const double ha = 0.5 * fmax(shi, pool[16 * kYStride + up]);
         __syncthreads();                      // the y exchange has been read
         double H[10];
 #pragma unroll
         for (int k = 0; k < 10; ++k) {
-            H[k] = face_flux<1>(hi, lo, k, a, im);
-            if (lane) pool[k * kYStride + t] = H[k];
+            H[k] = face_flux<1>(hi, lo, k, ha, im);
+            pool[k * kYStride + ts] = H[k];
         }
+        // this half writes the block's results and loads U_n meanwhile
+        const int cols = nx - i0 < kCols ? nx - i0 : kCols, rows = ny - j0 < kRows ? ny - j0 : kRows;
+        const size_t g0 = ((size_t)j0 * nx + i0) * 10, stride = (size_t)nx * 10;
+        const double* Un = (A.a != 0.0 ? S.Un[sp] : Us) + g0;    // first stage: weight 0
+        const unsigned o = tid < cols * 10 ? (unsigned)tid : 0u;
+        double un[kRows];
+#pragma unroll
+        for (int jj = 0; jj < kRows; ++jj) un[jj] = (Un + (jj < rows ? jj : 0) * stride)[o];
         __syncthreads();                      // the y fluxes are stored
         const int dn = ty > 0 ? t - kCols : t;
 #pragma unroll
-        for (int k = 0; k < 10; ++k) H[k] = (pool[k * kYStride + dn] - H[k]) * A.idy;
-        __syncthreads();                      // the sums are stored
-        // 4. both directions
+        for (int k = 0; k < 10; ++k) H[k] = (H[k] - pool[k * kYStride + dn]) * A.idy;
         if (lane && ty >= 1 && ty <= kRows) {
-            const double* sum = part + (ty - 1) * (kCols + 2) + tx + 1;
-            double* out = pool + ((ty - 1) * kCols + tx) * 10;
+            double* d = part + (ty - 1) * (kCols + 2) + tx + 1;
 #pragma unroll
-            for (int k = 0; k < 10; ++k) out[k] = fma(A.dt, H[k], sum[k * kXStride]);
+            for (int k = 0; k < 10; ++k) d[k * kXStride] = H[k];
         }
+        __syncthreads();                      // the y differences are stored
         __syncthreads();                      // the results are stored
+        if (tid < cols * 10) {
+            double* Uo = S.Uo[sp] + g0;
+            const bool first = A.a == 0.0;
+#pragma unroll
+            for (int jj = 0; jj < kRows; ++jj) {
+                const double v = pool[jj * kCols * 10 + tid];
+                if (jj < rows) (Uo + jj * stride)[(unsigned)tid] = first ? v : fma(A.b, v, A.a * un[jj]);
+            }
+        }
     }
 }
 
@@ -483,9 +524,9 @@ __global__ void __launch_bounds__(256) line_rk3_kernel(LineFluid G) {
     double us[3] = {un[0], un[1], un[2]};
     const double m = G.m;
     auto spd = [m](const double* V) {
-        const double u = V[1] / V[0];
-        const double p = V[2] - m * V[0] * u * u;
-        return fabs(u) + sqrt(fmax(3.0 * p / (m * V[0]), 0.0));
+        const double u = V[1] / V[0], mn = m * V[0];
+        const double p = fma(-u, mn * u, V[2]);
+        return fabs(u) + sqrt(fmax(3.0 * p / mn, 0.0));
     };
 #pragma unroll 1
     for (int s = 0; s < 3; ++s) {
@@ -519,11 +560,11 @@ __global__ void __launch_bounds__(256) line_rk3_kernel(LineFluid G) {
                 e = (s == 0 ? G.E_t : (s == 1 ? G.E_t1 : G.E_th))[i];
             }
             const double a = s == 0 ? 0.0 : (s == 1 ? 0.75 : 1.0 / 3.0), b = s == 0 ? 1.0 : (s == 1 ? 0.25 : 2.0 / 3.0);
-            const double L[3] = {0.0, (G.q / m) * us[0] * e, 2.0 * G.q * us[1] * e};
+            const double f[3] = {0.0, (G.q / m) * us[0], 2.0 * G.q * us[1]};     // source: f e
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const double v = us[k] + G.dt * (L[k] - (F[k][c] - F[k][c - 1]) / G.dx);
-                us[k] = (a != 0.0 ? a * un[k] : 0.0) + b * v;
+                const double v = fma(G.dt, fma(f[k], e, -((F[k][c] - F[k][c - 1]) / G.dx)), us[k]);
+                us[k] = fma(b, v, a != 0.0 ? a * un[k] : 0.0);
             }
         }
         __syncthreads();
