@@ -421,51 +421,49 @@ __device__ __forceinline__ void affine_exact(T (&g)[N], T d0, T d1, T F2) {
 }
 
 // The general case, one pencil in shared memory: the feet clamped to the box
-// [0, n] (F_0 = 0, F_n = n); F = j + t (0 <= t < 1) splits a foot, and
+// [0, N] (F_0 = 0, F_N = N); F = j + t (0 <= t < 1) splits a foot, and
 // R = phi(j, 1 - t) is the mass of cell j above it (phi the limited partial flux;
 // R = f_j exactly at t = 0, 0 beyond the box).  Output cell i holds the mass
 // between its two feet:
 //   j_{i+1} == j_i:  R_i - R_{i+1}
 //   else:            R_i + f_{j_i+1} + ... + f_{j_{i+1}-1} + (f_{j_{i+1}} - R_{i+1}),
-// so whole-cell moves are exact and the pencil's mass telescopes.
-template <class T, int NMAX>
-__device__ __attribute__((noinline)) void affine_far(T* pc, int stride, int n, T ia, T ib, T finf) {
-    auto val = [&](int j) -> T { return (j >= 0 && j < n) ? pc[j * stride] : T(0); };
-    // right part of cell j above a foot at j + t
-    auto rpart = [&](int j, T t) -> T {
-        if (j >= n) return T(0);
-        const T a = T(1) - t;
-        const T c1 = t * (T(1) + t) * T(1.0 / 6.0), c2 = t * (T(2) - t) * T(1.0 / 6.0);
-        return pfc_phi(val(j - 1), val(j), val(j + 1), a, c1, c2, finf);
-    };
-    T out[NMAX];
+// so whole-cell moves are exact and the pencil's mass telescopes.  A foot's
+// three cells are read at indices clamped to the pencil and set to zero beyond
+// it: with a branch around each read, and the length a run-time number, a face
+// took 150 instructions instead of about 50, and a wave that holds pencils of
+// both kinds runs this after affine_exact.
+template <class T, int N>
+__device__ __attribute__((noinline)) void affine_far(LdsPtr<T> pc, int stride, T ia, T ib, T F2) {
+    auto at = [&](int k) -> T { return pc[__umul24((unsigned)k, (unsigned)stride)]; };
+    T out[N];
     int jp = 0;
-    T Rp = val(0);                                  // face 0: F = 0
-    const T nT = (T)n;
+    T Rp = pc[0];                                   // face 0: F = 0
 #pragma unroll
-    for (int i = 0; i < NMAX; ++i) {
-        if (i < n) {
-            T F = (i + 1 == n) ? nT : fmin(fmax(fma((T)(i + 1), ia, ib), T(0)), nT);
+    for (int i = 0; i < N; ++i) {
+        int j = N;
+        T R = T(0), f0 = T(0);                      // face N: F = N
+        if (i + 1 < N) {
+            const T F = fmin(fmax(fma((T)(i + 1), ia, ib), T(0)), (T)N);
             const T fj = floor(F);
-            const int j = (int)fj;
+            j = (int)fj;
             const T t = F - fj;
-            const T R = rpart(j, t);
-            T o;
-            if (j == jp) {
-                o = Rp - R;
-            } else {
-                T acc = Rp;
-                for (int m = jp + 1; m < j; ++m) acc += val(m);
-                o = acc + (val(j) - R);
-            }
-            out[i] = fmax(o, T(0));
-            jp = j;
-            Rp = R;
+            const T m0 = at(j < N ? j : N - 1), mm = at(j > 0 ? j - 1 : 0), mp = at(j + 1 < N ? j + 1 : N - 1);
+            f0 = j < N ? m0 : T(0);
+            const T fm = j > 0 ? mm : T(0), fp = j + 1 < N ? mp : T(0);
+            const T c1 = fma(t, t, t) * T(1.0 / 6.0), c2 = (t + t - t * t) * T(1.0 / 6.0);
+            const T f2 = f0 + f0, r2 = fmax(F2 - f2, T(0));
+            R = (T(1) - t) * fma(c2, med3(f0 - fm, -f2, r2), fma(c1, med3(fp - f0, -r2, f2), f0));
         }
+        T acc = Rp;
+#pragma unroll 1
+        for (int m = jp + 1; m < j; ++m) acc += at(m);
+        out[i] = fmax(j == jp ? Rp - R : acc + (f0 - R), T(0));
+        asm volatile("" : "+v"(out[i]));            // formed here: moved to the stores, it holds seven registers a face
+        jp = j;
+        Rp = R;
     }
 #pragma unroll
-    for (int i = 0; i < NMAX; ++i)
-        if (i < n) pc[i * stride] = out[i];
+    for (int i = 0; i < N; ++i) pc[i * stride] = out[i];
 }
 
 // One pencil of N cells (kIn: read from global memory) into shared memory.
@@ -491,13 +489,13 @@ __device__ __forceinline__ void affine_pencil(const T* __restrict__ src, unsigne
 #pragma unroll
             for (int m = 0; m < N; ++m) pc[m * stride] = g[m];
         }
-        affine_far<T, (N <= 16 ? 16 : (N <= 32 ? 32 : N))>(pc, stride, N, (T)ia, (T)(-sa), finf);
+        affine_far<T, N>(lds_ptr(pc), stride, (T)ia, (T)(-sa), T(2) * finf);
     }
 }
 
 // One sweep of the cell's block.  C: the twelve coefficients of the factored
 // map, then the reciprocals of its three stretches.
-template <class T, bool kIn, int NEXACT>
+template <class T, bool kIn, int NEXACT, int LMAX>
 __device__ __forceinline__ void sweep_affine(const T* __restrict__ src, T* blk, int dd, const double* C,
                                              const V3Params& P, T finf) {
     const int pz = P.nvz | 1;
@@ -523,7 +521,7 @@ __device__ __forceinline__ void sweep_affine(const T* __restrict__ src, T* blk, 
         } else {
 #define VL_LEN(N)                                                                                 \
     case N:                                                                                       \
-        affine_pencil<T, N, kIn>(src + pen, plane, blk + base, stride, ia, sa, finf);             \
+        if constexpr (N <= LMAX) affine_pencil<T, N, kIn>(src + pen, plane, blk + base, stride, ia, sa, finf); \
         break;
             VL_LENGTHS(n)
 #undef VL_LEN
@@ -542,10 +540,15 @@ __device__ __forceinline__ void sweep_affine(const T* __restrict__ src, T* blk, 
 // first, 640 of 34^3 FP32 279 -> 162.  Six waves per SIMD (80 registers, spills)
 // instead of four: 160.
 //
-// NEXACT: cube edge, or 0 for any axes of 2 to 32 cells (code for each exact
-// length, chosen by a switch).
-template <class T, int NEXACT, int NTH, bool kFold>
-__global__ void __launch_bounds__(NTH)
+// NEXACT: cube edge, or 0 for any axes of 2 to LMAX cells (code for each exact
+// length, chosen by a switch).  LMAX 32 takes 255 registers in FP32, two waves
+// a SIMD, because of the longest pencils; the cubes and grids of short axes have
+// code of their own, which takes 79 to 117: 8^3 256x128 cells FP32 51 us against
+// 56, 12^3 200x100 104 against 150, 16^3 232 against 334 (FP64 79, 198, 452
+// against 80, 245, 536), 4^3 300x200 with axes up to 8 53 against 124.  Holding
+// LMAX 32 to 128 registers spills: 20x16x24 100x50 383 against 175.
+template <class T, int NEXACT, int LMAX, int NTH, bool kFold>
+__global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(LMAX <= 8 ? (sizeof(T) == 4 ? 6 : 4) : 1)))
 pfc_v3b_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B,
                V3Params P, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
@@ -569,11 +572,11 @@ pfc_v3b_kernel(const T* fin, T* fout, const double* __restrict__ E, const double
     }
     __syncthreads();
     const T* src = fin + cell * nv;
-    sweep_affine<T, true, NEXACT>(src, blk, 0, Cs, P, finf);
+    sweep_affine<T, true, NEXACT, LMAX>(src, blk, 0, Cs, P, finf);
     __syncthreads();
 #pragma unroll 1
     for (int d = 1; d < 3; ++d) {
-        sweep_affine<T, false, NEXACT>(src, blk, d, Cs, P, finf);
+        sweep_affine<T, false, NEXACT, LMAX>(src, blk, d, Cs, P, finf);
         __syncthreads();
     }
     T* dst = fout + cell * nv;
@@ -674,7 +677,9 @@ pfc_v1_kernel(const T* fin, T* fout, int nx, int nv, LineField S, double qm_tau_
 // whole pencils in registers.
 //
 // The pencil length is a run-time number, but each sweep runs code for exactly
-// that length (a switch, uniform over the launch): a pencil of 20 cells in code
+// that length (a switch over 2 to LMAX, uniform over the launch; LMAX 8 for grids
+// of short axes, whose 64 registers leave room for more one-wave blocks: 4^3
+// 300x200 cells FP32 66 us against 81, FP64 87 against 156): a pencil of 20 cells in code
 // for 32 with a window shifted by K, guards on every cell and unmerged
 // differences took 3.5 times the instructions.  The first v_x sweep reads its
 // pencils from global memory and the last writes them there (unit stride over
@@ -713,33 +718,39 @@ __device__ __forceinline__ void sweep_exact(T (&g)[N], T a, T c1, T c2, T finf) 
 }
 
 // A pencil in shared memory that moves by K >= 1 cells (element k at
-// first + k step, downwind order), in place from its far end: output p reads
-// cells up to p - K + 1, which outputs below p have not overwritten; the wall
-// cell keeps all that reaches it.
-template <class T>
-__device__ __attribute__((noinline)) void pencil_far(T* blk, int first, int step, int n, int K, T a, T c1, T c2,
+// first + k step, downwind order), in place: cell p reads cells p - K - 2 ..
+// p - K + 1, held in registers as a window; the wall cell keeps all that
+// reaches it.  Code for each length, called: 60000 cells of 4^3 FP64 moving by
+// several cells 199 us with one loop for all lengths, four dependent reads a cell.
+template <class T, int N>
+__device__ __attribute__((noinline)) void pencil_far(LdsPtr<T> blk, int first, int step, int K, T a, T c1, T c2,
                                                       T finf) {
 #pragma clang fp contract(off)
-    auto val = [&](int k) -> T { return k >= 0 ? blk[first + k * step] : T(0); };
-    auto factor = [&](int k) {
-        const T w = val(k);
-        return flux_factor(w, w - val(k - 1), val(k + 1) - w, c1, c2, finf);
-    };
-    T top = T(0);
-    for (int m = n - 1 - K > 0 ? n - 1 - K : 0; m < n; ++m) top += val(m);
-    T X = factor(n - 2 - K);
-    const T wall = fmax(fma(X, a, top), T(0));
-    T phi = X * a;                                    // leaving window position p = n - 2
-    for (int p = n - 2; p >= 0; --p) {
-        const T w = val(p - K);
-        X = factor(p - 1 - K);
-        const T below = X * a;
-        // the cells at and above p are read by no later output
-        const T o = fmax((w + below) - phi, T(0));
-        blk[first + p * step] = o;
-        phi = below;
+    T W[N + 2];                                       // W[j + 2]: cell j - K
+    int q = first - (K + 2) * step;
+#pragma unroll
+    for (int j = -2; j < N; ++j) {
+        const bool in = j - K >= 0;
+        const T v = blk[in ? q : first];
+        W[j + 2] = in ? v : T(0);
+        q += step;
     }
-    blk[first + (n - 1) * step] = wall;
+    T top = T(0);
+    for (int m = N - 1 - K > 0 ? N - 1 - K : 0; m < N; ++m) top += blk[first + m * step];
+    auto factor = [&](int p) {                        // cell p - K
+        const T w = W[p + 2];
+        return flux_factor(w, w - W[p + 1], W[p + 3] - w, c1, c2, finf);
+    };
+    T X = factor(-1);
+    T below = X * a;
+#pragma unroll
+    for (int p = 0; p < N - 1; ++p) {
+        X = factor(p);
+        const T phi = X * a;
+        blk[first + p * step] = fmax((W[p + 2] + below) - phi, T(0));
+        below = phi;
+    }
+    blk[first + (N - 1) * step] = fmax(fma(X, a, top), T(0));
 }
 
 // One pencil of N cells: kIn from global memory (else from shared), kOut to
@@ -758,6 +769,10 @@ __device__ __forceinline__ void pencil_exact(const T* __restrict__ src, T* __res
     }
     if (sh.K == 0) {
         sweep_exact<T, N>(g, sh.a, sh.c1, sh.c2, finf);
+        if constexpr (!kOut) {
+#pragma unroll
+            for (int m = 0; m < N; ++m) blk[first + m * step] = g[m];
+        }
     } else {
         // beyond n + 2 cells every output but the wall cell is 0 either way
         const int K = sh.K > (long long)(N + 2) ? N + 2 : (int)sh.K;
@@ -765,9 +780,11 @@ __device__ __forceinline__ void pencil_exact(const T* __restrict__ src, T* __res
 #pragma unroll
             for (int m = 0; m < N; ++m) blk[first + m * step] = g[m];
         }
-        pencil_far<T>(blk, first, step, N, K, sh.a, sh.c1, sh.c2, finf);
+        pencil_far<T, N>(lds_ptr(blk), first, step, K, sh.a, sh.c1, sh.c2, finf);
+        if constexpr (kOut) {
 #pragma unroll
-        for (int m = 0; m < N; ++m) g[m] = blk[first + m * step];
+            for (int m = 0; m < N; ++m) g[m] = blk[first + m * step];
+        }
     }
     if constexpr (kOut) {
 #pragma unroll
@@ -775,13 +792,10 @@ __device__ __forceinline__ void pencil_exact(const T* __restrict__ src, T* __res
             dst[goff + (unsigned)m * gstep] = g[m];
             mx = fmax(mx, g[m]);
         }
-    } else {
-#pragma unroll
-        for (int m = 0; m < N; ++m) blk[first + m * step] = g[m];
     }
 }
 
-template <class T, bool kIn, bool kOut>
+template <class T, bool kIn, bool kOut, int LMAX>
 __device__ __forceinline__ void sweep_any(const T* __restrict__ src, T* __restrict__ dst, T* blk, int d, double sigma,
                                           const V3Params& P, const double (&EB)[6], T finf, T& mx) {
     const int pz = P.nvz | 1;
@@ -819,15 +833,16 @@ __device__ __forceinline__ void sweep_any(const T* __restrict__ src, T* __restri
         const unsigned gstep = pos ? plane : 0u - plane;
 #define VL_LEN(N)                                                                                     \
     case N:                                                                                           \
-        pencil_exact<T, N, kIn, kOut>(src, dst, blk, goff, gstep, first, step, sh, finf, mx);         \
+        if constexpr (N <= LMAX)                                                                      \
+            pencil_exact<T, N, kIn, kOut>(src, dst, blk, goff, gstep, first, step, sh, finf, mx);     \
         break;
         VL_LENGTHS(n)
 #undef VL_LEN
     }
 }
 
-template <class T>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+template <class T, int LMAX, int NTH>
+__global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(LMAX <= 8 ? (sizeof(T) == 4 ? 8 : 5) : (sizeof(T) == 4 ? 4 : 2))))
 pfc_v3_kernel(const T* fin, T* fout, const double* __restrict__ E, const double* __restrict__ B,
               V3Params P, MaxRef finf_r, typename Bits<T>::U* __restrict__ max_out) {
     extern __shared__ unsigned char smem_raw[];
@@ -845,16 +860,16 @@ pfc_v3_kernel(const T* fin, T* fout, const double* __restrict__ E, const double*
     T* dst = fout + cell * nv;
     const double half = 0.5 * P.tau;
     T mx = T(0);
-    sweep_any<T, true, false>(src, dst, blk, 0, half, P, eb, finf, mx);
+    sweep_any<T, true, false, LMAX>(src, dst, blk, 0, half, P, eb, finf, mx);
     __syncthreads();
     // one copy of the in-block code: vy, vz, vy
 #pragma unroll 1
     for (int k = 0; k < 3; ++k) {
         const int d = k == 1 ? 2 : 1;
-        sweep_any<T, false, false>(src, dst, blk, d, d == 2 ? P.tau : half, P, eb, finf, mx);
+        sweep_any<T, false, false, LMAX>(src, dst, blk, d, d == 2 ? P.tau : half, P, eb, finf, mx);
         __syncthreads();
     }
-    sweep_any<T, false, true>(src, dst, blk, 0, half, P, eb, finf, mx);
+    sweep_any<T, false, true, LMAX>(src, dst, blk, 0, half, P, eb, finf, mx);
     if (max_out) block_max_part(mx, max_out);
 }
 
@@ -934,8 +949,8 @@ __device__ __forceinline__ void regs_mixed(T (&g)[N], bool pos, T a, T ac1, T ac
 
 // Shifts of a cell or more (any lane of the wave): windows gathered in the
 // sweep direction, the cells within K of the far wall summed into it.
-template <class T, int N>
-__device__ __attribute__((noinline)) void pencil_shifted(T* blk, int first, int step, int K, T a, T ac1, T ac2,
+template <class T, int N, class Ptr>
+__device__ __attribute__((noinline)) void pencil_shifted(Ptr blk, int first, int step, int K, T a, T ac1, T ac2,
                                                           T F2) {
     T W[N + 2];
     int q = first - (K + 2) * step;
@@ -984,7 +999,7 @@ __device__ __forceinline__ void sweep_pencil_regs(T (&g)[N], bool pos, const Shi
         for (int m = 0; m < N; ++m) blk[base + m * stride] = g[m];
         const int K = sh.K > N + 2 ? N + 2 : sh.K;
         const int first = pos ? base : base + (N - 1) * stride;
-        pencil_shifted<T, N>(blk, first, pos ? stride : -stride, K, sh.a, sh.ac1, sh.ac2, F2);
+        pencil_shifted<T, N>(lds_ptr(blk), first, pos ? stride : -stride, K, sh.a, sh.ac1, sh.ac2, F2);
 #pragma unroll
         for (int m = 0; m < N; ++m) g[m] = blk[base + m * stride];
     }
@@ -1034,7 +1049,7 @@ __device__ __forceinline__ void sweep_cube_pencil(T* blk, int d, int pen, bool p
     } else {
         const int K = sh.K > N + 2 ? N + 2 : sh.K;
         const int first = pos ? base : base + (N - 1) * stride;
-        pencil_shifted<T, N>(blk, first, pos ? stride : -stride, K, sh.a, sh.ac1, sh.ac2, F2);
+        pencil_shifted<T, N>(lds_ptr(blk), first, pos ? stride : -stride, K, sh.a, sh.ac1, sh.ac2, F2);
     }
 }
 
@@ -1779,8 +1794,9 @@ hipError_t launch_pfc_v3(const T* fin, T* fout, long long cells, const double* E
         hipLaunchKernelGGL((finf.n > 1 ? pfc_v3_cube_kernel<T, 8, 64, true> : pfc_v3_cube_kernel<T, 8, 64, false>), grid, dim3(64), 0, st, fin, fout, E, B, P, finf, mo);
     } else if (nmax <= 32) {
         const int pens[5] = {P.nvy * P.nvz, P.nvx * P.nvz, P.nvx * P.nvy, P.nvx * P.nvz, P.nvy * P.nvz};
-        const int threads = pencil_threads(pens, 5, shm, sizeof(T) == 4 ? 16 : 8, cells, true);
-        hipLaunchKernelGGL((pfc_v3_kernel<T>), grid, dim3(threads), shm, st, fin, fout, E, B, P, finf, mo);
+        const int threads = nmax <= 8 ? 64 : pencil_threads(pens, 5, shm, sizeof(T) == 4 ? 16 : 8, cells, true);
+        hipLaunchKernelGGL((nmax <= 8 ? pfc_v3_kernel<T, 8, 64> : pfc_v3_kernel<T, 32, 512>), grid, dim3(threads), shm,
+                           st, fin, fout, E, B, P, finf, mo);
     } else {
         return hipErrorInvalidValue;
     }
@@ -1802,7 +1818,7 @@ hipError_t launch_pfc_v3b(const T* fin, T* fout, long long cells, const double* 
             if (!cube || P.nvx != kBigCube || shm > 160 * 1024) return hipErrorInvalidValue;
             // one workgroup per CU (the block fills the LDS): 640 threads, two
             // pencils each per sweep (1156 per sweep)
-            hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, kBigCube, 640, true> : pfc_v3b_kernel<T, kBigCube, 640, false>),
+            hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, kBigCube, kBigCube, 640, true> : pfc_v3b_kernel<T, kBigCube, kBigCube, 640, false>),
                                grid, dim3(640), shm, st, fin, fout, E, B, P, finf, mo);
             return finish_max<T>(sink, cells, st);
         } else {
@@ -1810,16 +1826,21 @@ hipError_t launch_pfc_v3b(const T* fin, T* fout, long long cells, const double* 
         }
     }
     const int pens[3] = {P.nvy * P.nvz, P.nvx * P.nvz, P.nvx * P.nvy};
-    const int threads = pencil_threads(pens, 3, shm, sizeof(T) == 4 ? 16 : 8, cells, true);
-    const dim3 blk(threads);
+    const int threads = nmax <= 8 ? 64 : pencil_threads(pens, 3, shm, sizeof(T) == 4 ? 16 : 8, cells, true);
+#define VL_V3B(N, L, NTH)                                                                                    \
+    hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, N, L, NTH, true> : pfc_v3b_kernel<T, N, L, NTH, false>), grid, \
+                       dim3(threads), shm, st, fin, fout, E, B, P, finf, mo)
     if (cube && P.nvx == 16)
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 16, 512, true> : pfc_v3b_kernel<T, 16, 512, false>), grid, blk, shm, st, fin, fout, E, B, P, finf, mo);
+        VL_V3B(16, 16, 512);
     else if (cube && P.nvx == 12)
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 12, 512, true> : pfc_v3b_kernel<T, 12, 512, false>), grid, blk, shm, st, fin, fout, E, B, P, finf, mo);
+        VL_V3B(12, 12, 512);
     else if (cube && P.nvx == 8)
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 8, 512, true> : pfc_v3b_kernel<T, 8, 512, false>), grid, blk, shm, st, fin, fout, E, B, P, finf, mo);
+        VL_V3B(8, 8, 64);
+    else if (nmax <= 8)
+        VL_V3B(0, 8, 64);
     else
-        hipLaunchKernelGGL((finf.n > 1 ? pfc_v3b_kernel<T, 0, 512, true> : pfc_v3b_kernel<T, 0, 512, false>), grid, blk, shm, st, fin, fout, E, B, P, finf, mo);
+        VL_V3B(0, 32, 512);
+#undef VL_V3B
     return finish_max<T>(sink, cells, st);
 }
 

@@ -120,6 +120,16 @@ __device__ __forceinline__ void block_sum_rs(const double (&a)[K], double* red, 
         VL_LEN(29) VL_LEN(30) VL_LEN(31) VL_LEN(32)                                                          \
     }
 
+// Pointer to shared memory for functions that are not inlined: given a generic
+// pointer they use flat accesses, or test it for null and convert it at each
+// one, unless every caller passes the same array.
+template <class T>
+using LdsPtr = __attribute__((address_space(3))) T*;
+template <class T>
+__device__ __forceinline__ LdsPtr<T> lds_ptr(T* p) {
+    return (LdsPtr<T>)p;
+}
+
 // Streaming access to f: non-temporal (the lines are not kept in the caches)
 // when NT, else an ordinary access.  Velocity blocks whose rows are not whole
 // 128-byte lines (12^3 FP32: 576 B) have lines shared by two wave accesses;
