@@ -1417,10 +1417,15 @@ pfc_v3_planes_kernel(const T* fin, T* fout, const double* __restrict__ E, const 
 
 // ---------------------------------------------------------------------------
 // Maximum of an array: 16-byte loads (where f is 16-byte aligned), four in
-// flight per thread, read once and not kept in the caches.  226 MB: 58 us with
-// one 4-byte load in flight, 48 with 16-byte loads that go through the caches,
-// now 38 (6.0 TB/s).
-template <class T>
+// flight per thread.  Read past the caches where f is larger than the last-level
+// cache (226 MB: 58 us with one 4-byte load in flight, 48 with 16-byte loads
+// through the caches, 38 past them, 6.0 TB/s), else through it: the operator
+// that needs the maximum reads f next and gains more than this kernel loses.
+// X and its maximum, FP64 8^3 256x128 (134 MB) 103 us past and 94 through the
+// caches, FP32 10^3 200x100 (80 MB) 72 and 67, 12^3 at 224 MB 158 and 151;
+// beyond, V or X of 268 to 450 MB is 1 to 5 % slower through them.
+constexpr long long kLastLevelBytes = 224ll << 20;
+template <class T, bool kPast>
 __global__ void __launch_bounds__(256)
 array_max_kernel(const T* __restrict__ f, long long n, typename Bits<T>::U* __restrict__ out) {
     constexpr int V = 16 / (int)sizeof(T);
@@ -1433,7 +1438,10 @@ array_max_kernel(const T* __restrict__ f, long long n, typename Bits<T>::U* __re
     for (; i + 3 * stride < nvec; i += 4 * stride) {
         Vec v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(fv + i + u * stride);
+        for (int u = 0; u < 4; ++u) {
+            if constexpr (kPast) v[u] = __builtin_nontemporal_load(fv + i + u * stride);
+            else v[u] = fv[i + u * stride];
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -1849,8 +1857,9 @@ hipError_t launch_array_max(const T* f, long long n, const MaxSink& sink, hipStr
     long long blocks = (n + 2047) / 2048;
     if (blocks > kMaxArrayBlocks) blocks = kMaxArrayBlocks;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL((array_max_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, st, f, n,
-                       sink.target<T>(blocks));
+    const bool past = n * (long long)sizeof(T) > kLastLevelBytes;
+    hipLaunchKernelGGL((past ? array_max_kernel<T, true> : array_max_kernel<T, false>), dim3((unsigned)blocks), dim3(256),
+                       0, st, f, n, sink.target<T>(blocks));
     return finish_max<T>(sink, blocks, st);
 }
 
