@@ -65,7 +65,7 @@ struct NetLdsT {
     unsigned short wt4[kWid * kLdt4];     // W4^T [64][16]
 };
 
-__device__ void load_net(const float* __restrict__ P, NetLds& N, NetLdsT* T) {
+__device__ __forceinline__ void load_net(const float* __restrict__ P, NetLds& N, NetLdsT* T) {
     const int tid = threadIdx.x, nthr = blockDim.x;
     if (nthr == 512 && !((uintptr_t)P & 15u)) {
         // 512 threads, 16-byte aligned parameters: all seven float4 loads of a
