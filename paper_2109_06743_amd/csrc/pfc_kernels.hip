@@ -156,6 +156,7 @@ __device__ __forceinline__ T sub_cell_flux(T w, T Dm, T Dp, T a, T cA, T cB, T F
 // flight cover whole rows and neighbouring strips (x halos) together.
 struct XYArgs {
     int nx, ny, Nv, nvy, nvz, S, nchunks, nst, nseg, per;
+    int pad;              // entries of max_out; those beyond the grid's are set to 0
     float inv_nvz, inv_nvyz;
     double vx_lo, dvx, tau_dx, vy_lo, dvy, tau_dy;
 };
@@ -325,7 +326,11 @@ pfc_xy_kernel(const T* __restrict__ fin, T* __restrict__ fout, XYArgs A, MaxRef 
         if (i + 1 <= ie) step(i + 1, W1, W0);
         if (i + 2 <= ie) step(i + 2, W2, W1);
     }
-    if (max_out) block_max_part(mx, max_out);
+    if (max_out) {
+        block_max_part(mx, max_out);
+        if (blockIdx.x == 0)
+            for (int k = (int)(gridDim.x + threadIdx.x); k < A.pad; k += 256) max_out[k] = 0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1629,11 +1634,13 @@ static double xy_even(int nx, int ny, long long Nv, int kb, int cols) {
     return (double)w / (double)((w + simds - 1) / simds * simds);
 }
 
-// Upper bound of the launch's blocks over every segment length it can pick
-// (sizes the per-block partial maxima).
+// Upper bound of the launch's blocks over every strip width and segment length
+// it can pick, for any tau (sizes the per-block partial maxima).
 long long pfc_xy_blocks(int nx, int ny, int nvx, int nvy, int nvz) {
     const long long Nv = (long long)nvx * nvy * nvz;
-    const long long nseg = ny < kXyMaxSeg ? ny : kXyMaxSeg;
+    // more than one segment: S = ceil(ny / n) >= 4 in xy_segment, or 128 rows each
+    const int most = ny > 4 ? (ny - 1) / 3 : 1;
+    const long long nseg = most < kXyMaxSeg ? most : ((ny + 127) / 128 > kXyMaxSeg ? (ny + 127) / 128 : kXyMaxSeg);
     const long long w = xy_waves_per_seg(nx, Nv, 4) * nseg;    // 4 columns: a bound for every strip width
     return (w + 3) / 4;
 }
@@ -1668,6 +1675,7 @@ static hipError_t launch_pfc_xy_cols(const T* fin, T* fout, int nx, int ny, int 
     const size_t rowbytes = (size_t)nx * A.Nv * sizeof(T);
     const bool wide = (double)(2 * kb + 3) * (double)rowbytes >= 4294967296.0;
     auto* mo = sink.target<T>(blocks);
+    A.pad = mo && sink.direct(blocks) ? sink.fixed : 0;
     // Workgroups resident per CU, set through a reservation of shared memory
     // the kernel does not use: with fewer waves in flight the walks of large
     // velocity blocks thrash the caches and the address translation less.

@@ -116,6 +116,16 @@ vl::MaxSink max_to(vl_ctx* c, int which, int s) {
     return {slot(c, which, s), c->bpart[s], &c->slot_n[which][s],
             (which == 0 || which == 2) ? vl::kDirectX : vl::kDirectV};     // slots 1 and 3 feed V
 }
+// Slot 0 of species s from the last X sweep of a 2X3V step without fitting: the
+// one producer whose block count varies with dt.
+vl::MaxSink max_kept_by_x(vl_ctx* c, int s) {
+    const vl_species& sp = c->cfg.sp[s];
+    const long long most = vl::pfc_xy_blocks(c->cfg.nx, c->cfg.ny, sp.nv[0], sp.nv[1], sp.nv[2]);
+    vl::MaxSink m = max_to(c, 0, s);
+    m.most = most <= vl::kSlotMax ? vl::kSlotMax : 0;
+    m.fixed = (int)(most <= vl::kSlotMax ? most : 0);
+    return m;
+}
 constexpr vl::MaxSink kNoMax{};
 
 vl_status ensure_device(vl_ctx* ctx) {
@@ -498,7 +508,7 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
                 VL_OK)
                 return r;
             if ((r = advect_x_typed<T>(ctx, s, tmp, f, 0.5 * dt, max_in(ctx, 2, s),
-                                       c.fit ? kNoMax : max_to(ctx, 0, s), st)) != VL_OK)
+                                       c.fit ? kNoMax : max_kept_by_x(ctx, s), st)) != VL_OK)
                 return r;
             if ((r = moments_typed<T>(ctx, s, f, S->mom_pre[s], st)) != VL_OK) return r;
             if (!c.fit) {

@@ -24,7 +24,10 @@ struct V3Params;  // pfc_kernels.hip
 // them: its waves are few and walk many cells (1024 partials: two batches of
 // loads).  kDirectV where the velocity operator does: every cell's waves fold
 // them again (1024 partials cost it 20 % at 256x128x16^3, 64 nothing).
-// slot null: no maximum wanted.  *n receives the number of entries the slot holds.
+// slot null: no maximum wanted.  *n receives the number of entries the slot
+// holds; with `fixed` set that number whatever the launch's blocks, the producer
+// filling up with zeros (a maximum kept for the next step, which may be part of a
+// graph, must not depend on dt).
 constexpr int kSlotMax = 1024;
 constexpr int kDirectX = 1024, kDirectV = 64;
 struct MaxSink {
@@ -32,11 +35,12 @@ struct MaxSink {
     void* part = nullptr;
     int* n = nullptr;
     int most = 0;
+    int fixed = 0;
     bool direct(long long blocks) const { return blocks <= most; }
     template <class T>
     typename Bits<T>::U* target(long long blocks) const {
         if (!slot) return nullptr;
-        *n = direct(blocks) ? (int)blocks : 1;
+        *n = direct(blocks) ? (fixed ? fixed : (int)blocks) : 1;
         return (typename Bits<T>::U*)(direct(blocks) ? slot : part);
     }
 };
