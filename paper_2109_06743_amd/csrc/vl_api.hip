@@ -145,19 +145,25 @@ vl_status ensure_device(vl_ctx* ctx) {
     const size_t clip_bytes = (4 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
     void* p = nullptr;
     VL_HIP(hipMalloc(&p, bytes + (part_bytes + clip_bytes) * ctx->cfg.nspecies));
-    VL_HIP(hipMemset(p, 0, slot_bytes));
+    auto* slots = (unsigned long long*)p;
+    double* green = (double*)(slots + (size_t)kSlots * VL_MAX_SPECIES * vl::kSlotMax);
+    hipError_t e = hipMemset(p, 0, slot_bytes);
+    if (e == hipSuccess && ctx->cfg.dim_x == 1) {
+        // once per context; finished before any stream can use it
+        e = vl::launch_poisson_green(ctx->cfg.nx, ctx->cfg.x_hi - ctx->cfg.x_lo, green, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    }
+    if (e != hipSuccess) {          // nothing is kept: the next call starts over
+        (void)hipFree(p);
+        return fail(ctx, VL_EHIP, "context scratch: %s", hipGetErrorString(e));
+    }
     for (int s = 0; s < ctx->cfg.nspecies; ++s) {
         ctx->bpart[s] = (char*)p + bytes + s * (part_bytes + clip_bytes);
         ctx->bclip[s] = (unsigned*)((char*)ctx->bpart[s] + part_bytes);
     }
-    ctx->slots = (unsigned long long*)p;
-    ctx->green = (double*)(ctx->slots + (size_t)kSlots * VL_MAX_SPECIES * vl::kSlotMax);
-    ctx->part = ctx->green + (size_t)ctx->cfg.nx;
-    if (ctx->cfg.dim_x == 1) {
-        // once per context; finished before any stream can use it
-        VL_HIP(vl::launch_poisson_green(ctx->cfg.nx, ctx->cfg.x_hi - ctx->cfg.x_lo, ctx->green, nullptr));
-        VL_HIP(hipStreamSynchronize(nullptr));
-    }
+    ctx->slots = slots;
+    ctx->green = green;
+    ctx->part = green + (size_t)ctx->cfg.nx;
     ctx->device = dev;
     return VL_OK;
 }
