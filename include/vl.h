@@ -105,7 +105,7 @@ typedef struct vl_ctx vl_ctx;
 
 /* Create a context for one problem geometry.  Host-only: validates and copies
  * *cfg; device scratch (64 KB, 12 bytes per species and block of the largest
- * launch, 8 nx, plus 160 bytes per spatial cell and species for the 3V moment
+ * launch, 16 nx, plus 160 bytes per spatial cell and species for the 3V moment
  * fitting on its first call) is allocated on first use on the
  * device current at that time and freed by vl_destroy.  Errors: VL_EINVAL (bad geometry, velocity
  * grid not symmetric in v_y for 2X3V), VL_ENOTSUP (unsupported combination, or a row of f --
@@ -169,7 +169,8 @@ vl_status vl_moment_fit_noalloc(vl_ctx* ctx, int32_t s, const void* f_in, void* 
 
 /* Fields.  1X1V: E[nx] at cell centres from Gauss's law with the uniform
  * neutralising background (Sec. 3.1), spectral, E_0 = 0.  The density is
- * taken from mom (species 0 moments, [nx][4]). */
+ * taken from mom (species 0 moments, [nx][4]).  E may lie in the memory of
+ * mom, which it then overwrites. */
 vl_status vl_poisson(vl_ctx* ctx, const double* mom, double* E, vl_stream stream);
 
 /* 2X3V Yee fields, FP64, concatenated: Ex[ny][nx] (i+1/2, j), Ey[ny+1][nx]

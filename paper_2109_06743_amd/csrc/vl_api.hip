@@ -27,8 +27,8 @@ struct vl_ctx {
     double t_ms[VL_T_COUNT] = {0};
     int64_t t_cnt[VL_T_COUNT] = {0};
     // device scratch: kSlots slots of kSlotMax maxima per species (slot_n: the
-    // entries each holds), then the Poisson table (1X1V), then the diagnostics
-    // partials
+    // entries each holds), then the Poisson table and room for one solve (nx
+    // doubles each), then the diagnostics partials
     unsigned long long* slots = nullptr;
     int slot_n[4][VL_MAX_SPECIES] = {{1, 1}, {1, 1}, {1, 1}, {1, 1}};
     double* green = nullptr;
@@ -140,7 +140,7 @@ vl_status ensure_device(vl_ctx* ctx) {
     // species the per-block maxima (8 bytes a block) and the clip counts (4
     // bytes), each followed by the stage of its two-level reduction
     const size_t slot_bytes = sizeof(unsigned long long) * kSlots * VL_MAX_SPECIES * vl::kSlotMax;
-    const size_t bytes = (slot_bytes + sizeof(double) * ((size_t)ctx->cfg.nx + kPartials) + 255) / 256 * 256;
+    const size_t bytes = (slot_bytes + sizeof(double) * (2 * (size_t)ctx->cfg.nx + kPartials) + 255) / 256 * 256;
     const size_t part_bytes = (8 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
     const size_t clip_bytes = (4 * (size_t)ctx->max_blocks + vl::kFinSlack + 255) / 256 * 256;
     void* p = nullptr;
@@ -163,7 +163,7 @@ vl_status ensure_device(vl_ctx* ctx) {
     }
     ctx->slots = slots;
     ctx->green = green;
-    ctx->part = green + (size_t)ctx->cfg.nx;
+    ctx->part = green + 2 * (size_t)ctx->cfg.nx;
     ctx->device = dev;
     return VL_OK;
 }
@@ -852,7 +852,14 @@ vl_status vl_poisson(vl_ctx* ctx, const double* mom, double* E, vl_stream stream
     if (!mom || !E) return fail(ctx, VL_EINVAL, "null argument");
     vl_status r;
     if ((r = ensure_device(ctx)) != VL_OK) return r;
-    VL_HIP(vl::launch_poisson(mom, ctx->cfg.nx, ctx->cfg.sp[0].q, ctx->green, E, (hipStream_t)stream));
+    // every block reads the densities of all cells: an E in the memory of mom is
+    // written once all have been read
+    const int nx = ctx->cfg.nx;
+    const bool shared = (uintptr_t)E < (uintptr_t)(mom + 4 * (size_t)nx) && (uintptr_t)mom < (uintptr_t)(E + nx);
+    double* out = shared ? ctx->green + nx : E;
+    VL_HIP(vl::launch_poisson(mom, nx, ctx->cfg.sp[0].q, ctx->green, out, (hipStream_t)stream));
+    if (shared)
+        VL_HIP(hipMemcpyAsync(E, out, sizeof(double) * (size_t)nx, hipMemcpyDeviceToDevice, (hipStream_t)stream));
     return VL_OK;
 }
 
