@@ -68,11 +68,13 @@ def test_kinetic(nx, ny, s, bc):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("closure", ["gradient", "mlp"])
-@pytest.mark.parametrize("nx,ny", [(15, 17), (43, 48)])
-def test_closures(nx, ny, closure):
+@pytest.mark.parametrize("closure,nx,ny", [("gradient", 15, 17), ("gradient", 43, 48), ("mlp", 1, 2), ("mlp", 15, 17),
+                                           ("mlp", 63, 3), ("mlp", 64, 4), ("mlp", 65, 5), ("mlp", 129, 9)])
+def test_closures(closure, nx, ny):
     """Both species of a fluid-model step; the stage fields and the network's
-    outputs are the library's own, the rest is formed on the host."""
+    outputs are the library's own (of the separate features and forward calls;
+    the step has both in one kernel of 64 x 4 tiles), the rest is formed on the
+    host.  The network adds 1e-5 of U and less, a billion times what would show."""
     import torch
     from paper_2109_06743_amd import vl
     ensure_lib()
@@ -111,6 +113,34 @@ def test_closures(nx, ny, closure):
         ref = FR.rk3_3v(U[s], third, fields, sp["q"], sp["m"], dx, dy, dt, "reflect",
                         FR.eq5_strength(sp["q"], sp["m"]) if closure == "gradient" else None)
         np.testing.assert_array_equal(host(fs.U[s], U[s].shape), ref, err_msg=f"species {s}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(1, 2), (63, 3), (64, 4), (65, 5), (129, 9)])
+def test_features_at_tile_edges(nx, ny):
+    """The features that test_closures takes as given, against the oracle's: FP64
+    values rounded to FP32 and BF16, so at most one BF16 step apart where a
+    rounding flips, differences of equal values aside."""
+    import torch
+    from oracle import mlp as OM
+    from paper_2109_06743_amd import vl
+    ensure_lib()
+    cfg, U, _ = W.gem_fluid(nx=nx, ny=ny)
+    rng = np.random.default_rng(nx * 100 + ny)
+    B = rng.normal(size=(ny, nx, 3))
+    ctx = vl.Context(cfg, "f64")
+    for s, sp in enumerate(cfg["species"]):
+        V = U[s] * (1 + 0.05 * rng.uniform(-1, 1, size=U[s].shape))
+        x = torch.zeros((ny * nx, 64), dtype=torch.int16, device="cuda")
+        sc = torch.zeros(ny * nx, dtype=torch.float64, device="cuda")
+        ctx.mlp_features(s, dev(V, "f64"), 10, x, sc, B=dev(B, "f64"))
+        ctx.sync()
+        rx, rs = OM.features_bf16(V, sp["m"], s, B)
+        rx = np.asarray(rx, dtype=np.float64).reshape(ny * nx, 64)
+        got = x.view(torch.bfloat16).double().cpu().numpy()
+        np.testing.assert_allclose(got, rx, rtol=2.0 ** -7, atol=1e-12)
+        assert (np.abs(got - rx) > 1e-12).mean() < 1e-3
+        np.testing.assert_allclose(host(sc), np.asarray(rs).reshape(-1), rtol=1e-13)
 
 
 @pytest.mark.gpu
