@@ -904,14 +904,4 @@ hipError_t launch_mlp_judge_set(const MlpSet& S, int ns, const double* scale, co
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_judge(const double* M, const double* scale, const float* y, long long cells, double m,
-                            double tol, double* part, int* fallback, double* err, hipStream_t st) {
-    MlpSet S{};
-    S.M[0] = M;
-    S.m[0] = m;
-    S.fallback[0] = fallback;
-    S.err[0] = err;
-    return launch_mlp_judge_set(S, 1, scale, y, cells, tol, part, st);
-}
-
 }  // namespace vl

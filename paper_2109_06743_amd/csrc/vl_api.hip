@@ -182,31 +182,43 @@ size_t yee_doubles(const vl_config& c) {
 
 size_t fluid_doubles(const vl_config& c) {
     if (c.dim_v == 3) return vl::fluid_rk3_3v_doubles(c.nx, c.ny);
-    return 9 * (size_t)c.nx;
+    return 3 * (size_t)c.nx;
 }
 
-// Learned-closure scratch of the step: network outputs (FP32 [cells][16] = 8
-// doubles per cell), scale (1), judge partials behind 45 doubles per cell.
-size_t mlp_step_doubles(const vl_config& c) {
-    if (c.closure != VL_CLOSURE_MLP) return 0;
-    const size_t cells = (size_t)c.nx * c.ny;
-    return (size_t)c.nspecies * (45 * cells + vl::mlp_judge_part_doubles()) + 2;   // every species at once
-}
+// Learned-closure scratch of every species: network outputs (FP32 [cells][16] =
+// 8 doubles per cell), scales (1), and one entry for the outputs' alignment.
+size_t network_doubles(const vl_config& c) { return (size_t)c.nspecies * 9 * c.nx * c.ny + 1; }
 
-// Fluid-only closure step: the step's field arrays (18 per cell), U1 and U2 of
-// two species (40), the network's outputs and scales of two species (18) and
-// the Yee fields between the half steps (6 and 3 per column), with some to
-// spare.
-size_t fluid_closure_doubles(const vl_config& c) {
-    const size_t cells = (size_t)c.nx * c.ny;
-    return 18 * cells + fluid_doubles(c) + 20 * cells + 6 * cells + 25 * cells + 2;
-}
+// Work of the steps in 2X3V: E and B at cell centres at t, t+1/2 and t+1 (18 per
+// cell), the Yee fields between the half steps, U1 and U2 of every species, the
+// network's scratch and (vl_step) its judge's partials.
+struct Work3V {
+    double *E_t, *B_t, *E_h, *B_h, *E_1, *B_1, *yee, *fluid, *network;
+    Work3V(const vl_config& c, double* work) {
+        const size_t cells = (size_t)c.nx * c.ny;
+        E_t = work;
+        B_t = E_t + 3 * cells;
+        E_h = B_t + 3 * cells;
+        B_h = E_h + 3 * cells;
+        E_1 = B_h + 3 * cells;
+        B_1 = E_1 + 3 * cells;
+        yee = B_1 + 3 * cells;
+        fluid = yee + yee_doubles(c);
+        network = fluid + c.nspecies * fluid_doubles(c);
+        network += ((uintptr_t)network & 15u) ? 1 : 0;     // its outputs are stored as 16-byte vectors
+    }
+    static size_t doubles(const vl_config& c) {            // without the network's
+        return 18 * (size_t)c.nx * c.ny + yee_doubles(c) + c.nspecies * fluid_doubles(c);
+    }
+};
+
+size_t fluid_closure_doubles(const vl_config& c) { return Work3V::doubles(c) + network_doubles(c); }
 
 size_t step_doubles(const vl_config& c) {
-    const size_t cells = (size_t)c.nx * c.ny;
-    // the fluid steps of all species run together (a fluid scratch each)
-    if (c.dim_v == 3) return 18 * cells + (size_t)c.nspecies * fluid_doubles(c) + mlp_step_doubles(c);
-    return 4 * (size_t)c.nx + 3 * (size_t)c.nx + fluid_doubles(c);
+    if (c.dim_v == 3)
+        return Work3V::doubles(c) + (c.closure == VL_CLOSURE_MLP
+                                         ? network_doubles(c) + c.nspecies * vl::mlp_judge_part_doubles() : 0);
+    return 4 * (size_t)c.nx + 3 * (size_t)c.nx;            // moments at t+1/2, the advanced fluid
 }
 
 // ------------------------------------------------------------ typed paths --
@@ -385,8 +397,8 @@ vl_status fluid_step_mlp_all(vl_ctx* ctx, const vl_state* S, const double* E_t, 
     const int ns = c.nspecies;
     const long long cells = ctx->cells;
     float* y = (float*)mwork;                           // 16-byte aligned (the caller aligns mwork)
-    double* scale = mwork + 24 * ns * cells;
-    double* part = mwork + 45 * ns * cells;
+    double* scale = mwork + 8 * ns * cells;
+    double* part = mwork + 9 * ns * cells;
     Timed tm(ctx, VL_T_FLUID, st);
     vl::MlpSet J{};
     for (int s = 0; s < ns; ++s) {
@@ -424,21 +436,12 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
     const int ns = c.nspecies;
     const long long cells = ctx->cells;
     const double q[2] = {c.sp[0].q, ns > 1 ? c.sp[1].q : 0.0};
-    double* E_t = S->work;
-    double* B_t = E_t + 3 * cells;
-    double* E_h = B_t + 3 * cells;
-    double* B_h = E_h + 3 * cells;
-    double* E_1 = B_h + 3 * cells;
-    double* B_1 = E_1 + 3 * cells;
-    // U1, U2 of both species, then the network's scratch of both
-    double* fwork = B_1 + 3 * cells;
-    double* mw = fwork + 40 * cells;
-    mw += ((uintptr_t)mw & 15u) ? 1 : 0;                 // network outputs are stored as 16-byte vectors
-    float* y = (float*)mw;
-    double* scale = mw + 8 * ns * cells;
+    const Work3V w(c, S->work);
+    double *const E_t = w.E_t, *const B_t = w.B_t, *const E_h = w.E_h, *const B_h = w.B_h, *const E_1 = w.E_1,
+           *const B_1 = w.B_1, *const fwork = w.fluid, *const yee1 = w.yee;
+    float* y = (float*)w.network;
+    double* scale = w.network + 8 * ns * cells;
     const double* Uc[2] = {S->U[0], ns > 1 ? S->U[1] : nullptr};
-    // the fields after the first half step wait behind the network's outputs
-    double* yee1 = mw + 9 * ns * cells;
     {
         Timed tm(ctx, VL_T_FIELDS, st);
         VL_HIP(vl::launch_yee_half(S->fields, yee1, c.nx, c.ny, Uc, q, ns, dt, c.c, dx_of(c), dy_of(c), 10, per_y(c),
@@ -452,7 +455,7 @@ vl_status fluid_closure_step_impl(vl_ctx* ctx, const vl_fluid_state* S, int clos
             vl::FluidSet G{};
             for (int s = 0; s < ns; ++s) {
                 const vl_species& sp = c.sp[s];
-                vl::rk3_buffers(G, s, k, S->U[s], fwork + (size_t)s * 20 * cells, cells);
+                vl::rk3_buffers(G, s, k, S->U[s], fwork + (size_t)s * fluid_doubles(c), cells);
                 G.m[s] = sp.m;
                 G.q[s] = sp.q;
                 // chi / k0 with chi = 2 sqrt(2/pi), k0 = 1/d_s, d_s = sqrt(m / q^2)
@@ -485,18 +488,9 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
 
     if (c.dim_x == 2) {
         const long long cells = ctx->cells;
-        double* E_t = S->work;
-        double* B_t = E_t + 3 * cells;
-        double* E_h = B_t + 3 * cells;
-        double* B_h = E_h + 3 * cells;
-        double* E_1 = B_h + 3 * cells;
-        double* B_1 = E_1 + 3 * cells;
-        double* fwork = B_1 + 3 * cells;
-        double* mwork = fwork + (size_t)ns * fluid_doubles(c);
-        mwork += ((uintptr_t)mwork & 15u) ? 1 : 0;         // network outputs are stored as 16-byte vectors
-        // the fields after the first half step wait in the part of the fluid
-        // scratch that its stages leave free
-        double* yee1 = fwork + vl::fluid_rk3_3v_used(c.nx, c.ny);
+        const Work3V w(c, S->work);
+        double *const E_t = w.E_t, *const B_t = w.B_t, *const E_h = w.E_h, *const B_h = w.B_h, *const E_1 = w.E_1,
+               *const B_1 = w.B_1, *const fwork = w.fluid, *const mwork = w.network, *const yee1 = w.yee;
         {
             Timed tm(ctx, VL_T_FIELDS, st);
             const double* mom_t[2] = {S->mom_post[0], ns > 1 ? S->mom_post[1] : nullptr};

@@ -182,10 +182,8 @@ struct FluidSet {
 // source of P (gchi = chi / k0); that of the network's heat flux.
 enum { kThirdFromF = 0, kThirdGradient = 1, kThirdNetwork = 2 };
 
-// Scratch of one species' SSP-RK3 step of the 3V fluid (doubles): U1, U2 (10
-// per cell each); the rest is the caller's to use meanwhile.
-inline size_t fluid_rk3_3v_doubles(int nx, int ny) { return 30 * (size_t)nx * ny + 10 * (size_t)nx * (ny + 1); }
-inline size_t fluid_rk3_3v_used(int nx, int ny) { return 20 * (size_t)nx * ny; }
+// Scratch of one species' SSP-RK3 step of the 3V fluid (doubles): U1, U2.
+inline size_t fluid_rk3_3v_doubles(int nx, int ny) { return 20 * (size_t)nx * ny; }
 
 // State buffers of stage k (0..2) of species s: U -> U1 -> U2 -> U.
 inline void rk3_buffers(FluidSet& S, int s, int k, double* U, double* work, long long cells) {
@@ -245,8 +243,6 @@ hipError_t launch_mlp_train_step(float* P, float* m1, float* m2, long long step,
                                  const unsigned short* x, const float* t, long long n, float* part, float* grad,
                                  hipStream_t st, const long long* idx = nullptr, long long nrows = 0);
 size_t mlp_judge_part_doubles();
-hipError_t launch_mlp_judge(const double* M, const double* scale, const float* y, long long cells, double m,
-                            double tol, double* part, int* fallback, double* err, hipStream_t st);
 
 template <class T>
 hipError_t launch_mass_energy(const T* f, const double* mom, long long cells, long long nv, int kmom, int dimv,
