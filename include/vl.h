@@ -357,7 +357,9 @@ vl_status vl_field_energy(vl_ctx* ctx, const double* fields, double* out, vl_str
  * stream, so timing few categories perturbs the step least.  vl_timing_read
  * waits for the recorded events, returns the summed milliseconds and
  * launch-group counts per category (arrays of VL_T_COUNT entries) since the
- * previous read, and clears them. */
+ * previous read, and clears them.  A step's fits are one group per species.
+ * In a 1X1V step the field solves run inside the velocity sweep and the fluid
+ * step and count there: VL_T_FIELDS is that of 2X3V. */
 enum { VL_T_MAX = 0, VL_T_PFC_X, VL_T_PFC_Y, VL_T_PFC_V, VL_T_MOMENTS, VL_T_FLUID, VL_T_FIT, VL_T_FIELDS,
        VL_T_COPY, VL_T_COUNT };
 #define VL_T_ALL ((uint32_t)((1u << VL_T_COUNT) - 1u))

@@ -303,7 +303,6 @@ vl_status fit_params(vl_ctx* ctx, int s0, int ns, const double* const* mom_pre, 
                      hipStream_t st) {
     const vl_config& c = ctx->cfg;
     if (c.dim_v == 1) return VL_OK;
-    Timed tm(ctx, VL_T_FIT, st);
     if (!ctx->fit_scratch) {
         void* p = nullptr;
         VL_HIP(hipMalloc(&p, sizeof(double) * vl::kFitCellDoubles * (size_t)ctx->cells * c.nspecies));
@@ -320,7 +319,6 @@ vl_status fit_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* mom
                     int64_t* counters, const vl::MaxSink& sink, hipStream_t st) {
     const vl_config& c = ctx->cfg;
     const vl_species& sp = c.sp[s];
-    Timed tm(ctx, VL_T_FIT, st);
     if (c.dim_v == 1)
         VL_HIP((vl::launch_fit1<T>(fin, fout, mom_pre, U, U, mom_post, counters, ctx->cells, sp.nv[0], sp.v_lo[0],
                                    dv_of(sp, 0), sp.m, sink, st)));
@@ -335,7 +333,6 @@ vl_status fit_typed(vl_ctx* ctx, int s, const T* fin, T* fout, const double* mom
 template <class T>
 vl_status fit_fold(vl_ctx* ctx, int s0, int ns, const vl::MaxSink* sinks, int64_t* counters, hipStream_t st) {
     if (ctx->cfg.dim_v == 1) return VL_OK;
-    Timed tm(ctx, VL_T_FIT, st);
     VL_HIP((vl::launch_fit_fold<T>(ns, sinks, ctx->bclip + s0, counters, ctx->cells, st)));
     return VL_OK;
 }
@@ -531,13 +528,16 @@ vl_status step_typed(vl_ctx* ctx, vl_state* S, double dt, hipStream_t st) {
                 VL_HIP(vl::launch_fluid_rk3_3v_set(ns, S->U, mt, mt1, E_t, B_t, E_1, B_1, E_h, B_h, dt, c.nx, c.ny, q,
                                                    ms, dx_of(c), dy_of(c), fwork, st, per_y(c)));
             }
-            if ((r = fit_params<T>(ctx, 0, ns, S->mom_pre, S->U, S->counters, st)) != VL_OK) return r;
-            for (int s = 0; s < ns; ++s)
-                if ((r = fit_typed<T>(ctx, s, (T*)S->f[s], (T*)S->f[s], S->mom_pre[s], S->U[s], S->mom_post[s],
-                                      S->counters, max_to(ctx, 0, s), st)) != VL_OK)
-                    return r;
             const vl::MaxSink sinks[2] = {max_to(ctx, 0, 0), ns > 1 ? max_to(ctx, 0, 1) : kNoMax};
-            if ((r = fit_fold<T>(ctx, 0, ns, sinks, S->counters, st)) != VL_OK) return r;
+            for (int s = 0; s < ns; ++s) {
+                // one group per species: the launches for all belong to the first and the last
+                Timed tm(ctx, VL_T_FIT, st);
+                if (s == 0 && (r = fit_params<T>(ctx, 0, ns, S->mom_pre, S->U, S->counters, st)) != VL_OK) return r;
+                if ((r = fit_typed<T>(ctx, s, (T*)S->f[s], (T*)S->f[s], S->mom_pre[s], S->U[s], S->mom_post[s],
+                                      S->counters, sinks[s], st)) != VL_OK)
+                    return r;
+                if (s == ns - 1 && (r = fit_fold<T>(ctx, 0, ns, sinks, S->counters, st)) != VL_OK) return r;
+            }
         }
         const double* mom_t1[2] = {S->mom_post[0], ns > 1 ? S->mom_post[1] : nullptr};
         Timed tm(ctx, VL_T_FIELDS, st);
@@ -809,6 +809,7 @@ vl_status vl_moment_fit(vl_ctx* ctx, int32_t s, const void* f_in, void* f_out, c
     if (!f_in || !f_out || !mom_pre || !U) return fail(ctx, VL_EINVAL, "null argument");
     if ((r = ensure_device(ctx)) != VL_OK) return r;
     hipStream_t st = (hipStream_t)stream;
+    Timed tm(ctx, VL_T_FIT, st);
     r = DISPATCH(ctx, fit_params<float>(ctx, s, 1, &mom_pre, &U, counters, st),
                  fit_params<double>(ctx, s, 1, &mom_pre, &U, counters, st));
     if (r != VL_OK) return r;
