@@ -110,9 +110,9 @@ __device__ __forceinline__ double row_next(double v) {
 // source first: 125 + 63 + 25 + 22 us a stage at 1024 x 512, one species; this
 // takes 71 (Eq. 5), and 11.4 us instead of 6.6 + 4.1 on 32 x 16 cells (both
 // species), with the same bits.  Estimated reciprocals in place of the quotients
-// and the two differences added to U one after the other took 65 and 10.9: the
-// bits of U changed, and with them, in one cell of a 1024 x 512 magnetotail step
-// in a few million, the FP32 distribution by 6e-8.
+// and the two differences added to U one after the other took 65 and 10.9, but
+// changed the bits of U, and in a magnetotail step about one cell in ten million
+// then got another FP32 distribution, by 6e-8.
 enum { kThirdKinetic = 0, kThirdZero = 1, kThirdNet = 2 };
 constexpr int kRows = 16, kCols = 14;
 constexpr int kHaloR = kRows + 4, kHaloC = kCols + 4;

@@ -180,9 +180,10 @@ __device__ __forceinline__ void buf_st(float v, __amdgpu_buffer_rsrc_t r, unsign
 
 // Maximum over the block of non-negative values, stored (as its bit pattern)
 // in part[blockIdx.x].  No atomics: many blocks folding into one address
-// serialise at the memory-side atomic unit, so a second launch
-// (launch_max_finalize) reduces the partials.  Every thread of the block must
-// call it (it synchronises).
+// serialise at the memory-side atomic unit.  Few partials are folded by the
+// kernel that needs the maximum (max_of), many by a launch of their own
+// (launch_max_finalize, launch_fit_fold).  Every thread of the block must call
+// it (it synchronises).
 template <class T>
 __device__ __forceinline__ void block_max_part(T v, typename Bits<T>::U* part) {
     __shared__ T red[16];

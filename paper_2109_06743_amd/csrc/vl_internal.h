@@ -77,9 +77,11 @@ hipError_t launch_pfc_v3b(const T* fin, T* fout, long long cells, const double* 
                           MaxRef finf, const MaxSink& sink, hipStream_t st);
 template <class T>
 hipError_t launch_array_max(const T* f, long long n, const MaxSink& sink, hipStream_t st);
-// Launchers that produce a maximum store per-block partials in `part` (8 bytes
-// per block of their grid) and reduce them into the slot in a second launch;
-// these give the grid sizes, to size `part`.
+// Launchers that produce a maximum leave it as their sink says: few per-block
+// maxima in the slot itself, for the consumer to fold; more in `part` (8 bytes
+// per block of their grid), which they fold into the slot in another launch --
+// but for launch_fit3, whose partials launch_fit_fold folds.  These give the
+// grid sizes, to size `part`.
 long long pfc_x_blocks(int rows, int nx, long long Nv);
 long long pfc_xy_blocks(int nx, int ny, int nvx, int nvy, int nvz);
 // Fused X(tau) of 2X3V (x then y sweep, one f_inf); fout must not alias fin.
@@ -133,7 +135,8 @@ hipError_t launch_fit3(const T* fin, T* fout, double* mom_post, void* counters, 
                        const MaxSink& sink, unsigned* clip_part, const double* params, hipStream_t st);
 // launch_fit3 leaves per-block maxima in the sink and per-cell clip counts in
 // clip_part; launch_fit_fold, after the fits of all ns species, folds them
-// into the sinks' slots and the counters.
+// into the sinks' slots and the counters.  Until then a slot is valid only
+// where its sink is direct for that many cells.
 template <class T>
 hipError_t launch_fit_fold(int ns, const MaxSink* sinks, unsigned* const* clips, void* counters, long long cells,
                            hipStream_t st);
