@@ -725,8 +725,8 @@ __device__ __forceinline__ void sweep_exact(T (&g)[N], T a, T c1, T c2, T finf) 
 // A pencil in shared memory that moves by K >= 1 cells (element k at
 // first + k step, downwind order), in place: cell p reads cells p - K - 2 ..
 // p - K + 1, held in registers as a window; the wall cell keeps all that
-// reaches it.  Code for each length, called: 60000 cells of 4^3 FP64 moving by
-// several cells 199 us with one loop for all lengths, four dependent reads a cell.
+// reaches it.  Code for each length up to 12, called: 60000 cells of 4^3 FP64
+// moving by several cells 141 us, 199 with the loop below.
 template <class T, int N>
 __device__ __attribute__((noinline)) void pencil_far(LdsPtr<T> blk, int first, int step, int K, T a, T c1, T c2,
                                                       T finf) {
@@ -758,6 +758,39 @@ __device__ __attribute__((noinline)) void pencil_far(LdsPtr<T> blk, int first, i
     blk[first + (N - 1) * step] = fmax(fma(X, a, top), T(0));
 }
 
+// The same for longer pencils (n > 12) by a loop from the far end: output p reads
+// cells up to p - K + 1, which outputs below p have not overwritten.  In a step
+// the corner velocities of a block alone move by a cell, and a wave with one
+// such pencil runs all of pencil_far beside the sub-cell code: steps of
+// 100x50x20x16x24 FP32 855 us with it, 844 with the loop, 90x60x28x18x15 995 and
+// 989.  Where most pencils move by cells (V alone, tau of hundreds of steps), the
+// loop is slower: 20x16x24 262 and 315, FP64 10^3 230 and 413.
+template <class T>
+__device__ __attribute__((noinline)) void pencil_loop(LdsPtr<T> blk, int first, int step, int n, int K, T a,
+                                                       T c1, T c2, T finf) {
+#pragma clang fp contract(off)
+    auto val = [&](int k) -> T { return k >= 0 ? blk[first + k * step] : T(0); };
+    auto factor = [&](int k) {
+        const T w = val(k);
+        return flux_factor(w, w - val(k - 1), val(k + 1) - w, c1, c2, finf);
+    };
+    T top = T(0);
+    for (int m = n - 1 - K > 0 ? n - 1 - K : 0; m < n; ++m) top += val(m);
+    T X = factor(n - 2 - K);
+    const T wall = fmax(fma(X, a, top), T(0));
+    T phi = X * a;                                    // leaving window position p = n - 2
+    for (int p = n - 2; p >= 0; --p) {
+        const T w = val(p - K);
+        X = factor(p - 1 - K);
+        const T below = X * a;
+        // the cells at and above p are read by no later output
+        const T o = fmax((w + below) - phi, T(0));
+        blk[first + p * step] = o;
+        phi = below;
+    }
+    blk[first + (n - 1) * step] = wall;
+}
+
 // One pencil of N cells: kIn from global memory (else from shared), kOut to
 // global memory (else back to shared).  Element m lives at first + m step in
 // shared and goff + m gstep in global memory, in the direction of motion.
@@ -785,7 +818,10 @@ __device__ __forceinline__ void pencil_exact(const T* __restrict__ src, T* __res
 #pragma unroll
             for (int m = 0; m < N; ++m) blk[first + m * step] = g[m];
         }
-        pencil_far<T, N>(lds_ptr(blk), first, step, K, sh.a, sh.c1, sh.c2, finf);
+        if constexpr (N <= 12)
+            pencil_far<T, N>(lds_ptr(blk), first, step, K, sh.a, sh.c1, sh.c2, finf);
+        else
+            pencil_loop<T>(lds_ptr(blk), first, step, N, K, sh.a, sh.c1, sh.c2, finf);
         if constexpr (kOut) {
 #pragma unroll
             for (int m = 0; m < N; ++m) g[m] = blk[first + m * step];
@@ -1428,8 +1464,9 @@ pfc_v3_planes_kernel(const T* fin, T* fout, const double* __restrict__ E, const 
 // that needs the maximum reads f next and gains more than this kernel loses.
 // X and its maximum, FP64 8^3 256x128 (134 MB) 103 us past and 94 through the
 // caches, FP32 10^3 200x100 (80 MB) 72 and 67, 12^3 at 224 MB 158 and 151;
-// beyond, V or X of 268 to 450 MB is 1 to 5 % slower through them.
-constexpr long long kLastLevelBytes = 224ll << 20;
+// beyond, V or X of 268 to 450 MB is 1 to 5 % slower through them, and
+// backsubstitution at 226 MB 194 against 190.
+constexpr long long kLastLevelBytes = 208ll << 20;
 template <class T, bool kPast>
 __global__ void __launch_bounds__(256)
 array_max_kernel(const T* __restrict__ f, long long n, typename Bits<T>::U* __restrict__ out) {
